@@ -11,6 +11,16 @@ constexpr int kHistWin = 512;    // LDS bucket window of one streaming tile
 constexpr int kWaveCap = 512;    // records one wave sorts and flattens on its own
 constexpr int kWaveBins = 512;   // sub-bins of the wave path's counting sort (at most)
 
+// One add call's chunk to copy into the record arena: `count` starts to dst_s, ends to dst_e.
+struct CopyChunk {
+  const int64_t* s;
+  const int64_t* e;
+  int64_t* dst_s;
+  int64_t* dst_e;
+  int64_t count;
+};
+hipError_t launch_gather(const CopyChunk* chunks, int n, hipStream_t st);  // host array, any n
+
 hipError_t launch_reset(const Plan& p, hipStream_t st);
 hipError_t launch_stats(const Plan& p, hipStream_t st);
 hipError_t launch_hist(const Plan& p, hipStream_t st);

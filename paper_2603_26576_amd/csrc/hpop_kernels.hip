@@ -17,6 +17,56 @@
 namespace hpop {
 
 // ----------------------------------------------------------------------------
+// gather: the chunks of one add call into the record arena
+// ----------------------------------------------------------------------------
+
+// Up to kGatherChunks chunks of a launch, in the kernel's arguments (no table
+// to upload): chunk i covers workgroups [first[i], first[i + 1]), each of
+// kGatherPiece records of both arrays. A few hundred copies of some ten
+// thousand bytes are bound by what enqueueing each costs the host (about 4 us
+// per copy, two copies per chunk); one launch per 80 chunks took the add and
+// build of 264 chunks (9e5 records) from 1049 to 232 us.
+constexpr int kGatherChunks = 80;
+constexpr int kGatherPiece = 4096;
+struct GatherArgs {
+  CopyChunk c[kGatherChunks];
+  unsigned int first[kGatherChunks + 1];
+  int n;
+};
+static_assert(sizeof(GatherArgs) <= 4000, "kernel arguments");
+
+// n words from src to dst (256 B aligned) by the workgroup: pairs of words
+// when src is 16 B aligned, with four loads in flight per thread.
+__device__ __forceinline__ void copy_words(const int64_t* src, int64_t* dst, int n) {
+  if ((((uintptr_t)src) & 15) == 0 && n == kGatherPiece) {
+    const longlong2* a = (const longlong2*)src;
+    longlong2* b = (longlong2*)dst;
+    for (int i = threadIdx.x; i < kGatherPiece / 2; i += 4 * 256) {
+      const longlong2 x0 = a[i], x1 = a[i + 256], x2 = a[i + 512], x3 = a[i + 768];
+      b[i] = x0;
+      b[i + 256] = x1;
+      b[i + 512] = x2;
+      b[i + 768] = x3;
+    }
+  } else {
+    for (int i = threadIdx.x; i < n; i += 256) dst[i] = src[i];
+  }
+}
+
+__global__ __launch_bounds__(256) void k_gather(GatherArgs g) {
+  int lo = 0, hi = g.n - 1;  // the last chunk whose first workgroup is at or before this one
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (g.first[mid] <= blockIdx.x) lo = mid; else hi = mid - 1;
+  }
+  const CopyChunk c = g.c[lo];
+  const long long at = (long long)(blockIdx.x - g.first[lo]) * kGatherPiece;
+  const int n = (int)min((long long)kGatherPiece, c.count - at);
+  copy_words(c.s + at, c.dst_s + at, n);
+  copy_words(c.e + at, c.dst_e + at, n);
+}
+
+// ----------------------------------------------------------------------------
 // reset: per-build counters to their identities
 // ----------------------------------------------------------------------------
 
@@ -1821,6 +1871,44 @@ __global__ __launch_bounds__(THREADS) void k_region_multi(const RegionDesc* regi
 // ----------------------------------------------------------------------------
 // launchers
 // ----------------------------------------------------------------------------
+
+hipError_t launch_gather(const CopyChunk* chunks, int n, hipStream_t st) {
+  // a launch holds fewer than 2^31 threads: a chunk past that (1.7e10 records) is cut
+  constexpr long long kMaxPieces = 1ll << 22;
+  GatherArgs g;
+  g.n = 0;
+  long long pieces = 0;
+  auto flush = [&]() -> hipError_t {
+    if (g.n == 0) return hipSuccess;
+    g.first[g.n] = (unsigned int)pieces;
+    hipLaunchKernelGGL(k_gather, dim3((unsigned)pieces), dim3(256), 0, st, g);
+    g.n = 0;
+    pieces = 0;
+    return hipGetLastError();
+  };
+  for (int i = 0; i < n; ++i) {
+    CopyChunk c = chunks[i];
+    while (c.count > 0) {
+      const long long room = (kMaxPieces - pieces) * (long long)kGatherPiece;
+      if (g.n == kGatherChunks || room <= 0) {
+        const hipError_t e = flush();
+        if (e != hipSuccess) return e;
+        continue;
+      }
+      CopyChunk part = c;
+      part.count = std::min<long long>(c.count, room);
+      g.first[g.n] = (unsigned int)pieces;
+      g.c[g.n++] = part;
+      pieces += (part.count + kGatherPiece - 1) / kGatherPiece;
+      c.s += part.count;
+      c.e += part.count;
+      c.dst_s += part.count;
+      c.dst_e += part.count;
+      c.count -= part.count;
+    }
+  }
+  return flush();
+}
 
 hipError_t launch_reset(const Plan& p, hipStream_t st) {
   const long long work = max(3 * p.n_buckets + p.n_segs, p.n_tiles) + 64;

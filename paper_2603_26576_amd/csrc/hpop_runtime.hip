@@ -879,6 +879,33 @@ hpop_status hpop_add_events(hpop_session* s, int32_t resource, int32_t kind, con
   return hpop_add_events_multi(s, &c, 1, mem_space);
 }
 
+// Whether the kernels of device `dev` may read [p, p + bytes): plain device
+// memory of that device, inside one allocation. The last allocation found is
+// kept for the rest of the call (the chunks of a call mostly share one).
+namespace {
+struct DeviceRange {
+  const char* base = nullptr;
+  size_t bytes = 0;
+  bool holds(const void* p, size_t n) const {
+    return base && (const char*)p >= base && n <= bytes && (size_t)((const char*)p - base) <= bytes - n;
+  }
+  bool find(const void* p, size_t n, int dev) {
+    if (holds(p, n)) return true;
+    hipPointerAttribute_t a;
+    hipDeviceptr_t b = nullptr;
+    size_t sz = 0;
+    if (hipPointerGetAttributes(&a, p) != hipSuccess || a.type != hipMemoryTypeDevice || a.device != dev ||
+        hipMemGetAddressRange(&b, &sz, (hipDeviceptr_t)p) != hipSuccess) {
+      (void)hipGetLastError();
+      return false;
+    }
+    base = (const char*)b;
+    bytes = sz;
+    return holds(p, n);
+  }
+};
+}  // namespace
+
 hpop_status hpop_add_events_multi(hpop_session* s, const hpop_event_chunk* chunks, int32_t n_chunks,
                                   int32_t mem_space) {
   HPOP_GUARD_BEGIN
@@ -941,13 +968,23 @@ hpop_status hpop_add_events_multi(hpop_session* s, const hpop_event_chunk* chunk
     if (e != hipSuccess) return fail(s, HPOP_E_HIP, std::string("hipMemcpyAsync: ") + hipGetErrorString(e));
     off += o;
   } else {
+    // chunks in this device's own memory go in one kernel per 80 chunks; any
+    // other kind of pointer (managed, another device's, not a device pointer)
+    // is left to the runtime's copy, which knows or refuses it
+    std::vector<CopyChunk> gather;
+    DeviceRange known;
     for (int32_t i = 0; i < n_chunks; ++i) {
       const hpop_event_chunk& c = chunks[i];
       if (c.count == 0) continue;
       const size_t b = size_t(c.count) * 8, bp = (b + 255) & ~size_t(255);
-      hipError_t e = hipMemcpyAsync(base + off, c.start, b, hipMemcpyDeviceToDevice, s->stream);
-      if (e == hipSuccess) e = hipMemcpyAsync(base + off + bp, c.end, b, hipMemcpyDeviceToDevice, s->stream);
-      if (e != hipSuccess) return fail(s, HPOP_E_HIP, std::string("hipMemcpyAsync: ") + hipGetErrorString(e));
+      if (((uintptr_t)c.start & 7) == 0 && ((uintptr_t)c.end & 7) == 0 && known.find(c.start, b, s->device) &&
+          known.find(c.end, b, s->device)) {
+        gather.push_back({c.start, c.end, (int64_t*)(base + off), (int64_t*)(base + off + bp), c.count});
+      } else {
+        hipError_t e = hipMemcpyAsync(base + off, c.start, b, hipMemcpyDeviceToDevice, s->stream);
+        if (e == hipSuccess) e = hipMemcpyAsync(base + off + bp, c.end, b, hipMemcpyDeviceToDevice, s->stream);
+        if (e != hipSuccess) return fail(s, HPOP_E_HIP, std::string("hipMemcpyAsync: ") + hipGetErrorString(e));
+      }
       RecChunk rc;
       rc.resource = c.resource;
       rc.kind = c.kind;
@@ -958,6 +995,8 @@ hpop_status hpop_add_events_multi(hpop_session* s, const hpop_event_chunk* chunk
       added.push_back(rc);
       off += 2 * bp;
     }
+    const hipError_t e = launch_gather(gather.data(), (int)gather.size(), s->stream);
+    if (e != hipSuccess) return fail(s, HPOP_E_HIP, std::string("k_gather: ") + hipGetErrorString(e));
   }
   s->arena_used = off;
   s->arena.used = off;
