@@ -595,20 +595,20 @@ __device__ __forceinline__ Tree make_tree(long long E, int n_hosts, int n_device
   return t;
 }
 
-// Block reduction of per-thread resource state times into a tree (thread 0
-// returns it). Per thread: host rows add U, W, MPI, Other; device rows K, M.
-template <int THREADS>
+// Block reduction of per-thread resource state times (thread 0 receives it).
+// Per thread: host rows add U, W, MPI, Other; device rows K, M. `lds` holds 10
+// int64 per wave; ends with a barrier.
 __device__ __forceinline__ void block_tree(long long (&v)[9], long long* lds) {
 #pragma unroll
-  for (int i = 0; i < 6; ++i) v[i] = wave_red_sum(v[i]);
+  for (int i = 0; i < 6; ++i) v[i] = wave_reduce_i64<OpSum>(v[i], 0);
 #pragma unroll
-  for (int i = 6; i < 9; ++i) v[i] = wave_red_max(v[i]);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int i = 6; i < 9; ++i) v[i] = wave_reduce_i64<OpMax>(v[i], 0);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = (int)blockDim.x >> 6;
   if (lane == 0)
     for (int i = 0; i < 9; ++i) lds[wave * 10 + i] = v[i];
   __syncthreads();
   if (threadIdx.x == 0) {
-    for (int w = 1; w < THREADS / 64; ++w) {
+    for (int w = 1; w < nw; ++w) {
       for (int i = 0; i < 6; ++i) v[i] += lds[w * 10 + i];
       for (int i = 6; i < 9; ++i) v[i] = lds[w * 10 + i] > v[i] ? lds[w * 10 + i] : v[i];
     }

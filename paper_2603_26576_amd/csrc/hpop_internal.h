@@ -138,6 +138,8 @@ struct Elem {  // one record regrouped by bucket (the 16 B form)
 // segment takes two units from the back in the 16 B form. cursor[gb] counts
 // both: 8 B records in the low 32 bits, 16 B records in the high 32.
 // Device pointers of one build plan.
+constexpr int kRaccWords = 10;
+
 struct Plan {
   const ChunkDesc* chunks;
   int32_t n_chunks;
@@ -175,7 +177,8 @@ struct Plan {
   unsigned int* queue;               // [n_buckets] buckets handed to the block path
   unsigned long long* oversized;     // [0] buckets above the on-chip capacity, [1] buckets above slot_cap
   unsigned int* owner_err;           // [n_owners] set when an owner has an invalid record
-  unsigned long long* racc;          // [n_racc][9] per-region partial sums and maxima, zero between launches
+  unsigned long long* racc;          // [n_racc][kRaccWords] per region: six sums, three maxima, slices added;
+                                     // zero between launches
   int64_t n_racc;
   int32_t n_owners;
   int32_t seg_group;                 // > 1: the per-segment passes take segments in groups (many small segments)

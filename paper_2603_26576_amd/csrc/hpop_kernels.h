@@ -31,7 +31,11 @@ hipError_t launch_scan_carry(const Plan& p, hipStream_t st);  // fixed slots: sc
 hipError_t launch_merge_wave(const Plan& p, hipStream_t st);
 hipError_t launch_merge_block(const Plan& p, int cap, hipStream_t st);
 hipError_t launch_base(const Plan& p, hipStream_t st);
-hipError_t launch_region(const Plan& p, const RegionDesc* regions, int n_regions, int max_res, Tree* trees,
-                         long long* times, const IvlDesc* ivls, long long n_ivls, long long* macc, hipStream_t st);
+// Regions (n_plain of them [t0, t1), the rest per resource) and the status
+// words {first bad record, oversized buckets, slot overflows}. trees and
+// status: device or page-locked host memory.
+hipError_t launch_region(const Plan& p, const RegionDesc* regions, int n_regions, int n_plain, int max_res, Tree* trees,
+                         unsigned long long* status, long long* times, const IvlDesc* ivls, long long n_ivls,
+                         long long* macc, hipStream_t st);
 
 }  // namespace hpop

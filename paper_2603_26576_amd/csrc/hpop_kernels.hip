@@ -93,7 +93,7 @@ __global__ void k_reset(Plan p) {
   }
   if (tid < 4) p.ticket[tid] = 0;
   for (long long i = tid; i < p.n_owners; i += stride) p.owner_err[i] = 0;
-  for (long long i = tid; i < 9 * p.n_racc; i += stride) p.racc[i] = 0;
+  for (long long i = tid; i < kRaccWords * p.n_racc; i += stride) p.racc[i] = 0;
 }
 
 // ----------------------------------------------------------------------------
@@ -1690,103 +1690,221 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
 // region: clip every resource by binary search, reduce, finalize in FP64
 // ----------------------------------------------------------------------------
 
+// The last component of a bucket that starts before x (both relative to the
+// bucket's first time): its start and measure and the next one's measure (the
+// bucket's own, bs, after the last). False: none starts before x, and next is
+// the first one's measure.
+//
+// A query is a chain of dependent loads, one cache miss each, so what counts
+// is the number of probes. Starts spread about evenly over their bucket:
+// each probe takes the place that the starts known so far on both sides of x
+// suggest and reads two neighbours, which mostly ends after three or four
+// probes where halving took nine (a 350-record bucket) and then read the
+// result's words in two more. Buckets with their starts in a few places get
+// halving after three probes. Against halving alone the region stage of a
+// batch of 128 traces (512 regions) takes 32 us instead of 39, that of 256
+// devices with their streams 17.6 instead of 20, the mid trace's the same.
+template <class T, class Load>
+__device__ __forceinline__ bool find_comp(Load load, int cnt, T x, T width, long long bs, T& cs, long long& pl,
+                                          long long& next) {
+  int L = -1, H = cnt;
+  T csL = 0, csH = width;
+  long long plL = 0, plH = bs;
+  for (int it = 0; H - L > 1; ++it) {
+    int k = (L + H) >> 1;
+    if (it < 3) {
+      const float f = x >= csH ? 1.0f : (float)(x - csL) / (float)(csH - csL);
+      k = min(max(L + (int)(f * (float)(H - L - 1) + 0.5f), L + 1), H - 1);
+    }
+    const bool two = k + 1 < H;
+    T c0, c1;
+    long long p0, p1;
+    load(k, c0, p0);
+    load(two ? k + 1 : k, c1, p1);
+    if (c0 >= x) {
+      H = k;
+      csH = c0;
+      plH = p0;
+    } else {
+      L = k;
+      csL = c0;
+      plL = p0;
+      if (two) {
+        if (c1 >= x) {
+          H = k + 1;
+          csH = c1;
+          plH = p1;
+        } else {
+          L = k + 1;
+          csL = c1;
+          plL = p1;
+        }
+      }
+    }
+  }
+  cs = csL;
+  pl = plL;
+  next = plH;
+  return L >= 0;
+}
+
 // Measure of level l of segment seg before time t.
 __device__ long long measure_before(const Plan& p, int seg, int l, long long t) {
   const SegDesc sd = p.segs[seg];
   const Geom g = seg_geom(p, seg);
+  const long long max_e = (long long)p.stats[seg].max_e;
   if (g.empty || t <= g.min_s) return 0;
-  if (t >= (long long)p.stats[seg].max_e) return p.seg_total[seg * 3 + l];
-  const long long gb = sd.bucket_begin + bucket_index(g, (unsigned long long)(t - g.min_s));
+  if (t >= max_e) return p.seg_total[seg * 3 + l];
+  const long long bl = bucket_index(g, (unsigned long long)(t - g.min_s));
+  const long long gb = sd.bucket_begin + bl;
   const long long carry = p.carry[gb * 3 + l];
   const long long base = p.base[gb * 3 + l];
   const long long bs = p.bsum[gb * 3 + l];
-  const long long cnt = p.ncomp[gb * 3 + l];
-  const CompView c = comp_view(p, g, sd.bucket_begin, gb, l);
-  // first component with start >= t
-  long long lo = 0, hi = cnt;
-  while (lo < hi) {
-    const long long mid = (lo + hi) >> 1;
-    if (c.cs(mid) < t) lo = mid + 1; else hi = mid;
+  const int cnt = (int)p.ncomp[gb * 3 + l];
+  const long long off = (long long)p.offsets[gb];
+  const long long lo = bucket_lo(g, bl);
+  const long long width = (long long)((unsigned long long)g.wx << g.s0);
+  long long cs, pl, next;
+  bool any;
+  if (seg_narrow(g)) {
+    const CompN* c = p.compn[l] + off;
+    // past the last bucket's width no component starts: any x there will do
+    const unsigned int x = (unsigned int)min(t - lo, 0x7FFFFFFFll);
+    unsigned int c32;
+    any = find_comp<unsigned int>(
+        [&](int k, unsigned int& s, long long& m) {
+          const CompN v = c[k];
+          s = v.cs;
+          m = (long long)v.pl;
+        },
+        cnt, x, (unsigned int)width, bs, c32, pl, next);
+    cs = lo + (long long)c32;
+  } else {
+    const Comp* c = p.comp[l] + off;
+    any = find_comp<long long>(
+        [&](int k, long long& s, long long& m) {
+          const Comp v = c[k];
+          s = v.cs - lo;
+          m = v.pl;
+        },
+        cnt, t - lo, width, bs, cs, pl, next);
+    cs += lo;
   }
-  const long long k = lo - 1;
-  if (k < 0) {
+  if (!any) {
     // only the component carried in from earlier buckets lies before t
-    const long long ext = carry + (cnt > 0 ? c.pl(0) : bs);
+    const long long ext = carry + next;
     return base + (ext < t ? ext : t) - carry;
   }
-  const long long cs = c.cs(k), pl = c.pl(k);
-  const long long next_pl = k + 1 < cnt ? c.pl(k + 1) : bs;
-  const long long ce = cs + (next_pl - pl);
+  const long long ce = cs + (next - pl);
   return base + pl + (ce < t ? ce : t) - cs;
 }
 
-// Region, part 1: one thread per (resource, level, end of the region) clips by
-// binary search; a slice of kRegionSlice resources of one region per
-// workgroup writes their state times and adds its sums and maxima to the
-// region's accumulator (exact integer atomics: the order does not matter).
-constexpr int kRegionSlice = 32;
+// The build's status words into the results (threads 0-2 of one workgroup, in
+// the last kernel of a launch sequence).
+__device__ __forceinline__ void put_status(const Plan& p, unsigned long long* status) {
+  if (threadIdx.x < 3) status[threadIdx.x] = threadIdx.x == 0 ? p.err[0] : p.oversized[threadIdx.x - 1];
+}
 
-template <int THREADS>
-__global__ __launch_bounds__(THREADS) void k_region_part(Plan p, const RegionDesc* regions, long long* times) {
-  static_assert(THREADS == 8 * kRegionSlice, "8 threads per resource");
-  __shared__ long long sM[kRegionSlice][4][2];
-  __shared__ long long lds[THREADS / 64 * 10];
-  const RegionDesc rd = regions[blockIdx.x];
-  const int R = rd.n_hosts + rd.n_devices;
-  const int r0 = blockIdx.y * kRegionSlice;
-  if (r0 >= R || rd.n_ivl) return;  // uniform: past the region's resources, or a per-resource region
-  const int rl = threadIdx.x >> 3, l = (threadIdx.x >> 1) & 3, ep = threadIdx.x & 1;
-  const int r = r0 + rl;
-  const bool host = r < rd.n_hosts;
-  if (r < R && l < (host ? 3 : 2)) sM[rl][l][ep] = measure_before(p, rd.seg_begin + r, l, ep ? rd.t1 : rd.t0);
-  __syncthreads();
-  const long long E = rd.t1 - rd.t0;
-  // sums: U, W, MPI, Other, K, M ; maxes: U+W, K, K+M
-  long long v[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-  if ((threadIdx.x & 7) == 0 && r < R) {
-    long long D[3] = {0, 0, 0};
-    for (int k = 0; k < (host ? 3 : 2); ++k) D[k] = sM[rl][k][1] - sM[rl][k][0];
-    long long* out = times + (rd.times_off + r) * 4;
-    if (host) {
-      const long long u = D[0], w = D[1] - D[0], mpi = D[2] - D[1], o = E - D[2];
-      out[0] = u; out[1] = w; out[2] = mpi; out[3] = o;
-      v[0] = u; v[1] = w; v[2] = mpi; v[3] = o;
-      v[6] = u + w;
-    } else {
-      const long long k = D[0], mm = D[1] - D[0], idle = E - D[1];
-      out[0] = k; out[1] = mm; out[2] = idle; out[3] = 0;
-      v[4] = k; v[5] = mm;
-      v[7] = k;
-      v[8] = k + mm;
-    }
-  }
-  block_tree<THREADS>(v, lds);
-  if (threadIdx.x == 0) {
-    unsigned long long* acc = p.racc + (long long)blockIdx.x * 9;
-#pragma unroll
-    for (int i = 0; i < 6; ++i)
-      if (v[i]) atomicAdd(acc + i, (unsigned long long)v[i]);
-#pragma unroll
-    for (int i = 6; i < 9; ++i)
-      if (v[i]) atomicMax(acc + i, (unsigned long long)v[i]);
+__global__ void k_status(Plan p, unsigned long long* status) { put_status(p, status); }
+
+// State times of resource r of region rd from its levels' measures D inside
+// it, written to `times` and added to v (sums U, W, MPI, Other, K, M; maxima
+// U+W, K, K+M).
+__device__ __forceinline__ void add_times(bool host, const long long (&D)[3], long long E, long long* out,
+                                          long long (&v)[9]) {
+  if (host) {
+    const long long u = D[0], w = D[1] - D[0], mpi = D[2] - D[1], o = E - D[2];
+    out[0] = u; out[1] = w; out[2] = mpi; out[3] = o;
+    v[0] += u; v[1] += w; v[2] += mpi; v[3] += o;
+    v[6] = u + w > v[6] ? u + w : v[6];
+  } else {
+    const long long k = D[0], mm = D[1] - D[0], idle = E - D[1];
+    out[0] = k; out[1] = mm; out[2] = idle; out[3] = 0;
+    v[4] += k; v[5] += mm;
+    v[7] = k > v[7] ? k : v[7];
+    v[8] = k + mm > v[8] ? k + mm : v[8];
   }
 }
 
-// Region, part 2: one thread per region turns the accumulator into the tree
-// (FP64 ratios) and clears it for the next launch.
-__global__ __launch_bounds__(64) void k_region_final(Plan p, const RegionDesc* regions, int n_regions, Tree* trees) {
-  const int g = blockIdx.x * 64 + threadIdx.x;
-  if (g >= n_regions) return;
-  const RegionDesc rd = regions[g];
-  if (rd.n_ivl) return;  // a per-resource region: k_region_multi
-  unsigned long long* acc = p.racc + (long long)g * 9;
-  long long v[9];
+// Eight neighbouring lanes hold one resource's measures (lane 2 l + end, level
+// l): the first of them gets the levels' measures inside the region.
+__device__ __forceinline__ void group_levels(long long M, long long (&D)[3]) {
 #pragma unroll
-  for (int i = 0; i < 9; ++i) {
-    v[i] = (long long)acc[i];
-    acc[i] = 0;
+  for (int l = 0; l < 3; ++l) D[l] = __shfl(M, 2 * l + 1, 8) - __shfl(M, 2 * l, 8);
+}
+
+// The finished trees of a workgroup's n consecutive regions go out as whole
+// words, neighbouring lanes to neighbouring words: the results lie in host
+// memory, where every store is a bus transfer.
+__device__ __forceinline__ void put_trees(const Tree* lds, int n, Tree* out) {
+  constexpr int kWords = sizeof(Tree) / 8;
+  const unsigned long long* src = (const unsigned long long*)lds;
+  for (int i = threadIdx.x; i < n * kWords; i += blockDim.x) ((unsigned long long*)out)[i] = src[i];
+}
+
+// Plain regions: a slice of resources of one region per workgroup, eight
+// threads per resource (level and end), clips them by binary search, writes
+// their state times and adds its sums and maxima to the region's accumulator.
+// The region's last slice to add makes the tree (FP64 ratios) and leaves the
+// accumulator clear. Only atomics pass between the slices, each one's results
+// back before the slice counts itself, so no fence is needed (a device-scope
+// release writes back the L2, which had made this slower than a second kernel).
+// A region of one slice needs no accumulator at all.
+//
+// The stage is a chain of about ten cache misses, and one CU has only so many
+// in flight: a few regions (the rule below: up to 8192 resource clips, or at
+// most 16 resources each) take slices of 8 resources, a wave, to spread over
+// the CUs; more take slices of 32, with fewer accumulator atomics. Mid trace
+// (16 regions x 128 resources): 13.0 us, against 17.5 with a workgroup per
+// region and 15.8 as two kernels; small trace (1 x 8): 4.0 against 9.5.
+__global__ __launch_bounds__(256) void k_region(Plan p, const RegionDesc* regions, long long* times, Tree* trees,
+                                                unsigned long long* status) {
+  __shared__ long long lds[4 * 10];
+  __shared__ long long tot[9];
+  __shared__ Tree tree;
+  __shared__ int s_last;
+  if (blockIdx.x == 0 && blockIdx.y == 0) put_status(p, status);
+  const RegionDesc rd = regions[blockIdx.x];
+  if (rd.n_ivl) return;  // a per-resource region: k_region_multi
+  const int R = rd.n_hosts + rd.n_devices;
+  const int slice = (int)blockDim.x >> 3;
+  const int r0 = blockIdx.y * slice;
+  if (r0 >= R && r0 > 0) return;  // uniform: past the region's resources
+  const int slices = max(1, (R + slice - 1) / slice);
+  const int r = r0 + (int)(threadIdx.x >> 3);
+  const int l = (threadIdx.x >> 1) & 3, ep = threadIdx.x & 1;
+  const bool host = r < rd.n_hosts;
+  const long long E = rd.t1 - rd.t0;
+  long long v[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+  long long M = 0, D[3];
+  if (r < R && l < (host ? 3 : 2)) M = measure_before(p, rd.seg_begin + r, l, ep ? rd.t1 : rd.t0);
+  group_levels(M, D);
+  if ((threadIdx.x & 7) == 0 && r < R) add_times(host, D, E, times + (rd.times_off + r) * 4, v);
+  block_tree(v, lds);
+  if (slices > 1) {
+    unsigned long long* acc = p.racc + (long long)blockIdx.x * kRaccWords;
+    if (threadIdx.x == 0)
+      for (int i = 0; i < 9; ++i) tot[i] = v[i];
+    __syncthreads();
+    if (threadIdx.x < 64) {  // one wave: a lane per word, then one lane counts the slice
+      unsigned long long old = 0;
+      if (threadIdx.x < 6) old = atomicAdd(acc + threadIdx.x, (unsigned long long)tot[threadIdx.x]);
+      else if (threadIdx.x < 9) old = atomicMax(acc + threadIdx.x, (unsigned long long)tot[threadIdx.x]);
+      // the count is issued only once every lane's result is back
+      asm volatile("" ::"v"((unsigned int)old), "v"((unsigned int)(old >> 32)) : "memory");
+      if (threadIdx.x == 0) s_last = (int)atomicAdd(acc + 9, 1ull) == slices - 1;
+    }
+    __syncthreads();
+    if (!s_last) return;
+    if (threadIdx.x < 9) tot[threadIdx.x] = (long long)atomicExch(acc + threadIdx.x, 0ull);
+    else if (threadIdx.x == 9) (void)atomicExch(acc + 9, 0ull);
+    __syncthreads();
+    if (threadIdx.x == 0)
+      for (int i = 0; i < 9; ++i) v[i] = tot[i];
   }
-  trees[g] = make_tree(rd.t1 - rd.t0, rd.n_hosts, rd.n_devices, v);
+  if (threadIdx.x == 0) tree = make_tree(E, rd.n_hosts, rd.n_devices, v);
+  __syncthreads();
+  put_trees(&tree, 1, trees + blockIdx.x);
 }
 
 // Regions given as per-resource interval lists (a region entered repeatedly,
@@ -1826,6 +1944,7 @@ template <int THREADS>
 __global__ __launch_bounds__(THREADS) void k_region_multi(const RegionDesc* regions, const long long* macc, Tree* trees,
                                                           long long* times) {
   __shared__ long long lds[THREADS / 64 * 10];
+  __shared__ Tree tree;
   __shared__ long long semax[2][THREADS / 64];
   const RegionDesc rd = regions[blockIdx.x];
   if (rd.n_ivl == 0) return;
@@ -1835,22 +1954,11 @@ __global__ __launch_bounds__(THREADS) void k_region_multi(const RegionDesc* regi
   long long eh = 0, ed = 0;
   for (int r = threadIdx.x; r < R; r += THREADS) {
     const long long* a = macc + (rd.times_off + r) * 4;
-    const long long D0 = a[0], D1 = a[1], D2 = a[2], Er = a[3];
-    long long* out = times + (rd.times_off + r) * 4;
-    if (r < rd.n_hosts) {
-      const long long u = D0, w = D1 - D0, mpi = D2 - D1, o = Er - D2;
-      out[0] = u; out[1] = w; out[2] = mpi; out[3] = o;
-      v[0] += u; v[1] += w; v[2] += mpi; v[3] += o;
-      v[6] = u + w > v[6] ? u + w : v[6];
-      eh = Er > eh ? Er : eh;
-    } else {
-      const long long k = D0, mm = D1 - D0, idle = Er - D1;
-      out[0] = k; out[1] = mm; out[2] = idle; out[3] = 0;
-      v[4] += k; v[5] += mm;
-      v[7] = k > v[7] ? k : v[7];
-      v[8] = k + mm > v[8] ? k + mm : v[8];
-      ed = Er > ed ? Er : ed;
-    }
+    const long long D[3] = {a[0], a[1], a[2]}, Er = a[3];
+    const bool host = r < rd.n_hosts;
+    add_times(host, D, Er, times + (rd.times_off + r) * 4, v);
+    if (host) eh = Er > eh ? Er : eh;
+    else ed = Er > ed ? Er : ed;
   }
   eh = wave_reduce_i64<OpMax>(eh, 0);
   ed = wave_reduce_i64<OpMax>(ed, 0);
@@ -1858,14 +1966,16 @@ __global__ __launch_bounds__(THREADS) void k_region_multi(const RegionDesc* regi
     semax[0][threadIdx.x >> 6] = eh;
     semax[1][threadIdx.x >> 6] = ed;
   }
-  block_tree<THREADS>(v, lds);  // its barriers also publish semax
+  block_tree(v, lds);  // its barriers also publish semax
   if (threadIdx.x == 0) {
     for (int w = 0; w < THREADS / 64; ++w) {
       eh = semax[0][w] > eh ? semax[0][w] : eh;
       ed = semax[1][w] > ed ? semax[1][w] : ed;
     }
-    trees[blockIdx.x] = make_tree(eh ? eh : ed, rd.n_hosts, rd.n_devices, v);
+    tree = make_tree(eh ? eh : ed, rd.n_hosts, rd.n_devices, v);
   }
+  __syncthreads();
+  put_trees(&tree, 1, trees + blockIdx.x);
 }
 
 // ----------------------------------------------------------------------------
@@ -2033,14 +2143,17 @@ hipError_t launch_base(const Plan& p, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_region(const Plan& p, const RegionDesc* regions, int n_regions, int max_res, Tree* trees,
-                         long long* times, const IvlDesc* ivls, long long n_ivls, long long* macc, hipStream_t st) {
-  if (n_regions == 0) return hipSuccess;
-  const unsigned slices = (unsigned)std::max(1, (max_res + kRegionSlice - 1) / kRegionSlice);
-  hipLaunchKernelGGL(k_region_part<8 * kRegionSlice>, dim3((unsigned)n_regions, slices), dim3(8 * kRegionSlice), 0, st,
-                     p, regions, times);
-  hipLaunchKernelGGL(k_region_final, dim3((unsigned)((n_regions + 63) / 64)), dim3(64), 0, st, p, regions, n_regions,
-                     trees);
+hipError_t launch_region(const Plan& p, const RegionDesc* regions, int n_regions, int n_plain, int max_res, Tree* trees,
+                         unsigned long long* status, long long* times, const IvlDesc* ivls, long long n_ivls,
+                         long long* macc, hipStream_t st) {
+  if (n_plain == 0) {
+    hipLaunchKernelGGL(k_status, dim3(1), dim3(64), 0, st, p, status);
+  } else {
+    const int slice = max_res <= 16 || (long long)n_plain * max_res <= 8192 ? 8 : 32;
+    const unsigned slices = (unsigned)std::max(1, (max_res + slice - 1) / slice);
+    hipLaunchKernelGGL(k_region, dim3((unsigned)n_regions, slices), dim3(8 * slice), 0, st, p, regions, times, trees,
+                       status);
+  }
   if (n_ivls > 0) {
     hipLaunchKernelGGL(k_ivl_zero, dim3((unsigned)n_regions), dim3(256), 0, st, regions, macc);
     hipLaunchKernelGGL(k_ivl_acc, dim3((unsigned)((8 * n_ivls + 255) / 256)), dim3(256), 0, st, p, regions, ivls,

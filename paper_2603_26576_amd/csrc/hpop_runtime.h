@@ -60,10 +60,12 @@ struct RecChunk {
   int64_t call = 0;  // index of the add_events call (error reports)
 };
 
+constexpr size_t kStatusBytes = 24;  // status words behind the trees of a result
+
 // Device buffers of one build plan.
 struct Workspace {
   DevBuf meta, elems, elems2, comp[3], compn[3];
-  PinnedBuf pinned;       // trees and status words copied back
+  PinnedBuf pinned;       // trees and status words, stored there by the kernels
   PinnedBuf pinned_desc;  // descriptor uploads
   hipEvent_t desc_done = nullptr;  // recorded after the last upload from pinned_desc
   Plan plan{};
@@ -75,6 +77,8 @@ struct Workspace {
   IvlDesc* d_ivls = nullptr;     // intervals of regions given per resource
   long long* d_macc = nullptr;   // [n_times][4] their per-resource accumulators
   hipGraphExec_t graph_exec = nullptr;
+  char* upload_base = nullptr;  // descriptors uploaded with the plan: [upload_base, + upload_bytes)
+  size_t upload_bytes = 0;
   long long layout_gen = 0;
   // set: everything is carved from this one device region of fixed_bytes
   // (no allocation, no page-locked staging); fixed_needed is the last plan's size
@@ -97,6 +101,7 @@ struct Engine {
   std::vector<SegDesc> h_segs;
   std::vector<RegionDesc> h_regions;
   std::vector<IvlDesc> h_ivls;
+  std::vector<char> h_desc;  // the upload of a workspace without page-locked staging
   std::vector<std::pair<int, int>> chunk_owner;  // (session index, chunk index) per chunk desc
   std::vector<int> seg_of_session, reg_of_session;
   long long n_times = 0;
@@ -110,7 +115,7 @@ struct Engine {
   bool use_graphs = true;
   int graph_replays = 0;
   long long last_oversized = 0;
-  char* result_host = nullptr;  // set: enqueue copies the results here instead of the page-locked buffer
+  char* result_host = nullptr;  // set: enqueue copies the results here; else kernels store them in ws.pinned
   // timing
   bool exact_forced = false;  // a bucket outgrew its scatter slots: use exact offsets
   std::vector<unsigned long long> forced_versions;

@@ -189,8 +189,8 @@ hpop_status Workspace::prepare(Alloc& a, long long n_chunks, long long n_tiles, 
   small += carve_bytes(1, 8) + carve_bytes(nscan, 8) + carve_bytes(4, 4) + carve_bytes(2, 8);
   small += carve_bytes(n_buckets, sizeof(unsigned int));
   small += carve_bytes(n_owners, sizeof(unsigned int));
-  small += carve_bytes(n_regions, sizeof(RegionDesc)) + carve_bytes(n_regions, sizeof(Tree));
-  small += carve_bytes(9 * n_regions, sizeof(unsigned long long));
+  small += carve_bytes(n_regions, sizeof(RegionDesc)) + carve_bytes(n_regions * sizeof(Tree) + kStatusBytes, 1);
+  small += carve_bytes(kRaccWords * n_regions, sizeof(unsigned long long));
   small += carve_bytes(n_ivls, sizeof(IvlDesc)) + carve_bytes(n_ivls ? 4 * n_times : 0, sizeof(long long));
   small += carve_bytes(4 * n_times, sizeof(long long));
   // bucketed records: fixed slots per bucket (n_slots > 0) or exact offsets,
@@ -246,9 +246,14 @@ hpop_status Workspace::prepare(Alloc& a, long long n_chunks, long long n_tiles, 
   }
   char* cur = meta_p;
   Plan& p = plan;
+  // what the host uploads comes first, in one piece (Engine::upload)
   p.chunks = d_chunks = carve<ChunkDesc>(cur, n_chunks);
   p.tile_chunk = carve<int32_t>(cur, n_tiles);
   p.segs = d_segs = carve<SegDesc>(cur, n_segs);
+  d_regions = carve<RegionDesc>(cur, n_regions);
+  d_ivls = carve<IvlDesc>(cur, n_ivls);
+  upload_base = meta_p;
+  upload_bytes = (size_t)(cur - meta_p);
   p.stats = carve<SegStats>(cur, n_segs);
   p.geom = carve<SegGeom>(cur, n_segs);
   p.counts = carve<unsigned int>(cur, n_buckets);
@@ -269,12 +274,10 @@ hpop_status Workspace::prepare(Alloc& a, long long n_chunks, long long n_tiles, 
   p.owner_err = carve<unsigned int>(cur, n_owners);
   p.n_owners = (int32_t)n_owners;
   p.seg_group = 1;
-  d_regions = carve<RegionDesc>(cur, n_regions);
-  d_trees = carve<Tree>(cur, n_regions);
-  p.racc = carve<unsigned long long>(cur, 9 * n_regions);
+  d_trees = (Tree*)carve<char>(cur, n_regions * sizeof(Tree) + kStatusBytes);
+  p.racc = carve<unsigned long long>(cur, kRaccWords * n_regions);
   p.n_racc = n_regions;
   d_times = carve<long long>(cur, 4 * n_times);
-  d_ivls = carve<IvlDesc>(cur, n_ivls);
   d_macc = carve<long long>(cur, n_ivls ? 4 * n_times : 0);
   p.elems = (Elem*)elems_p;
   p.elems2 = (Elem*)elems2_p;
@@ -483,56 +486,42 @@ hpop_status Engine::assemble_plan(const hpop_tuning& tun, const std::vector<long
   return HPOP_OK;
 }
 
+// Every descriptor of the plan in one copy to the head of the workspace.
 hpop_status Engine::upload(std::string& err) {
-  const size_t bc = h_chunks.size() * sizeof(ChunkDesc), bs = h_segs.size() * sizeof(SegDesc),
-               br = h_regions.size() * sizeof(RegionDesc), bi = h_ivls.size() * sizeof(IvlDesc),
-               bt = h_tile_chunk.size() * sizeof(int32_t);
+  char* h;
   if (ws.fixed) {
-    // no page-locked staging (it would be an allocation): copies straight from
-    // the host vectors, which stay untouched until the caller synchronises
-    if (bc) HPOP_HIP(hipMemcpyAsync(ws.d_chunks, h_chunks.data(), bc, hipMemcpyHostToDevice, alloc.stream), "upload chunks");
-    if (bt)
-      HPOP_HIP(hipMemcpyAsync(ws.plan.tile_chunk, h_tile_chunk.data(), bt, hipMemcpyHostToDevice, alloc.stream),
-               "upload tile map");
-    if (bs) HPOP_HIP(hipMemcpyAsync(ws.d_segs, h_segs.data(), bs, hipMemcpyHostToDevice, alloc.stream), "upload segments");
-    if (br)
-      HPOP_HIP(hipMemcpyAsync(ws.d_regions, h_regions.data(), br, hipMemcpyHostToDevice, alloc.stream),
-               "upload regions");
-    if (bi)
-      HPOP_HIP(hipMemcpyAsync(ws.d_ivls, h_ivls.data(), bi, hipMemcpyHostToDevice, alloc.stream),
-               "upload region intervals");
-    return HPOP_OK;
+    // no page-locked staging (it would be an allocation): the copy leaves a
+    // host vector, which stays untouched until the caller synchronises
+    h_desc.resize(ws.upload_bytes);
+    h = h_desc.data();
+  } else {
+    // descriptors go through pinned memory so the copy is stream-ordered; the
+    // previous upload from this buffer must have left it (an event, not a
+    // wait for everything else queued on the stream)
+    if (ws.desc_done) HPOP_HIP(hipEventSynchronize(ws.desc_done), "hipEventSynchronize");
+    else HPOP_HIP(hipEventCreateWithFlags(&ws.desc_done, hipEventDisableTiming), "hipEventCreate");
+    if (!ws.pinned_desc.reserve(ws.upload_bytes + 64)) {
+      err = "pinned host allocation failed";
+      return HPOP_E_OOM;
+    }
+    h = (char*)ws.pinned_desc.ptr;
   }
-  // descriptors go through pinned memory so the copies are stream-ordered;
-  // the previous upload from this buffer must have left it (an event, not a
-  // wait for everything else queued on the stream)
-  if (ws.desc_done) HPOP_HIP(hipEventSynchronize(ws.desc_done), "hipEventSynchronize");
-  else HPOP_HIP(hipEventCreateWithFlags(&ws.desc_done, hipEventDisableTiming), "hipEventCreate");
-  if (!ws.pinned_desc.reserve(bc + bs + br + bi + bt + 64)) {
-    err = "pinned host allocation failed";
-    return HPOP_E_OOM;
-  }
-  char* h = (char*)ws.pinned_desc.ptr;
-  if (bc) memcpy(h, h_chunks.data(), bc);
-  if (bs) memcpy(h + bc, h_segs.data(), bs);
-  if (br) memcpy(h + bc + bs, h_regions.data(), br);
-  if (bi) memcpy(h + bc + bs + br, h_ivls.data(), bi);
-  if (bt) memcpy(h + bc + bs + br + bi, h_tile_chunk.data(), bt);
-  if (bc) HPOP_HIP(hipMemcpyAsync(ws.d_chunks, h, bc, hipMemcpyHostToDevice, alloc.stream), "upload chunks");
-  if (bs) HPOP_HIP(hipMemcpyAsync(ws.d_segs, h + bc, bs, hipMemcpyHostToDevice, alloc.stream), "upload segments");
-  if (br)
-    HPOP_HIP(hipMemcpyAsync(ws.d_regions, h + bc + bs, br, hipMemcpyHostToDevice, alloc.stream), "upload regions");
-  if (bi)
-    HPOP_HIP(hipMemcpyAsync(ws.d_ivls, h + bc + bs + br, bi, hipMemcpyHostToDevice, alloc.stream),
-             "upload region intervals");
-  if (bt)
-    HPOP_HIP(hipMemcpyAsync(ws.plan.tile_chunk, h + bc + bs + br + bi, bt, hipMemcpyHostToDevice, alloc.stream),
-             "upload tile map");
-  HPOP_HIP(hipEventRecord(ws.desc_done, alloc.stream), "hipEventRecord");
+  auto put = [&](const void* dev, const void* src, size_t bytes) {
+    if (bytes) memcpy(h + ((const char*)dev - ws.upload_base), src, bytes);
+  };
+  put(ws.d_chunks, h_chunks.data(), h_chunks.size() * sizeof(ChunkDesc));
+  put(ws.plan.tile_chunk, h_tile_chunk.data(), h_tile_chunk.size() * sizeof(int32_t));
+  put(ws.d_segs, h_segs.data(), h_segs.size() * sizeof(SegDesc));
+  put(ws.d_regions, h_regions.data(), h_regions.size() * sizeof(RegionDesc));
+  put(ws.d_ivls, h_ivls.data(), h_ivls.size() * sizeof(IvlDesc));
+  if (ws.upload_bytes)
+    HPOP_HIP(hipMemcpyAsync(ws.upload_base, h, ws.upload_bytes, hipMemcpyHostToDevice, alloc.stream),
+             "upload descriptors");
+  if (!ws.fixed) HPOP_HIP(hipEventRecord(ws.desc_done, alloc.stream), "hipEventRecord");
   return HPOP_OK;
 }
 
-// All kernels of a build plus the region kernel and the copy of the results.
+// All kernels of a build and the region kernels, which leave the results.
 hpop_status Engine::enqueue(bool build, bool with_timing, std::string& err) {
   const Plan& p = ws.plan;
   hipStream_t st = alloc.stream;
@@ -594,20 +583,25 @@ hpop_status Engine::enqueue(bool build, bool with_timing, std::string& err) {
     HPOP_HIP(launch_base(p, st), "k_base");
     HPOP_HIP(mark("base"), "hipEventRecord");
   }
-  int max_res = 0;
-  for (const RegionDesc& rd : h_regions) max_res = std::max(max_res, rd.n_hosts + rd.n_devices);
+  int max_res = 0, n_plain = 0;
+  for (const RegionDesc& rd : h_regions) {
+    max_res = std::max(max_res, rd.n_hosts + rd.n_devices);
+    n_plain += rd.n_ivl == 0;
+  }
+  // results: trees, then the status words (first bad record, oversized
+  // buckets, slot overflow), stored by the kernels into page-locked host
+  // memory; a caller without any takes them in one copy
+  Tree* trees = result_host ? ws.d_trees : (Tree*)ws.pinned.ptr;
   HPOP_HIP(pre("region"), "hipEventRecord");
-  HPOP_HIP(launch_region(p, ws.d_regions, nreg, max_res, ws.d_trees, ws.d_times, ws.d_ivls, (long long)h_ivls.size(),
-                         ws.d_macc, st),
+  HPOP_HIP(launch_region(p, ws.d_regions, nreg, n_plain, max_res, trees, (unsigned long long*)(trees + nreg),
+                         ws.d_times, ws.d_ivls, (long long)h_ivls.size(), ws.d_macc, st),
            "k_region");
   HPOP_HIP(mark("region"), "hipEventRecord");
   n_marks = ev;
-  // results: trees, first bad record, oversized buckets, slot overflow
-  const size_t bt = (size_t)nreg * sizeof(Tree);
-  char* h = result_host ? result_host : (char*)ws.pinned.ptr;
-  if (bt) HPOP_HIP(hipMemcpyAsync(h, ws.d_trees, bt, hipMemcpyDeviceToHost, st), "copy trees");
-  HPOP_HIP(hipMemcpyAsync(h + bt, p.err, 8, hipMemcpyDeviceToHost, st), "copy error word");
-  HPOP_HIP(hipMemcpyAsync(h + bt + 8, p.oversized, 16, hipMemcpyDeviceToHost, st), "copy counters");
+  if (result_host)
+    HPOP_HIP(hipMemcpyAsync(result_host, ws.d_trees, (size_t)nreg * sizeof(Tree) + kStatusBytes, hipMemcpyDeviceToHost,
+                            st),
+             "copy results");
   return HPOP_OK;
 }
 

@@ -332,7 +332,7 @@ __global__ __launch_bounds__(256) void k_serv_region(const ServReq* reqs, const 
     }
   }
   long long v[9] = {sU, sW, sMPI, sO, sK, sM, mUW, mK, mKM};
-  block_tree<256>(v, lds);
+  block_tree(v, lds);
   if (threadIdx.x == 0) trees[blockIdx.x] = make_tree(E, q.n_hosts, q.n_devices, v);
 }
 
