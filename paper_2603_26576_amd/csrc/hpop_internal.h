@@ -47,8 +47,21 @@ struct ChunkDesc {
   int32_t chunk_id;    // index in the chunk table (error reports)
   int32_t owner;       // session (or serving query) the records belong to
   int32_t tile_pos;    // -1: the chunk has tiles of its own; else its place among a shared tile's chunks
-  int32_t tile_off;    // in a shared tile: the tile's record index of the chunk's first record
+  int32_t tile_off;    // in a shared tile: the tile's record index of the chunk's first record;
+                       // in a plan of small segments: the segment's record index of it
 };
+
+// One segment of a plan whose segments are all small (k_build_small): its
+// chunks are consecutive in the chunk table, elem0 records come before them.
+struct SmallSeg {
+  int64_t elem0;
+  int32_t chunk0, n_chunks;
+  int32_t count;  // records
+  int32_t pad;
+};
+constexpr int kSmallChunks = 128;    // chunks of such a segment at most
+constexpr int kSmallRecords = 4096;  // records
+constexpr int kSmallBuckets = 64;    // buckets
 
 // Chunks smaller than half a tile share tiles: consecutive ones (in the
 // chunk table) fill a tile with at most this many chunks and tile_elems records.
@@ -153,6 +166,7 @@ struct Plan {
   int32_t slot_cap;                  // >0: single-pass scatter into fixed slots of this many records per bucket
   int32_t pad1;
   const SegDesc* segs;
+  const SmallSeg* sseg;              // [n_segs] when every segment is small, else null
   SegStats* stats;
   SegGeom* geom;                     // [n_segs] bucket geometry (filled by the geometry kernel)
   int64_t n_buckets;

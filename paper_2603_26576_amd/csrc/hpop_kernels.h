@@ -21,6 +21,7 @@ struct CopyChunk {
 };
 hipError_t launch_gather(const CopyChunk* chunks, int n, hipStream_t st);  // host array, any n
 
+hipError_t launch_build_small(const Plan& p, hipStream_t st);  // a plan with p.sseg: the whole build
 hipError_t launch_reset(const Plan& p, hipStream_t st);
 hipError_t launch_stats(const Plan& p, hipStream_t st);
 hipError_t launch_hist(const Plan& p, hipStream_t st);
@@ -33,9 +34,10 @@ hipError_t launch_merge_block(const Plan& p, int cap, hipStream_t st);
 hipError_t launch_base(const Plan& p, hipStream_t st);
 // Regions (n_plain of them [t0, t1), the rest per resource) and the status
 // words {first bad record, oversized buckets, slot overflows}. trees and
-// status: device or page-locked host memory.
+// status: device or page-locked host memory. reset: the build's own status
+// words go back to their identities once they are stored.
 hipError_t launch_region(const Plan& p, const RegionDesc* regions, int n_regions, int n_plain, int max_res, Tree* trees,
-                         unsigned long long* status, long long* times, const IvlDesc* ivls, long long n_ivls,
-                         long long* macc, hipStream_t st);
+                         unsigned long long* status, bool reset, long long* times, const IvlDesc* ivls,
+                         long long n_ivls, long long* macc, hipStream_t st);
 
 }  // namespace hpop

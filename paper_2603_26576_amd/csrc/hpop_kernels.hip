@@ -1607,6 +1607,23 @@ __device__ __forceinline__ bool wave_bucket(const Plan& p, WaveSmem& W, long lon
   return true;
 }
 
+// One bucket of ni records (1 <= ni <= kWaveCap, all in the 8 B form) by one
+// wave, with as many records per lane as it needs: every slot costs the same
+// instructions, filled or not. False: the bucket must take the block path.
+template <bool kSlots>
+__device__ __forceinline__ bool wave_merge(const Plan& p, WaveSmem& W, long long gb, long long off, int ni,
+                                           const uint2* rec, const uint2 (&pre)[kWavePre], long long lo, int nlev,
+                                           const long long (&carry)[3], const long long (&maxe)[3]) {
+  if (ni <= 64) return wave_bucket<1, kSlots>(p, W, gb, off, ni, rec, pre, lo, nlev, carry, maxe);
+  if (ni <= 128) return wave_bucket<2, kSlots>(p, W, gb, off, ni, rec, pre, lo, nlev, carry, maxe);
+  if (ni <= 192) return wave_bucket<3, kSlots>(p, W, gb, off, ni, rec, pre, lo, nlev, carry, maxe);
+  if (ni <= 256) return wave_bucket<4, kSlots>(p, W, gb, off, ni, rec, pre, lo, nlev, carry, maxe);
+  if (ni <= 320) return wave_bucket<5, kSlots>(p, W, gb, off, ni, rec, pre, lo, nlev, carry, maxe);
+  if (ni <= 384) return wave_bucket<6, kSlots>(p, W, gb, off, ni, rec, pre, lo, nlev, carry, maxe);
+  if (ni <= 448) return wave_bucket<7, kSlots>(p, W, gb, off, ni, rec, pre, lo, nlev, carry, maxe);
+  return wave_bucket<8, kSlots>(p, W, gb, off, ni, rec, pre, lo, nlev, carry, maxe);
+}
+
 // One wave per bucket, 8 waves per SIMD (64 VGPRs). Buckets that need the
 // block path go to its queue. kSlots: fixed slots of at least 128 records
 // (2 slot_cap record places per bucket, whatever its count).
@@ -1666,24 +1683,286 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
     return;
   }
   bool done = false;
-  if (br.n16 == 0 && n <= kWaveCap) {
-    // only 8 B records (so the segment is narrow: buckets at most 2^30 ns wide)
-    const int ni = (int)n;
-    const uint2* rec = br.narrow;
-    const long long lo = bucket_lo(g, gb - sd.bucket_begin);
-    const int nlev = sd.n_levels;
-    // as many records per lane as the bucket needs: every slot costs the
-    // same instructions, filled or not
-    if (ni <= 64) done = wave_bucket<1, kSlots>(p, W, gb, off, ni, rec, pre, lo, nlev, carry, maxe);
-    else if (ni <= 128) done = wave_bucket<2, kSlots>(p, W, gb, off, ni, rec, pre, lo, nlev, carry, maxe);
-    else if (ni <= 192) done = wave_bucket<3, kSlots>(p, W, gb, off, ni, rec, pre, lo, nlev, carry, maxe);
-    else if (ni <= 256) done = wave_bucket<4, kSlots>(p, W, gb, off, ni, rec, pre, lo, nlev, carry, maxe);
-    else if (ni <= 320) done = wave_bucket<5, kSlots>(p, W, gb, off, ni, rec, pre, lo, nlev, carry, maxe);
-    else if (ni <= 384) done = wave_bucket<6, kSlots>(p, W, gb, off, ni, rec, pre, lo, nlev, carry, maxe);
-    else if (ni <= 448) done = wave_bucket<7, kSlots>(p, W, gb, off, ni, rec, pre, lo, nlev, carry, maxe);
-    else done = wave_bucket<8, kSlots>(p, W, gb, off, ni, rec, pre, lo, nlev, carry, maxe);
-  }
+  if (br.n16 == 0 && n <= kWaveCap)  // only 8 B records (so the segment is narrow: buckets at most 2^30 ns wide)
+    done = wave_merge<kSlots>(p, W, gb, off, (int)n, br.narrow, pre, bucket_lo(g, gb - sd.bucket_begin), sd.n_levels,
+                              carry, maxe);
   if (!done && lane == 0) p.queue[atomicAdd(&p.ticket[2], 1u)] = (unsigned int)gb;
+}
+
+// ----------------------------------------------------------------------------
+// small builds: a workgroup per segment does every step of the build
+// ----------------------------------------------------------------------------
+
+// When every segment is small, the passes above are ten launches of a few
+// microseconds of latency each, with most of the GPU idle. Here one workgroup
+// takes one segment through all of them, with barriers in place of launches:
+// start range, geometry, scatter into the fixed slots (ranks, largest ends and
+// counts in LDS), carry and offsets, the wave merges of its buckets, the block
+// path for those that need it, and the base pass. It leaves the same
+// per-bucket words and records as the passes. A slot overflow is reported
+// like theirs, and the host redoes the build with exact offsets.
+//
+// The line lies at 4096 records per segment (kSmallRecords): up to there a
+// thread keeps its eight records in registers between the start range and the
+// scatter, and a build takes 16-35 us where the passes take 49 (a session of
+// 4 resources, 1.8e3 records, with its upload and regions: 96 -> 54 us). One
+// CU per segment runs out of VALU beyond: with 1e4 records per segment 51 us
+// against 49, with 3e4 105 against 64. 512 threads: two workgroups per CU.
+constexpr int kSmallThreads = 512;
+
+struct SmallSmem {
+  union {
+    WaveSmem w[kSmallThreads / 64];
+    SortSmem<kSmallThreads, 2048> sort;
+  } u;
+  unsigned long long cnt[kSmallBuckets];  // 8 B records | 16 B records << 32
+  unsigned long long maxe[kSmallBuckets * 3];
+  long long carry[kSmallBuckets * 3];
+  unsigned int off[kSmallBuckets];        // merged-interval offset within the segment
+  unsigned int queue[kSmallBuckets];      // buckets for the block path
+  unsigned int nq;
+  int seg;
+  const int64_t* s[kSmallChunks];
+  const int64_t* e[kSmallChunks];
+  int first[kSmallChunks];      // segment's record index of the chunk's first record
+  int slot[kSmallChunks];
+  long long red[2][kSmallThreads / 64];
+  SegStats st;
+  Geom g;
+};
+
+__global__ __launch_bounds__(kSmallThreads, 4) void k_build_small(Plan p) {
+  constexpr int THREADS = kSmallThreads, K = kSmallRecords / THREADS, NW = THREADS / 64;
+  __shared__ SmallSmem S;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int seg = blockIdx.x;
+  const SegDesc sd = p.segs[seg];
+  const SmallSeg ss = p.sseg[seg];
+  const int nb = sd.nb, nch = ss.n_chunks, N = ss.count;
+  for (int j = threadIdx.x; j < nch; j += THREADS) {
+    const ChunkDesc cd = p.chunks[ss.chunk0 + j];
+    S.s[j] = cd.s;
+    S.e[j] = cd.e;
+    S.first[j] = cd.tile_off;
+    S.slot[j] = cd.slot;
+  }
+  for (int b = threadIdx.x; b < nb; b += THREADS) {
+    S.cnt[b] = 0;
+    S.maxe[3 * b] = S.maxe[3 * b + 1] = S.maxe[3 * b + 2] = 0;
+  }
+  if (threadIdx.x == 0) S.nq = 0;
+  __syncthreads();
+  // a thread's K records: their chunks (the largest j with first[j] <= x),
+  // then all loads back to back, from positions clamped into the segment
+  long long sv[K], ev[K];
+  int jj[K];
+  long long mn = LLONG_MAX, mx = -1;  // start range (starts outside [0, 2^62) belong to invalid records)
+  if (N > 0) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const int x = min((int)threadIdx.x + k * THREADS, N - 1);
+      int lo = 0, hi = nch - 1;
+      while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (S.first[mid] <= x) lo = mid; else hi = mid - 1;
+      }
+      jj[k] = lo;
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const int i = min((int)threadIdx.x + k * THREADS, N - 1) - S.first[jj[k]];
+      sv[k] = S.s[jj[k]][i];
+      ev[k] = S.e[jj[k]][i];
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      if ((unsigned long long)sv[k] < (unsigned long long)kTimeLimit) {
+        mn = min(mn, sv[k]);
+        mx = max(mx, sv[k]);
+      }
+    }
+  }
+  mn = -wave_reduce_i64<OpMax>(-mn, -LLONG_MAX);
+  mx = wave_reduce_i64<OpMax>(mx, -1);
+  if (lane == 0) {
+    S.red[0][wave] = mn;
+    S.red[1][wave] = mx;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < NW; ++w) {
+      mn = min(mn, S.red[0][w]);
+      mx = max(mx, S.red[1][w]);
+    }
+    SegStats st;
+    st.min_s = mx < 0 ? ULLONG_MAX : (unsigned long long)mn;
+    st.max_s = mx < 0 ? 0ull : (unsigned long long)mx;
+    st.max_e = 0;
+    st.pad = 0;
+    S.st = st;
+    S.g = make_geom(st, sd);
+  }
+  __syncthreads();
+  const Geom g = S.g;
+  const bool narrow = seg_narrow(g);
+  const long long scap = p.slot_cap;
+  // scatter: lanes of one bucket and kind share one LDS atomic; the leader
+  // reserves their ranks and folds their largest end in
+  uint2* units = (uint2*)p.elems + 2 * sd.bucket_begin * scap;  // the segment's slots: 2 scap units per bucket
+  const unsigned long long lt = (1ull << lane) - 1ull;
+  {
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const int x = (int)threadIdx.x + k * THREADS;
+      if ((wave << 6) + k * THREADS >= N) break;  // wave-uniform
+      int key = -1;  // bucket << 2 | kind slot
+      unsigned int kx = 0, ex = 0;
+      if (x < N) {
+        if (!rec_valid(sv[k], ev[k])) {
+          // first bad record of the build: chunk << 40 | index (rare path)
+          const ChunkDesc& cd = p.chunks[ss.chunk0 + jj[k]];
+          atomicMin(p.err, ((unsigned long long)cd.chunk_id << 40) | (unsigned long long)(x - S.first[jj[k]]));
+          p.owner_err[cd.owner] = 1u;
+        } else if (sv[k] < ev[k]) {
+          const int b = bucket_of(sv[k], g), slot = S.slot[jj[k]];
+          const long long lo = bucket_lo(g, b);
+          key = b << 2 | slot;
+          kx = ((unsigned int)(sv[k] - lo) << 2) | (unsigned int)slot;
+          ex = ev[k] - lo < 0xFFFFFFFFll ? (unsigned int)(ev[k] - lo + 1) : 0xFFFFFFFFu;  // far ends clamped
+        }
+      }
+      unsigned long long todo = __ballot(key >= 0);
+      while (todo) {
+        const int leader = __ffsll((long long)todo) - 1;
+        const int lk = __builtin_amdgcn_readlane(key, leader);
+        const bool in = key == lk;
+        const unsigned long long m = __ballot(in);
+        const int b = lk >> 2;
+        long long emax;
+        unsigned int e32 = 0xFFFFFFFFu;
+        if (narrow) e32 = (unsigned int)wave_reduce_i32<OpMaxU32>((int)(in ? ex : 0u), 0);
+        if (e32 != 0xFFFFFFFFu) emax = bucket_lo(g, b) + (long long)e32 - 1;
+        else emax = wave_reduce_i64<OpMax>(in ? ev[k] : 0ll, 0ll);
+        unsigned long long old = 0;
+        if (lane == leader) {
+          const unsigned long long n = (unsigned long long)__popcll(m);
+          old = atomicAdd(&S.cnt[b], narrow ? n : n << 32);
+          atomicMax(&S.maxe[3 * b + (lk & 3)], (unsigned long long)emax);
+        }
+        old = (unsigned long long)readlane64((long long)old, leader);
+        if (in) {
+          const long long rank = (long long)(narrow ? (unsigned int)old : (unsigned int)(old >> 32)) + __popcll(m & lt);
+          uint2* ub = units + 2 * b * scap;
+          if (narrow) {
+            if (rank < 2 * scap) ub[rank] = make_uint2(kx, ex);
+          } else if (rank < scap) {
+            Elem el;
+            el.s = sv[k];
+            el.e_slot = (long long)((unsigned long long)ev[k] | ((unsigned long long)(lk & 3) << kSlotShift));
+            *(Elem*)(ub + 2 * scap - 2 * (rank + 1)) = el;
+          }
+        }
+        todo &= ~m;
+      }
+    }
+  }
+  __syncthreads();
+  // one wave: offsets of the merged intervals and the running largest end of
+  // all earlier buckets per level
+  if (wave == 0) {
+    const long long init = S.st.min_s > S.st.max_s ? -1 : (long long)S.st.min_s - 1;
+    long long run[3] = {init, init, init};
+    unsigned int roff = 0, over = 0;
+    for (int c0 = 0; c0 < nb; c0 += 64) {
+      const int b = c0 + lane;
+      unsigned int n = 0;
+      long long v[3] = {LLONG_MIN, LLONG_MIN, LLONG_MIN};
+      if (b < nb) {
+        const unsigned long long cu = S.cnt[b];
+        n = (unsigned int)cu + (unsigned int)(cu >> 32);
+        if (n > (unsigned int)scap) {
+          n = (unsigned int)scap;
+          over = 1;
+        }
+        const long long m0 = (long long)S.maxe[3 * b], m1 = (long long)S.maxe[3 * b + 1], m2 = (long long)S.maxe[3 * b + 2];
+        v[0] = m0 ? m0 : LLONG_MIN;
+        v[1] = m1 > v[0] && m1 ? m1 : v[0];
+        v[2] = m2 > v[1] && m2 ? m2 : v[1];
+      }
+      unsigned int all;
+      const unsigned int ex = wave_excl_scan_u32<OpSumU>(n, 0u, all);
+      if (b < nb) S.off[b] = roff + ex;
+      roff += all;
+#pragma unroll
+      for (int l = 0; l < 3; ++l) {
+        long long top;
+        const long long e = wave_excl_scan_dpp<OpMax>(v[l], LLONG_MIN, top);
+        if (b < nb) S.carry[3 * b + l] = e > run[l] ? e : run[l];
+        run[l] = top > run[l] ? top : run[l];
+      }
+    }
+    if (over) atomicAdd(&p.oversized[1], 1ull);  // slot overflow: the build is redone with exact offsets
+    if (lane == 0) {
+      SegStats st = S.st;
+      st.max_e = (unsigned long long)(run[2] > init ? run[2] : (init + 1 > 0 ? init + 1 : 0));
+      p.stats[seg] = st;
+      p.geom[seg] = g;
+    }
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < 3 * nb; i += THREADS) {
+    const long long q = sd.bucket_begin * 3 + i;
+    p.maxend[q] = S.maxe[i];
+    p.carry[q] = S.carry[i];
+  }
+  for (int b = threadIdx.x; b < nb; b += THREADS) {
+    const long long gb = sd.bucket_begin + b;
+    const unsigned long long cu = S.cnt[b];
+    const unsigned long long n = (cu & 0xFFFFFFFFull) + (cu >> 32);
+    p.cursor[gb] = cu;
+    p.counts[gb] = (unsigned int)(n < (unsigned long long)scap ? n : (unsigned long long)scap);
+    p.offsets[gb] = (unsigned long long)(ss.elem0 + S.off[b]);
+    p.bucket_seg[gb] = seg;
+  }
+  // merge: a wave per bucket
+  for (int b = wave; b < nb; b += NW) {
+    const long long gb = sd.bucket_begin + b;
+    const unsigned long long cu = (unsigned long long)readlane64((long long)S.cnt[b], 0);
+    const long long n = (long long)((cu & 0xFFFFFFFFull) + (cu >> 32));
+    if (n == 0 || n > scap) {  // empty, or a slot overflow that makes the host redo the build
+      if (lane < 3) {
+        p.bsum[gb * 3 + lane] = 0;
+        p.ncomp[gb * 3 + lane] = 0;
+      }
+      continue;
+    }
+    bool done = false;
+    if (narrow && n <= kWaveCap) {
+      const uint2* rec = units + 2 * b * scap;
+      uint2 pre[kWavePre];
+#pragma unroll
+      for (int r = 0; r < kWavePre; ++r) pre[r] = rec[lane + 64 * r];  // slots hold 2 scap >= 256 units
+      long long carry[3], maxe[3];
+#pragma unroll
+      for (int l = 0; l < 3; ++l) {
+        carry[l] = readlane64(S.carry[3 * b + l], 0);
+        maxe[l] = readlane64((long long)S.maxe[3 * b + l], 0);
+      }
+      maxe[1] = max(maxe[0], maxe[1]);
+      maxe[2] = max(maxe[1], maxe[2]);
+      const long long off = ss.elem0 + (long long)(unsigned int)__builtin_amdgcn_readfirstlane((int)S.off[b]);
+      done = wave_merge<true>(p, S.u.w[wave], gb, off, (int)n, rec, pre, bucket_lo(g, b), sd.n_levels, carry, maxe);
+    }
+    if (!done && lane == 0) S.queue[atomicAdd(&S.nq, 1u)] = (unsigned int)b;
+  }
+  __syncthreads();
+  // the block path, a bucket at a time by the whole workgroup
+  const unsigned int nq = S.nq;
+  for (unsigned int q = 0; q < nq; ++q)
+    merge_bucket_block<THREADS, 2048>(p, sd.bucket_begin + S.queue[q], S.u.sort, &S.seg);
+  __syncthreads();
+  if (wave == 0) base_segment(p, seg, lane);
 }
 
 // ----------------------------------------------------------------------------
@@ -1800,12 +2079,17 @@ __device__ long long measure_before(const Plan& p, int seg, int l, long long t) 
 }
 
 // The build's status words into the results (threads 0-2 of one workgroup, in
-// the last kernel of a launch sequence).
-__device__ __forceinline__ void put_status(const Plan& p, unsigned long long* status) {
-  if (threadIdx.x < 3) status[threadIdx.x] = threadIdx.x == 0 ? p.err[0] : p.oversized[threadIdx.x - 1];
+// the last kernel of a launch sequence), and back to their identities if asked.
+__device__ __forceinline__ void put_status(const Plan& p, unsigned long long* status, bool reset) {
+  const int i = threadIdx.x;
+  if (i < 3) {
+    unsigned long long* w = i == 0 ? p.err : p.oversized + (i - 1);
+    status[i] = *w;
+    if (reset) *w = i == 0 ? ULLONG_MAX : 0ull;
+  }
 }
 
-__global__ void k_status(Plan p, unsigned long long* status) { put_status(p, status); }
+__global__ void k_status(Plan p, unsigned long long* status, bool reset) { put_status(p, status, reset); }
 
 // State times of resource r of region rd from its levels' measures D inside
 // it, written to `times` and added to v (sums U, W, MPI, Other, K, M; maxima
@@ -1858,12 +2142,12 @@ __device__ __forceinline__ void put_trees(const Tree* lds, int n, Tree* out) {
 // (16 regions x 128 resources): 13.0 us, against 17.5 with a workgroup per
 // region and 15.8 as two kernels; small trace (1 x 8): 4.0 against 9.5.
 __global__ __launch_bounds__(256) void k_region(Plan p, const RegionDesc* regions, long long* times, Tree* trees,
-                                                unsigned long long* status) {
+                                                unsigned long long* status, bool reset) {
   __shared__ long long lds[4 * 10];
   __shared__ long long tot[9];
   __shared__ Tree tree;
   __shared__ int s_last;
-  if (blockIdx.x == 0 && blockIdx.y == 0) put_status(p, status);
+  if (blockIdx.x == 0 && blockIdx.y == 0) put_status(p, status, reset);
   const RegionDesc rd = regions[blockIdx.x];
   if (rd.n_ivl) return;  // a per-resource region: k_region_multi
   const int R = rd.n_hosts + rd.n_devices;
@@ -2020,6 +2304,12 @@ hipError_t launch_gather(const CopyChunk* chunks, int n, hipStream_t st) {
   return flush();
 }
 
+hipError_t launch_build_small(const Plan& p, hipStream_t st) {
+  if (p.n_segs == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_build_small, dim3((unsigned)p.n_segs), dim3(kSmallThreads), 0, st, p);
+  return hipGetLastError();
+}
+
 hipError_t launch_reset(const Plan& p, hipStream_t st) {
   const long long work = max(3 * p.n_buckets + p.n_segs, p.n_tiles) + 64;
   int blocks = (int)min(2048ll, (work + 255) / 256);
@@ -2144,15 +2434,15 @@ hipError_t launch_base(const Plan& p, hipStream_t st) {
 }
 
 hipError_t launch_region(const Plan& p, const RegionDesc* regions, int n_regions, int n_plain, int max_res, Tree* trees,
-                         unsigned long long* status, long long* times, const IvlDesc* ivls, long long n_ivls,
-                         long long* macc, hipStream_t st) {
+                         unsigned long long* status, bool reset, long long* times, const IvlDesc* ivls,
+                         long long n_ivls, long long* macc, hipStream_t st) {
   if (n_plain == 0) {
-    hipLaunchKernelGGL(k_status, dim3(1), dim3(64), 0, st, p, status);
+    hipLaunchKernelGGL(k_status, dim3(1), dim3(64), 0, st, p, status, reset);
   } else {
     const int slice = max_res <= 16 || (long long)n_plain * max_res <= 8192 ? 8 : 32;
     const unsigned slices = (unsigned)std::max(1, (max_res + slice - 1) / slice);
     hipLaunchKernelGGL(k_region, dim3((unsigned)n_regions, slices), dim3(8 * slice), 0, st, p, regions, times, trees,
-                       status);
+                       status, reset);
   }
   if (n_ivls > 0) {
     hipLaunchKernelGGL(k_ivl_zero, dim3((unsigned)n_regions), dim3(256), 0, st, regions, macc);

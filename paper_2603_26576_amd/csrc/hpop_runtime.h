@@ -71,6 +71,7 @@ struct Workspace {
   Plan plan{};
   ChunkDesc* d_chunks = nullptr;
   SegDesc* d_segs = nullptr;
+  SmallSeg* d_sseg = nullptr;
   RegionDesc* d_regions = nullptr;
   Tree* d_trees = nullptr;
   long long* d_times = nullptr;
@@ -88,7 +89,7 @@ struct Workspace {
   hpop_status prepare(Alloc& a, long long n_chunks, long long n_tiles, long long n_segs, long long n_buckets,
                       long long n_elems,
                       long long n_slots, long long n_regions, long long n_times, long long n_owners,
-                      long long n_ivls, std::string& err);
+                      long long n_ivls, bool small, std::string& err);
   void release(Alloc& a);
 };
 
@@ -99,6 +100,10 @@ struct Engine {
   std::vector<ChunkDesc> h_chunks;
   std::vector<int32_t> h_tile_chunk;  // [n_tiles] chunk of each streaming tile (see Plan::tile_chunk)
   std::vector<SegDesc> h_segs;
+  std::vector<SmallSeg> h_sseg;       // not empty: every segment is small (see k_build_small)
+  bool staged = false;                // the plan keeps the build's passes apart (their times are wanted)
+  bool keep_status = false;           // the build's status words are read after the enqueued kernels
+  int plan_passes = 0;                // builds run with the current plan
   std::vector<RegionDesc> h_regions;
   std::vector<IvlDesc> h_ivls;
   std::vector<char> h_desc;  // the upload of a workspace without page-locked staging
@@ -128,6 +133,9 @@ struct Engine {
   hpop_status assemble(hpop_session* const* ss, int k, std::string& err);
   hpop_status assemble_plan(const hpop_tuning& tun, const std::vector<long long>& seg_count,
                             const std::vector<char>& seg_host, int n_owners, long long times, std::string& err);
+  bool plan_small(const std::vector<long long>& seg_count, int slots, int cap);
+  hpop_status prepare_plan(long long tiles, long long own_tiles, long long n_segs, long long buckets, long long elems,
+                           int slots, int cap, int tile, int n_owners, long long times, std::string& err);
   hpop_status upload(std::string& err);
   std::string timing_stage;  // non-empty: time only this stage (see hpop_session_time_stage)
   hpop_status enqueue(bool build, bool with_timing, std::string& err);

@@ -171,12 +171,13 @@ static size_t carve_bytes(size_t n, size_t sz) { return (n * sz + 255) & ~size_t
 
 hpop_status Workspace::prepare(Alloc& a, long long n_chunks, long long n_tiles, long long n_segs,
                                long long n_buckets, long long n_elems, long long n_slots, long long n_regions,
-                               long long n_times, long long n_owners, long long n_ivls, std::string& err) {
+                               long long n_times, long long n_owners, long long n_ivls, bool small_segs,
+                               std::string& err) {
   const size_t nscan = (size_t)((n_buckets + kScanTile - 1) / kScanTile + 1);
   size_t small = 0;
   small += carve_bytes(n_chunks, sizeof(ChunkDesc));
   small += carve_bytes(n_tiles, sizeof(int32_t));
-  small += carve_bytes(n_segs, sizeof(SegDesc));
+  small += carve_bytes(n_segs, sizeof(SegDesc)) + carve_bytes(small_segs ? n_segs : 0, sizeof(SmallSeg));
   small += carve_bytes(n_segs, sizeof(SegStats));
   small += carve_bytes(n_segs, sizeof(SegGeom));
   small += carve_bytes(n_buckets, sizeof(unsigned int)) * 2;
@@ -252,6 +253,12 @@ hpop_status Workspace::prepare(Alloc& a, long long n_chunks, long long n_tiles, 
   p.segs = d_segs = carve<SegDesc>(cur, n_segs);
   d_regions = carve<RegionDesc>(cur, n_regions);
   d_ivls = carve<IvlDesc>(cur, n_ivls);
+  d_sseg = carve<SmallSeg>(cur, small_segs ? n_segs : 0);
+  p.sseg = small_segs ? d_sseg : nullptr;
+  p.err = carve<unsigned long long>(cur, 1);
+  p.oversized = carve<unsigned long long>(cur, 2);
+  p.owner_err = carve<unsigned int>(cur, n_owners);
+  p.racc = carve<unsigned long long>(cur, kRaccWords * n_regions);
   upload_base = meta_p;
   upload_bytes = (size_t)(cur - meta_p);
   p.stats = carve<SegStats>(cur, n_segs);
@@ -266,16 +273,12 @@ hpop_status Workspace::prepare(Alloc& a, long long n_chunks, long long n_tiles, 
   p.base = carve<long long>(cur, 3 * n_buckets);
   p.ncomp = carve<unsigned int>(cur, 3 * n_buckets);
   p.seg_total = carve<long long>(cur, 3 * n_segs);
-  p.err = carve<unsigned long long>(cur, 1);
   p.scan_state = carve<unsigned long long>(cur, nscan);
   p.ticket = carve<unsigned int>(cur, 4);
-  p.oversized = carve<unsigned long long>(cur, 2);
   p.queue = carve<unsigned int>(cur, n_buckets);
-  p.owner_err = carve<unsigned int>(cur, n_owners);
   p.n_owners = (int32_t)n_owners;
   p.seg_group = 1;
   d_trees = (Tree*)carve<char>(cur, n_regions * sizeof(Tree) + kStatusBytes);
-  p.racc = carve<unsigned long long>(cur, kRaccWords * n_regions);
   p.n_racc = n_regions;
   d_times = carve<long long>(cur, 4 * n_times);
   d_macc = carve<long long>(cur, n_ivls ? 4 * n_times : 0);
@@ -424,6 +427,11 @@ hpop_status Engine::assemble_plan(const hpop_tuning& tun, const std::vector<long
     buckets += sd.nb;
     h_segs.push_back(sd);
   }
+  if (plan_small(seg_count, slots, cap)) {
+    for (const auto& d : h_chunks) elems += d.count;
+    h_tile_chunk.clear();
+    return prepare_plan(0, 0, n_segs, buckets, elems, slots, cap, tile, n_owners, times, err);
+  }
   // Streaming tiles. A chunk of fewer than half a tile of records would leave
   // its own tile mostly empty (traces of many small record batches), so such
   // chunks share tiles: the chunks with tiles of their own come first in the
@@ -469,9 +477,46 @@ hpop_status Engine::assemble_plan(const hpop_tuning& tun, const std::vector<long
     while (c + 1 < nc && h_chunks[(size_t)c + 1].tile_begin <= t) ++c;
     h_tile_chunk[(size_t)t] = (int32_t)c;
   }
+  return prepare_plan(tiles, own_tiles, n_segs, buckets, elems, slots, cap, tile, n_owners, times, err);
+}
+
+// Whether every segment is small enough for k_build_small; then its chunks are
+// put next to each other in the chunk table (h_sseg).
+bool Engine::plan_small(const std::vector<long long>& seg_count, int slots, int cap) {
+  h_sseg.clear();
+  // the passes' own times are wanted; a merge of fixed slots needs 128 of
+  // them, and the workgroup's block path holds 2048 records
+  if (staged || slots < 128 || cap != 2048 || seg_count.empty()) return false;
+  for (size_t r = 0; r < seg_count.size(); ++r)
+    if (seg_count[r] > kSmallRecords || h_segs[r].nb > kSmallBuckets) return false;
+  std::vector<int> n(seg_count.size() + 1, 0);
+  for (const ChunkDesc& d : h_chunks)
+    if (++n[(size_t)d.seg + 1] > kSmallChunks) return false;
+  for (size_t r = 0; r < seg_count.size(); ++r) n[r + 1] += n[r];
+  h_sseg.resize(seg_count.size());
+  long long elem0 = 0;
+  for (size_t r = 0; r < seg_count.size(); ++r) {
+    h_sseg[r] = SmallSeg{elem0, n[r], n[r + 1] - n[r], (int32_t)seg_count[r], 0};
+    elem0 += seg_count[r];
+  }
+  std::vector<ChunkDesc> by_seg(h_chunks.size());
+  std::vector<int> fill(seg_count.size(), 0);
+  for (ChunkDesc d : h_chunks) {
+    d.tile_pos = -1;
+    d.tile_off = fill[d.seg];
+    fill[d.seg] += (int)d.count;
+    by_seg[(size_t)n[d.seg]++] = d;
+  }
+  h_chunks.swap(by_seg);
+  return true;
+}
+
+hpop_status Engine::prepare_plan(long long tiles, long long own_tiles, long long n_segs, long long buckets,
+                                 long long elems, int slots, int cap, int tile, int n_owners, long long times,
+                                 std::string& err) {
   hpop_status st = ws.prepare(alloc, (long long)h_chunks.size(), tiles, n_segs, buckets, elems,
                               slots > 0 ? buckets * (long long)slots : 0, (long long)h_regions.size(), times,
-                              std::max(1, n_owners), (long long)h_ivls.size(), err);
+                              std::max(1, n_owners), (long long)h_ivls.size(), !h_sseg.empty(), err);
   if (st != HPOP_OK) return st;
   ws.plan.n_tiles = tiles;
   ws.plan.n_own_tiles = own_tiles;
@@ -483,6 +528,7 @@ hpop_status Engine::assemble_plan(const hpop_tuning& tun, const std::vector<long
   ws.plan.slot_cap = slots;
   ws.plan.pad1 = 0;
   n_times = times;
+  plan_passes = 0;
   return HPOP_OK;
 }
 
@@ -514,6 +560,14 @@ hpop_status Engine::upload(std::string& err) {
   put(ws.d_segs, h_segs.data(), h_segs.size() * sizeof(SegDesc));
   put(ws.d_regions, h_regions.data(), h_regions.size() * sizeof(RegionDesc));
   put(ws.d_ivls, h_ivls.data(), h_ivls.size() * sizeof(IvlDesc));
+  put(ws.d_sseg, h_sseg.data(), h_sseg.size() * sizeof(SmallSeg));
+  // the status words and accumulators start at their identities (a build of
+  // small segments has no reset pass: its last kernel puts them back)
+  const Plan& p = ws.plan;
+  const unsigned long long none = ULLONG_MAX;
+  char* tail = h + ((const char*)p.err - ws.upload_base);
+  memset(tail, 0, ws.upload_bytes - (size_t)(tail - h));
+  put(p.err, &none, sizeof none);
   if (ws.upload_bytes)
     HPOP_HIP(hipMemcpyAsync(ws.upload_base, h, ws.upload_bytes, hipMemcpyHostToDevice, alloc.stream),
              "upload descriptors");
@@ -545,7 +599,9 @@ hpop_status Engine::enqueue(bool build, bool with_timing, std::string& err) {
     return hipEventRecord(events[ev++], st);
   };
   HPOP_HIP(mark(nullptr), "hipEventRecord");
-  if (build) {
+  if (build && p.sseg) {
+    HPOP_HIP(launch_build_small(p, st), "k_build_small");
+  } else if (build) {
     HPOP_HIP(pre("reset"), "hipEventRecord");
     HPOP_HIP(launch_reset(p, st), "k_reset");
     HPOP_HIP(mark("reset"), "hipEventRecord");
@@ -594,7 +650,7 @@ hpop_status Engine::enqueue(bool build, bool with_timing, std::string& err) {
   Tree* trees = result_host ? ws.d_trees : (Tree*)ws.pinned.ptr;
   HPOP_HIP(pre("region"), "hipEventRecord");
   HPOP_HIP(launch_region(p, ws.d_regions, nreg, n_plain, max_res, trees, (unsigned long long*)(trees + nreg),
-                         ws.d_times, ws.d_ivls, (long long)h_ivls.size(), ws.d_macc, st),
+                         !keep_status, ws.d_times, ws.d_ivls, (long long)h_ivls.size(), ws.d_macc, st),
            "k_region");
   HPOP_HIP(mark("region"), "hipEventRecord");
   n_marks = ev;
@@ -620,7 +676,7 @@ hpop_status Engine::collect_timing(std::string& err) {
 hpop_status Engine::run(hpop_session* const* ss, int k, uint32_t flags, hpop_metric_tree* out, bool timing,
                         std::string& err) {
   // does the current plan still describe these sessions?
-  bool same = (int)key_sessions.size() == k && built;
+  bool same = (int)key_sessions.size() == k && built && staged == timing;
   if (same) {
     for (int i = 0; i < k; ++i)
       if (key_sessions[i] != ss[i] || key_versions[i] != ss[i]->version || key_arena[i] != ss[i]->arena.ptr ||
@@ -644,6 +700,7 @@ hpop_status Engine::run(hpop_session* const* ss, int k, uint32_t flags, hpop_met
     return t;
   }();
   if (!same) {
+    staged = timing;
     hpop_status st = assemble(ss, k, err);
     if (st != HPOP_OK) {
       built = false;
@@ -667,8 +724,12 @@ hpop_status Engine::run(hpop_session* const* ss, int k, uint32_t flags, hpop_met
     return run(ss, k, flags, out, timing, err);
   }
   built = false;
-  if (build && use_graphs && !timing && !(flags & HPOP_NO_GRAPH)) {
-    // capture the whole launch sequence once per plan and replay it
+  if (build && use_graphs && !timing && !(flags & HPOP_NO_GRAPH) && (plan_passes > 0 || (flags & HPOP_FORCE_REBUILD))) {
+    // a plan that comes again, or is said to by a forced rebuild: capture its
+    // whole launch sequence once and replay it. The build that new records
+    // ask for launches its kernels one by one, which costs less than the
+    // capture and its instantiation (a session whose records change between
+    // computes never replays)
     if (!ws.graph_exec) {
       // capture starts on an idle stream: the descriptor upload has landed
       HPOP_HIP(hipStreamSynchronize(alloc.stream), "hipStreamSynchronize");
@@ -694,6 +755,7 @@ hpop_status Engine::run(hpop_session* const* ss, int k, uint32_t flags, hpop_met
     hpop_status st = enqueue(build, timing, err);
     if (st != HPOP_OK) return st;
   }
+  if (build) ++plan_passes;
   HPOP_HIP(hipStreamSynchronize(alloc.stream), "hipStreamSynchronize");
   if (timing) {
     hpop_status st = collect_timing(err);

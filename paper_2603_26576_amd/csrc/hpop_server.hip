@@ -1035,6 +1035,7 @@ hpop_status hpop_server_create(const hpop_server_config* cfg, hpop_server** out)
     }
     S->engine.alloc = S->alloc;
     S->engine.use_graphs = false;
+    S->engine.keep_status = true;  // the splice kernels read them after the build
     S->worker = std::thread(worker_loop, S);
     *out = S;
     return HPOP_OK;
