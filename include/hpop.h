@@ -392,10 +392,11 @@ typedef struct {
     /* Longest time of each phase of one device step. Host clocks: prep =
      * admission to the first enqueue (planning, growth of device buffers),
      * grow = the device allocations within prep, wait = the worker blocked on
-     * the step's end. Device times (HIP events on the server stream): h2d =
-     * host payload copies, build = bucketed build of the new records, move =
-     * list moves, splice = the merge into the session lists, region = the
-     * region trees and the copies of the results. */
+     * the step's end. Device times (h2d by HIP events, the others by the
+     * device clock, each up to the next one's first kernel): h2d = host
+     * payload copies, build = bucketed build of the new records, move = list
+     * moves, splice = the merge into the session lists, region = the region
+     * trees. */
     double max_prep_us, max_grow_us, max_wait_us;
     double max_h2d_us, max_build_us, max_move_us, max_splice_us, max_region_us;
     /* the same phases' mean per step */
@@ -411,15 +412,15 @@ typedef struct {
 } hpop_server_stats;
 
 /* Sites of hpop_server_stats.max_call_site. */
-#define HPOP_CALL_EVENT 0    /* a phase's HIP event record */
+#define HPOP_CALL_EVENT 0    /* a HIP event record around the payload copies */
 #define HPOP_CALL_PAYLOAD 1  /* a host payload's copy to the device */
-#define HPOP_CALL_MOVE 2     /* the list moves: table copy and kernel */
-#define HPOP_CALL_BUILD 3    /* the build of the step's records: descriptor copies and kernels */
-#define HPOP_CALL_TABLES 4   /* list, item and request table copies */
-#define HPOP_CALL_CONTROL 5  /* the scratch control word's copy */
+#define HPOP_CALL_MOVE 2     /* the list moves' kernel */
+#define HPOP_CALL_BUILD 3    /* the build of the step's records: the copy of descriptors and tables, the kernels */
+#define HPOP_CALL_TABLES 4   /* the list table's copy after a session opened */
+#define HPOP_CALL_CONTROL 5  /* the scratch control words' copy when a step's scratch ran out */
 #define HPOP_CALL_SPLICE 6   /* the prep and splice kernels */
 #define HPOP_CALL_REGION 7   /* the region kernel */
-#define HPOP_CALL_RESULTS 8  /* the copies of trees, lists and error flags to the host */
+#define HPOP_CALL_RESULTS 8  /* not taken: the kernels store the results in page-locked memory */
 
 hpop_status hpop_server_create(const hpop_server_config* cfg, hpop_server** out);
 hpop_status hpop_server_destroy(hpop_server* srv);

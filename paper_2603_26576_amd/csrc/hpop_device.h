@@ -561,6 +561,64 @@ __device__ Elem* sort_global(SortSmem<THREADS, CAP>& sm, Elem* src, Elem* dst, l
   return src;
 }
 
+// The last of cnt components that starts before x (both relative to the first
+// time of what holds them, width long): its start and measure and the next
+// one's measure (bs after the last). False: none starts before x, and next is
+// the first one's measure.
+//
+// A query is a chain of dependent loads, one cache miss each, so what counts
+// is the number of probes. Starts spread about evenly over their bucket:
+// each probe takes the place that the starts known so far on both sides of x
+// suggest and reads two neighbours, which mostly ends after three or four
+// probes where halving took nine (a 350-record bucket) and then read the
+// result's words in two more. Buckets with their starts in a few places get
+// halving after PROBES of them. Against halving alone the region stage of a
+// batch of 128 traces (512 regions) takes 32 us instead of 39, that of 256
+// devices with their streams 17.6 instead of 20, the mid trace's the same.
+template <int PROBES = 3, class T, class Load>
+__device__ __forceinline__ bool find_comp(Load load, int cnt, T x, T width, long long bs, T& cs, long long& pl,
+                                          long long& next) {
+  int L = -1, H = cnt;
+  T csL = 0, csH = width;
+  long long plL = 0, plH = bs;
+  for (int it = 0; H - L > 1; ++it) {
+    int k = (L + H) >> 1;
+    if (it < PROBES) {
+      const float f = x >= csH ? 1.0f : (float)(x - csL) / (float)(csH - csL);
+      k = min(max(L + (int)(f * (float)(H - L - 1) + 0.5f), L + 1), H - 1);
+    }
+    const bool two = k + 1 < H;
+    T c0, c1;
+    long long p0, p1;
+    load(k, c0, p0);
+    load(two ? k + 1 : k, c1, p1);
+    if (c0 >= x) {
+      H = k;
+      csH = c0;
+      plH = p0;
+    } else {
+      L = k;
+      csL = c0;
+      plL = p0;
+      if (two) {
+        if (c1 >= x) {
+          H = k + 1;
+          csH = c1;
+          plH = p1;
+        } else {
+          L = k + 1;
+          csL = c1;
+          plL = p1;
+        }
+      }
+    }
+  }
+  cs = csL;
+  pl = plL;
+  next = plH;
+  return L >= 0;
+}
+
 // Ratios of one region's metric trees from exact integer aggregates.
 // v: sumU, sumW, sumMPI, sumOther, sumK, sumM, maxUW, maxK, maxKM
 __device__ __forceinline__ Tree make_tree(long long E, int n_hosts, int n_devices, const long long (&v)[9]) {
@@ -593,6 +651,41 @@ __device__ __forceinline__ Tree make_tree(long long E, int n_hosts, int n_device
   t.undefined_mask = mask;
   t.reserved = 0;
   return t;
+}
+
+// State times of resource r of region rd from its levels' measures D inside
+// it, written to `times` and added to v (sums U, W, MPI, Other, K, M; maxima
+// U+W, K, K+M).
+__device__ __forceinline__ void add_times(bool host, const long long (&D)[3], long long E, long long* out,
+                                          long long (&v)[9]) {
+  if (host) {
+    const long long u = D[0], w = D[1] - D[0], mpi = D[2] - D[1], o = E - D[2];
+    out[0] = u; out[1] = w; out[2] = mpi; out[3] = o;
+    v[0] += u; v[1] += w; v[2] += mpi; v[3] += o;
+    v[6] = u + w > v[6] ? u + w : v[6];
+  } else {
+    const long long k = D[0], mm = D[1] - D[0], idle = E - D[1];
+    out[0] = k; out[1] = mm; out[2] = idle; out[3] = 0;
+    v[4] += k; v[5] += mm;
+    v[7] = k > v[7] ? k : v[7];
+    v[8] = k + mm > v[8] ? k + mm : v[8];
+  }
+}
+
+// Eight neighbouring lanes hold one resource's measures (lane 2 l + end, level
+// l): the first of them gets the levels' measures inside the region.
+__device__ __forceinline__ void group_levels(long long M, long long (&D)[3]) {
+#pragma unroll
+  for (int l = 0; l < 3; ++l) D[l] = __shfl(M, 2 * l + 1, 8) - __shfl(M, 2 * l, 8);
+}
+
+// The finished trees of a workgroup's n consecutive regions go out as whole
+// words, neighbouring lanes to neighbouring words: the results lie in host
+// memory, where every store is a bus transfer.
+__device__ __forceinline__ void put_trees(const Tree* lds, int n, Tree* out) {
+  constexpr int kWords = sizeof(Tree) / 8;
+  const unsigned long long* src = (const unsigned long long*)lds;
+  for (int i = threadIdx.x; i < n * kWords; i += blockDim.x) ((unsigned long long*)out)[i] = src[i];
 }
 
 // Block reduction of per-thread resource state times (thread 0 receives it).

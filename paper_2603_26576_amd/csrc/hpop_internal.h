@@ -150,9 +150,12 @@ struct Elem {  // one record regrouped by bucket (the 16 B form)
 // end of the bucket's records of that slot, maxend); a record of a wide
 // segment takes two units from the back in the 16 B form. cursor[gb] counts
 // both: 8 B records in the low 32 bits, 16 B records in the high 32.
-// Device pointers of one build plan.
 constexpr int kRaccWords = 10;
 
+// Points of a serving step whose device clock the kernels note (Plan::ts).
+constexpr int kTsMove = 0, kTsBuild = 1, kTsSplice = 2, kTsRegion = 3, kTsEnd = 4, kTsPoints = 5;
+
+// Device pointers of one build plan.
 struct Plan {
   const ChunkDesc* chunks;
   int32_t n_chunks;
@@ -194,6 +197,7 @@ struct Plan {
   unsigned long long* racc;          // [n_racc][kRaccWords] per region: six sums, three maxima, slices added;
                                      // zero between launches
   int64_t n_racc;
+  unsigned long long* ts;            // null, or the device clock at points of a serving step (kTs*)
   int32_t n_owners;
   int32_t seg_group;                 // > 1: the per-segment passes take segments in groups (many small segments)
 };

@@ -92,6 +92,7 @@ __global__ void k_reset(Plan p) {
     p.oversized[1] = 0;
   }
   if (tid < 4) p.ticket[tid] = 0;
+  if (tid == 0 && p.ts) p.ts[kTsBuild] = __builtin_amdgcn_s_memrealtime();
   for (long long i = tid; i < p.n_owners; i += stride) p.owner_err[i] = 0;
   for (long long i = tid; i < kRaccWords * p.n_racc; i += stride) p.racc[i] = 0;
 }
@@ -1751,7 +1752,10 @@ __global__ __launch_bounds__(kSmallThreads, 4) void k_build_small(Plan p) {
     S.cnt[b] = 0;
     S.maxe[3 * b] = S.maxe[3 * b + 1] = S.maxe[3 * b + 2] = 0;
   }
-  if (threadIdx.x == 0) S.nq = 0;
+  if (threadIdx.x == 0) {
+    S.nq = 0;
+    if (blockIdx.x == 0 && p.ts) p.ts[kTsBuild] = __builtin_amdgcn_s_memrealtime();
+  }
   __syncthreads();
   // a thread's K records: their chunks (the largest j with first[j] <= x),
   // then all loads back to back, from positions clamped into the segment
@@ -1969,64 +1973,6 @@ __global__ __launch_bounds__(kSmallThreads, 4) void k_build_small(Plan p) {
 // region: clip every resource by binary search, reduce, finalize in FP64
 // ----------------------------------------------------------------------------
 
-// The last component of a bucket that starts before x (both relative to the
-// bucket's first time): its start and measure and the next one's measure (the
-// bucket's own, bs, after the last). False: none starts before x, and next is
-// the first one's measure.
-//
-// A query is a chain of dependent loads, one cache miss each, so what counts
-// is the number of probes. Starts spread about evenly over their bucket:
-// each probe takes the place that the starts known so far on both sides of x
-// suggest and reads two neighbours, which mostly ends after three or four
-// probes where halving took nine (a 350-record bucket) and then read the
-// result's words in two more. Buckets with their starts in a few places get
-// halving after three probes. Against halving alone the region stage of a
-// batch of 128 traces (512 regions) takes 32 us instead of 39, that of 256
-// devices with their streams 17.6 instead of 20, the mid trace's the same.
-template <class T, class Load>
-__device__ __forceinline__ bool find_comp(Load load, int cnt, T x, T width, long long bs, T& cs, long long& pl,
-                                          long long& next) {
-  int L = -1, H = cnt;
-  T csL = 0, csH = width;
-  long long plL = 0, plH = bs;
-  for (int it = 0; H - L > 1; ++it) {
-    int k = (L + H) >> 1;
-    if (it < 3) {
-      const float f = x >= csH ? 1.0f : (float)(x - csL) / (float)(csH - csL);
-      k = min(max(L + (int)(f * (float)(H - L - 1) + 0.5f), L + 1), H - 1);
-    }
-    const bool two = k + 1 < H;
-    T c0, c1;
-    long long p0, p1;
-    load(k, c0, p0);
-    load(two ? k + 1 : k, c1, p1);
-    if (c0 >= x) {
-      H = k;
-      csH = c0;
-      plH = p0;
-    } else {
-      L = k;
-      csL = c0;
-      plL = p0;
-      if (two) {
-        if (c1 >= x) {
-          H = k + 1;
-          csH = c1;
-          plH = p1;
-        } else {
-          L = k + 1;
-          csL = c1;
-          plL = p1;
-        }
-      }
-    }
-  }
-  cs = csL;
-  pl = plL;
-  next = plH;
-  return L >= 0;
-}
-
 // Measure of level l of segment seg before time t.
 __device__ long long measure_before(const Plan& p, int seg, int l, long long t) {
   const SegDesc sd = p.segs[seg];
@@ -2050,7 +1996,7 @@ __device__ long long measure_before(const Plan& p, int seg, int l, long long t) 
     // past the last bucket's width no component starts: any x there will do
     const unsigned int x = (unsigned int)min(t - lo, 0x7FFFFFFFll);
     unsigned int c32;
-    any = find_comp<unsigned int>(
+    any = find_comp(
         [&](int k, unsigned int& s, long long& m) {
           const CompN v = c[k];
           s = v.cs;
@@ -2060,7 +2006,7 @@ __device__ long long measure_before(const Plan& p, int seg, int l, long long t) 
     cs = lo + (long long)c32;
   } else {
     const Comp* c = p.comp[l] + off;
-    any = find_comp<long long>(
+    any = find_comp(
         [&](int k, long long& s, long long& m) {
           const Comp v = c[k];
           s = v.cs - lo;
@@ -2090,41 +2036,6 @@ __device__ __forceinline__ void put_status(const Plan& p, unsigned long long* st
 }
 
 __global__ void k_status(Plan p, unsigned long long* status, bool reset) { put_status(p, status, reset); }
-
-// State times of resource r of region rd from its levels' measures D inside
-// it, written to `times` and added to v (sums U, W, MPI, Other, K, M; maxima
-// U+W, K, K+M).
-__device__ __forceinline__ void add_times(bool host, const long long (&D)[3], long long E, long long* out,
-                                          long long (&v)[9]) {
-  if (host) {
-    const long long u = D[0], w = D[1] - D[0], mpi = D[2] - D[1], o = E - D[2];
-    out[0] = u; out[1] = w; out[2] = mpi; out[3] = o;
-    v[0] += u; v[1] += w; v[2] += mpi; v[3] += o;
-    v[6] = u + w > v[6] ? u + w : v[6];
-  } else {
-    const long long k = D[0], mm = D[1] - D[0], idle = E - D[1];
-    out[0] = k; out[1] = mm; out[2] = idle; out[3] = 0;
-    v[4] += k; v[5] += mm;
-    v[7] = k > v[7] ? k : v[7];
-    v[8] = k + mm > v[8] ? k + mm : v[8];
-  }
-}
-
-// Eight neighbouring lanes hold one resource's measures (lane 2 l + end, level
-// l): the first of them gets the levels' measures inside the region.
-__device__ __forceinline__ void group_levels(long long M, long long (&D)[3]) {
-#pragma unroll
-  for (int l = 0; l < 3; ++l) D[l] = __shfl(M, 2 * l + 1, 8) - __shfl(M, 2 * l, 8);
-}
-
-// The finished trees of a workgroup's n consecutive regions go out as whole
-// words, neighbouring lanes to neighbouring words: the results lie in host
-// memory, where every store is a bus transfer.
-__device__ __forceinline__ void put_trees(const Tree* lds, int n, Tree* out) {
-  constexpr int kWords = sizeof(Tree) / 8;
-  const unsigned long long* src = (const unsigned long long*)lds;
-  for (int i = threadIdx.x; i < n * kWords; i += blockDim.x) ((unsigned long long*)out)[i] = src[i];
-}
 
 // Plain regions: a slice of resources of one region per workgroup, eight
 // threads per resource (level and end), clips them by binary search, writes

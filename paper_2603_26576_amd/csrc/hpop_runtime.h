@@ -72,6 +72,8 @@ struct Workspace {
   ChunkDesc* d_chunks = nullptr;
   SegDesc* d_segs = nullptr;
   SmallSeg* d_sseg = nullptr;
+  char* d_extra = nullptr;       // a caller's own tables, uploaded with the descriptors
+  size_t extra_bytes = 0;        // their size (set before the plan is made)
   RegionDesc* d_regions = nullptr;
   Tree* d_trees = nullptr;
   long long* d_times = nullptr;
@@ -102,10 +104,11 @@ struct Engine {
   std::vector<SegDesc> h_segs;
   std::vector<SmallSeg> h_sseg;       // not empty: every segment is small (see k_build_small)
   bool staged = false;                // the plan keeps the build's passes apart (their times are wanted)
-  bool keep_status = false;           // the build's status words are read after the enqueued kernels
+  bool keep_status = false;           // only builds are enqueued: the caller's kernels read what they leave
   int plan_passes = 0;                // builds run with the current plan
   std::vector<RegionDesc> h_regions;
   std::vector<IvlDesc> h_ivls;
+  std::vector<char> h_extra;  // the caller's tables (ws.extra_bytes)
   std::vector<char> h_desc;  // the upload of a workspace without page-locked staging
   std::vector<std::pair<int, int>> chunk_owner;  // (session index, chunk index) per chunk desc
   std::vector<int> seg_of_session, reg_of_session;

@@ -194,6 +194,7 @@ hpop_status Workspace::prepare(Alloc& a, long long n_chunks, long long n_tiles, 
   small += carve_bytes(kRaccWords * n_regions, sizeof(unsigned long long));
   small += carve_bytes(n_ivls, sizeof(IvlDesc)) + carve_bytes(n_ivls ? 4 * n_times : 0, sizeof(long long));
   small += carve_bytes(4 * n_times, sizeof(long long));
+  small += carve_bytes(extra_bytes, 1);
   // bucketed records: fixed slots per bucket (n_slots > 0) or exact offsets,
   // where oversized buckets also need a scratch copy for their global sort
   const size_t big_e = carve_bytes(n_slots > 0 ? n_slots : n_elems, sizeof(Elem));
@@ -255,6 +256,7 @@ hpop_status Workspace::prepare(Alloc& a, long long n_chunks, long long n_tiles, 
   d_ivls = carve<IvlDesc>(cur, n_ivls);
   d_sseg = carve<SmallSeg>(cur, small_segs ? n_segs : 0);
   p.sseg = small_segs ? d_sseg : nullptr;
+  d_extra = carve<char>(cur, extra_bytes);
   p.err = carve<unsigned long long>(cur, 1);
   p.oversized = carve<unsigned long long>(cur, 2);
   p.owner_err = carve<unsigned int>(cur, n_owners);
@@ -561,6 +563,7 @@ hpop_status Engine::upload(std::string& err) {
   put(ws.d_regions, h_regions.data(), h_regions.size() * sizeof(RegionDesc));
   put(ws.d_ivls, h_ivls.data(), h_ivls.size() * sizeof(IvlDesc));
   put(ws.d_sseg, h_sseg.data(), h_sseg.size() * sizeof(SmallSeg));
+  put(ws.d_extra, h_extra.data(), ws.extra_bytes);
   // the status words and accumulators start at their identities (a build of
   // small segments has no reset pass: its last kernel puts them back)
   const Plan& p = ws.plan;
@@ -639,6 +642,7 @@ hpop_status Engine::enqueue(bool build, bool with_timing, std::string& err) {
     HPOP_HIP(launch_base(p, st), "k_base");
     HPOP_HIP(mark("base"), "hipEventRecord");
   }
+  if (keep_status) return HPOP_OK;  // the caller's kernels take over from here
   int max_res = 0, n_plain = 0;
   for (const RegionDesc& rd : h_regions) {
     max_res = std::max(max_res, rd.n_hosts + rd.n_devices);
@@ -650,7 +654,7 @@ hpop_status Engine::enqueue(bool build, bool with_timing, std::string& err) {
   Tree* trees = result_host ? ws.d_trees : (Tree*)ws.pinned.ptr;
   HPOP_HIP(pre("region"), "hipEventRecord");
   HPOP_HIP(launch_region(p, ws.d_regions, nreg, n_plain, max_res, trees, (unsigned long long*)(trees + nreg),
-                         !keep_status, ws.d_times, ws.d_ivls, (long long)h_ivls.size(), ws.d_macc, st),
+                         true, ws.d_times, ws.d_ivls, (long long)h_ivls.size(), ws.d_macc, st),
            "k_region");
   HPOP_HIP(mark("region"), "hipEventRecord");
   n_marks = ev;

@@ -25,6 +25,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <atomic>
 #include <chrono>
 #include <climits>
@@ -41,6 +42,7 @@
 #include "hpop.h"
 #include "hpop_device.h"
 #include "hpop_internal.h"
+#include "hpop_kernels.h"
 #include "hpop_runtime.h"
 
 namespace hpop {
@@ -52,6 +54,12 @@ struct ListDev {
   long long cap;
 };
 
+// What a step made of one (query, resource, level) list, for the host's tables.
+struct ListOut {
+  long long len;    // -1: not changed by the step
+  long long total;
+};
+
 struct ServItem {
   int32_t req;     // query index in the step
   int32_t seg;     // segment of the step's build
@@ -61,7 +69,7 @@ struct ServItem {
   int32_t pad;
   long long k0[3];       // prep: first list entry that may change (-1: nothing to do)
   long long xb[3];       // prep: last new bucket (segment-relative) merged with the old entries, -1: none
-  long long scr_off[3];  // prep: scratch offset per level
+  long long scr_off[3];  // prep: scratch offset per level, -1: the overlap fits LDS
   long long scr_len[3];
 };
 
@@ -73,11 +81,13 @@ struct ServReq {
   int32_t list_begin;  // list index of (resource 0, level 0); 3 slots per resource
 };
 
-// a list that moves to a new place in the list heap
+// a list that takes a new place in the list heap (len entries to copy)
 struct ListMove {
   const Comp* src;
   Comp* dst;
   long long len;
+  long long cap;
+  long long list;
 };
 
 struct ServCtl {
@@ -85,6 +95,13 @@ struct ServCtl {
   unsigned long long pool_cap;
   unsigned long long pool_overflow;
   unsigned long long pad;
+};
+
+// The results of a step besides its trees, in page-locked memory.
+struct ServOut {
+  ServCtl ctl;
+  unsigned long long slot_over;
+  unsigned long long ts[kTsPoints];
 };
 
 constexpr int kServThreads = 256;
@@ -98,91 +115,122 @@ __device__ __forceinline__ long long list_ce(const ListDev& L, long long k) {
 
 // measure of list L before time t
 __device__ __forceinline__ long long list_measure(const ListDev& L, long long t) {
-  long long lo = 0, hi = L.len;
-  while (lo < hi) {
-    const long long mid = (lo + hi) >> 1;
-    if (L.base[mid].cs < t) lo = mid + 1; else hi = mid;
-  }
-  const long long k = lo - 1;
-  if (k < 0) return 0;
-  const long long ce = list_ce(L, k);
-  return L.base[k].pl + (ce < t ? ce : t) - L.base[k].cs;
+  if (L.len == 0) return 0;
+  const Comp first = L.base[0], last = L.base[L.len - 1];
+  if (t <= first.cs) return 0;
+  if (t >= last.cs + (L.total - last.pl)) return L.total;
+  long long cs, pl, next;
+  const Comp* c = L.base;
+  // lists hold up to millions of entries: five probes by interpolation before halving
+  (void)find_comp<5>(
+      [&](int k, long long& s, long long& m) {
+        const Comp v = c[k];
+        s = v.cs - first.cs;
+        m = v.pl;
+      },
+      (int)L.len, (long long)(t - first.cs), (long long)(last.cs - first.cs + 1), L.total, cs, pl, next);
+  cs += first.cs;
+  const long long ce = cs + (next - pl);
+  return pl + (ce < t ? ce : t) - cs;
 }
 
-// one thread per (item, level)
-__global__ __launch_bounds__(64) void k_serv_prep(ServItem* items, int n_items, Plan p, const ListDev* lists,
-                                                  long long* frontier, ServCtl* ctl) {
-  const int t = blockIdx.x * 64 + threadIdx.x;
+// First entry of L whose end is at or after x (L.len: none), by one wave:
+// queries continue their session, so the last 64 entries are looked at first;
+// else each round narrows the range to one of 64 parts.
+__device__ __forceinline__ long long list_first_end(const ListDev& L, long long x, int lane) {
+  long long lo = 0, hi = L.len;  // every entry before lo ends before x, every one from hi on does not
+  long long at = max(0ll, hi - 64), step = 1;
+  while (lo < hi) {
+    const long long k = at + (long long)lane * step;
+    const unsigned long long before = __ballot(k < hi && list_ce(L, k) < x);
+    const int n = __popcll(before);  // ends increase: the lanes before x are the first ones
+    if (n < 64) hi = min(hi, at + n * step);
+    if (n > 0) lo = max(lo, at + (n - 1) * step + 1);
+    at = lo;
+    step = max(1ll, (hi - lo + 63) / 64);
+  }
+  return lo;
+}
+
+// A wave per (item, level): what the splice of its list has to redo.
+__global__ __launch_bounds__(256) void k_serv_prep(ServItem* items, int n_items, Plan p, const ListDev* lists,
+                                                   long long* frontier, ServCtl* ctl) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) p.ts[kTsSplice] = __builtin_amdgcn_s_memrealtime();
+  const int lane = threadIdx.x & 63;
+  const int t = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (t >= n_items * 3) return;
   ServItem& it = items[t / 3];
   const int l = t % 3;
-  it.k0[l] = -1;
-  it.xb[l] = -1;
-  it.scr_len[l] = 0;
-  it.scr_off[l] = 0;
+  long long k0 = -1, xb = -1, off = -1, need = 0;
   // a query with an invalid record is not applied; a build whose buckets
   // outgrew their slots is redone before anything is applied
-  if (l >= it.nlev || p.owner_err[it.req] || p.oversized[1]) return;
-  const SegDesc sd = p.segs[it.seg];
-  const SegStats stt = p.stats[it.seg];
-  if (l == 0 && stt.max_e > stt.min_s) atomicMax((unsigned long long*)&frontier[it.sid], stt.max_e);
-  const long long nb = sd.nb;
-  // first bucket with a new merged interval of this level
-  long long b0 = -1;
-  for (long long b = 0; b < nb; ++b)
-    if (p.ncomp[(sd.bucket_begin + b) * 3 + l]) {
-      b0 = b;
-      break;
+  if (l < it.nlev && !p.owner_err[it.req] && !p.oversized[1]) {
+    const SegDesc sd = p.segs[it.seg];
+    const SegStats stt = p.stats[it.seg];
+    if (l == 0 && lane == 0 && stt.max_e > stt.min_s) atomicMax((unsigned long long*)&frontier[it.sid], stt.max_e);
+    const long long nb = sd.nb;
+    // first bucket with a new merged interval of this level
+    long long b0 = -1;
+    for (long long c0 = 0; c0 < nb && b0 < 0; c0 += 64) {
+      const bool some = c0 + lane < nb && p.ncomp[(sd.bucket_begin + c0 + lane) * 3 + l] > 0;
+      const unsigned long long m = __ballot(some);
+      if (m) b0 = c0 + __ffsll((long long)m) - 1;
     }
-  if (b0 < 0) return;  // no new interval at this level
-  const ListDev L = lists[it.list0 + l];
-  const Geom g0 = seg_geom(p, it.seg);
-  const long long x = comp_view(p, g0, sd.bucket_begin, sd.bucket_begin + b0, l).cs(0);
-  long long lo = 0, hi = L.len;
-  while (lo < hi) {
-    const long long mid = (lo + hi) >> 1;
-    if (list_ce(L, mid) < x) lo = mid + 1; else hi = mid;
+    if (b0 >= 0) {
+      const ListDev L = lists[it.list0 + l];
+      const Geom g0 = seg_geom(p, it.seg);
+      const long long x = comp_view(p, g0, sd.bucket_begin, sd.bucket_begin + b0, l).cs(0);
+      k0 = list_first_end(L, x, lane);
+      // new buckets that may reach back into the old list: those starting at or before its largest end
+      if (L.len > 0) {
+        const long long X = list_ce(L, L.len - 1);
+        if (X >= g0.min_s) xb = bucket_index(g0, (unsigned long long)(X - g0.min_s));
+      }
+      long long n = 0;
+      for (long long b = lane; b <= xb; b += 64) n += p.counts[sd.bucket_begin + b];
+      need = L.len - k0 + wave_reduce_i64<OpSum>(n, 0);
+      if (need > kServCap) {
+        unsigned long long at = 0;
+        if (lane == 0) at = atomicAdd(&ctl->pool_used, (unsigned long long)(2 * need));
+        at = (unsigned long long)readlane64((long long)at, 0);
+        if (at + 2 * need > ctl->pool_cap) {
+          if (lane == 0) atomicAdd(&ctl->pool_overflow, (unsigned long long)(2 * need));
+          k0 = xb = -1;
+          need = 0;
+        } else {
+          off = (long long)at;
+        }
+      }
+    }
   }
-  const long long k0 = lo;
-  // new buckets that may reach back into the old list: those starting at or before its largest end
-  long long xb = -1;
-  if (L.len > 0) {
-    const long long X = list_ce(L, L.len - 1);
-    if (X >= g0.min_s) xb = bucket_index(g0, (unsigned long long)(X - g0.min_s));
+  if (lane == 0) {
+    it.k0[l] = k0;
+    it.xb[l] = xb;
+    it.scr_off[l] = off;
+    it.scr_len[l] = need;
   }
-  long long need = L.len - k0;
-  for (long long b = 0; b <= xb; ++b) need += p.counts[sd.bucket_begin + b];
-  const unsigned long long at = atomicAdd(&ctl->pool_used, (unsigned long long)(2 * need));
-  if (at + 2 * need > ctl->pool_cap) {
-    atomicAdd(&ctl->pool_overflow, (unsigned long long)(2 * need));
-    return;
-  }
-  it.k0[l] = k0;
-  it.xb[l] = xb;
-  it.scr_off[l] = (long long)at;
-  it.scr_len[l] = need;
 }
 
 // one workgroup per (item, level)
 __global__ __launch_bounds__(kServThreads) void k_serv_splice(const ServItem* items, Plan p, ListDev* lists,
-                                                              Elem* pool, const ServCtl* ctl) {
+                                                              Elem* pool, const ServCtl* ctl, ListOut* out_lists) {
   __shared__ SortSmem<kServThreads, kServCap> sm;
   __shared__ unsigned int s_fill;
   __shared__ long long s_min[kServThreads / 64];
   __shared__ long long s_pref[kServThreads + 1];
   if (ctl->pool_overflow || p.oversized[1]) return;  // the host redoes the step
-  const ServItem it = items[blockIdx.x / 3];
+  const ServItem& it = items[blockIdx.x / 3];
   const int l = blockIdx.x % 3;
-  if (l >= it.nlev || it.k0[l] < 0) return;
+  const long long k0 = it.k0[l];
+  if (l >= it.nlev || k0 < 0) return;
   ListDev& Lr = lists[it.list0 + l];
   const ListDev L = Lr;
-  const SegDesc sd = p.segs[it.seg];
+  const int seg = it.seg;
+  const SegDesc sd = p.segs[seg];
   const long long nb = sd.nb;
-  const long long k0 = it.k0[l], xb = it.xb[l];
+  const long long xb = it.xb[l];
   const long long nS = L.len - k0;
   const long long total = it.scr_len[l];
-  Elem* A = pool + it.scr_off[l];
-  Elem* B = A + total;
   FlatState st;
   for (int q = 0; q < 3; ++q) {
     st.M[q] = LLONG_MIN;
@@ -193,9 +241,13 @@ __global__ __launch_bounds__(kServThreads) void k_serv_splice(const ServItem* it
   st.P[0] = k0 < L.len ? L.base[k0].pl : L.total;
   st.R[0] = k0;
   Comp* out[3] = {L.base, nullptr, nullptr};
-  const Geom gs = seg_geom(p, it.seg);
+  const Geom gs = seg_geom(p, seg);
   if (total > 0) {
-    // old entries from k0 on, then the level's new records of buckets 0..xb
+    // old entries from k0 on, then the level's new records of buckets 0..xb:
+    // in LDS when they fit (the usual query reaches back into a bucket or
+    // two), else in the step's scratch
+    const bool in_lds = it.scr_off[l] < 0;
+    Elem* A = in_lds ? sm.E : pool + it.scr_off[l];
     for (long long i = threadIdx.x; i < nS; i += kServThreads) {
       Elem el;
       el.s = L.base[k0 + i].cs;
@@ -231,14 +283,12 @@ __global__ __launch_bounds__(kServThreads) void k_serv_splice(const ServItem* it
     long long lo = LLONG_MAX;
     for (int w = 0; w < kServThreads / 64; ++w) lo = s_min[w] < lo ? s_min[w] : lo;
     __syncthreads();
-    if (cnt <= kServCap) {
+    if (in_lds) {
       const int ni = (int)cnt;
-      for (int i = threadIdx.x; i < ni; i += kServThreads) sm.E[i] = A[i];
-      __syncthreads();
       const unsigned short* ord = sort_lds<kServThreads, kServCap>(sm, ni, lo);
       flatten_tile<kServThreads>(sm.E, ord, ni, 1, 0, out, nullptr, 0, st, sm.lds_scan, nullptr);
     } else if (cnt > 0) {
-      const Elem* src = sort_global<kServThreads, kServCap>(sm, A, B, cnt, lo);
+      const Elem* src = sort_global<kServThreads, kServCap>(sm, A, A + total, cnt, lo);
       for (long long t0 = 0; t0 < cnt; t0 += kServCap) {
         const int c = (int)min((long long)kServCap, cnt - t0);
         for (int i = threadIdx.x; i < c; i += kServThreads) sm.E[i] = src[t0 + i];
@@ -265,8 +315,9 @@ __global__ __launch_bounds__(kServThreads) void k_serv_splice(const ServItem* it
       s_pref[threadIdx.x] = ex[0];
       if (threadIdx.x == 0) s_pref[kServThreads] = tot[0];
       __syncthreads();
+      const int last = (int)min((long long)kServThreads, nb - b0) - 1;
       for (long long j = threadIdx.x; j < tot[0]; j += kServThreads) {
-        int a = 0, z = kServThreads - 1;  // last chunk bucket whose prefix is <= j
+        int a = 0, z = last;  // last chunk bucket whose prefix is <= j
         while (a < z) {
           const int mid = (a + z + 1) >> 1;
           if (s_pref[mid] <= j) a = mid; else z = mid - 1;
@@ -282,24 +333,43 @@ __global__ __launch_bounds__(kServThreads) void k_serv_splice(const ServItem* it
       R += tot[0];
       __syncthreads();
     }
-    P = p.seg_total[it.seg * 3 + l] + shift;
+    P = p.seg_total[seg * 3 + l] + shift;
   }
-  __syncthreads();
   if (threadIdx.x == 0) {
     Lr.len = R;
     Lr.total = P;
+    out_lists[blockIdx.x] = ListOut{R, P};
   }
 }
 
-// grid (moves, k): workgroup y of a move copies every k-th run of 256 entries
-__global__ __launch_bounds__(256) void k_list_move(const ListMove* mv) {
+// grid (moves, k): workgroup y of a move copies every k-th run of 256 entries;
+// the first one also enters the list's new place in the table
+__global__ __launch_bounds__(256) void k_list_move(const ListMove* mv, ListDev* lists, unsigned long long* ts) {
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) ts[kTsMove] = __builtin_amdgcn_s_memrealtime();
   const ListMove m = mv[blockIdx.x];
   for (long long i = (long long)blockIdx.y * 256 + threadIdx.x; i < m.len; i += 256ll * gridDim.y) m.dst[i] = m.src[i];
+  if (blockIdx.y == 0 && threadIdx.x == 0) {
+    lists[m.list].base = m.dst;
+    lists[m.list].cap = m.cap;
+  }
 }
 
-__global__ __launch_bounds__(256) void k_serv_region(const ServReq* reqs, const ListDev* lists,
-                                                     const long long* frontier, Tree* trees) {
-  __shared__ long long lds[4 * 10];
+// A workgroup per tree (a query's region, then its session's global region),
+// eight threads per resource (level and end). Trees, the step's control words
+// and the queries' error flags go straight to page-locked memory.
+__global__ __launch_bounds__(1024) void k_serv_region(const ServReq* reqs, int n_reqs, Plan p, const ListDev* lists,
+                                                      const long long* frontier, const ServCtl* ctl, Tree* trees,
+                                                      ServOut* out, unsigned int* out_err) {
+  __shared__ long long lds[16 * 10];
+  __shared__ Tree tree;
+  if (blockIdx.x == 0) {
+    if (threadIdx.x == 0) {
+      out->ts[kTsRegion] = __builtin_amdgcn_s_memrealtime();
+      out->ctl = *ctl;
+      out->slot_over = p.oversized[1];
+    }
+    for (int q = threadIdx.x; q < n_reqs; q += (int)blockDim.x) out_err[q] = p.owner_err[q];
+  }
   const ServReq q = reqs[blockIdx.x >> 1];
   const bool global = blockIdx.x & 1;
   const long long t0 = global ? q.origin : q.t0;
@@ -307,33 +377,21 @@ __global__ __launch_bounds__(256) void k_serv_region(const ServReq* reqs, const 
   if (t1 <= t0) t1 = t0 + 1;  // an empty session: a one-ns global region
   const long long E = t1 - t0;
   const int R = q.n_hosts + q.n_devices;
-  long long sU = 0, sW = 0, sMPI = 0, sO = 0, sK = 0, sM = 0, mUW = 0, mK = 0, mKM = 0;
-  for (int r = threadIdx.x; r < R; r += 256) {
+  const int l = (threadIdx.x >> 1) & 3, ep = threadIdx.x & 1;
+  long long v[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+  for (int r0 = 0; r0 < R; r0 += (int)(blockDim.x >> 3)) {
+    const int r = r0 + (int)(threadIdx.x >> 3);
     const bool host = r < q.n_hosts;
-    const int nl = host ? 3 : 2;
-    long long D[3] = {0, 0, 0};
-    for (int l = 0; l < nl; ++l) {
-      const ListDev L = lists[q.list_begin + r * 3 + l];
-      D[l] = list_measure(L, t1) - list_measure(L, t0);
-    }
-    if (host) {
-      const long long u = D[0], w = D[1] - D[0];
-      sU += u;
-      sW += w;
-      sMPI += D[2] - D[1];
-      sO += E - D[2];
-      mUW = u + w > mUW ? u + w : mUW;
-    } else {
-      const long long k = D[0], m = D[1] - D[0];
-      sK += k;
-      sM += m;
-      mK = k > mK ? k : mK;
-      mKM = k + m > mKM ? k + m : mKM;
-    }
+    long long M = 0, D[3], times[4];
+    if (r < R && l < (host ? 3 : 2)) M = list_measure(lists[q.list_begin + r * 3 + l], ep ? t1 : t0);
+    group_levels(M, D);
+    if ((threadIdx.x & 7) == 0 && r < R) add_times(host, D, E, times, v);
   }
-  long long v[9] = {sU, sW, sMPI, sO, sK, sM, mUW, mK, mKM};
   block_tree(v, lds);
-  if (threadIdx.x == 0) trees[blockIdx.x] = make_tree(E, q.n_hosts, q.n_devices, v);
+  if (threadIdx.x == 0) tree = make_tree(E, q.n_hosts, q.n_devices, v);
+  __syncthreads();
+  put_trees(&tree, 1, trees + blockIdx.x);
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out->ts[kTsEnd] = __builtin_amdgcn_s_memrealtime();
 }
 
 }  // namespace hpop
@@ -512,10 +570,14 @@ struct hpop_server {
   long long inflight_bytes = 0;
   // device buffers of a step
   Engine engine;  // the bucketed build of each step's records
-  DevBuf d_lists, d_items, d_reqs, d_pool, d_frontier, d_ctl, d_trees, d_stage, d_moves;
+  DevBuf d_lists;  // every list's ListDev, kept by the kernels; uploaded again after a session opened
+  size_t d_lists_n = 0;  // lists in it
+  DevBuf d_pool, d_frontier, d_stage;
   DevBuf heap;  // every session list, Comp entries; bump-allocated, compacted when full
   long long heap_cap = 0, heap_used = 0;
-  PinnedBuf h_out;
+  PinnedBuf h_out;   // a step's results, stored there by its kernels
+  PinnedBuf h_lists; // upload of d_lists
+  double us_per_tick = 0.01;  // of the device clock
   HostArena staging;  // host payloads of queued queries
   long long pool_cap = 0;
   // statistics
@@ -527,7 +589,7 @@ struct hpop_server {
   double max_phase_us[5] = {0, 0, 0, 0, 0};  // h2d, move, build, splice, region
   double sum_phase_us[5] = {0, 0, 0, 0, 0};
   double sum_prep_us = 0.0, sum_grow_us = 0.0, sum_wait_us = 0.0;
-  hipEvent_t ev[6] = {};
+  hipEvent_t ev[2] = {};  // around the host payload copies
   bool have_events = false;
   double step_prep_us = 0.0, step_wait_us = 0.0;  // of the step just run (set by run_step)
   // longest single runtime call of the step's enqueueing, and its site (set by run_step)
@@ -553,6 +615,10 @@ bool ensure(DevBuf& b, Alloc& a, size_t bytes) { return b.reserve(a, bytes, fals
 
 // Runs one device step over `batch` (queries of distinct sessions). Returns a
 // status for the whole step; per-query failures are stored in the queries.
+// Everything the step's kernels need goes up in one copy with the build's
+// descriptors, and they store its results in page-locked memory: five
+// launches, one copy and one wait (a step took 13 launches, about 17 copies
+// and 11 event calls, most of its time on the host).
 hpop_status run_step(hpop_server* S, std::vector<Query*>& batch, std::string& err) {
   Alloc& A = S->alloc;
   Engine& En = S->engine;
@@ -573,8 +639,8 @@ hpop_status run_step(hpop_server* S, std::vector<Query*>& batch, std::string& er
   std::vector<long long> seg_count;
   std::vector<char> seg_host;
   std::vector<ServItem> items;
+  std::vector<std::array<long long, 3>> level_new;  // per item: records of each level
   std::vector<ServReq> reqs(nq);
-  std::vector<long long> level_new(S->lists.size(), 0);
   size_t hoff = 0;
   const auto t_start = std::chrono::steady_clock::now();
   // host time of one runtime call (copies, launches, event records; not the
@@ -589,8 +655,9 @@ hpop_status run_step(hpop_server* S, std::vector<Query*>& batch, std::string& er
     }
     return r;
   };
+  // events only around host payload copies; the kernels note the device clock
   auto mark = [&](int i) {
-    if (S->have_events) (void)timed(HPOP_CALL_EVENT, [&] { return hipEventRecord(S->ev[i], st); });
+    if (host_bytes && S->have_events) (void)timed(HPOP_CALL_EVENT, [&] { return hipEventRecord(S->ev[i], st); });
   };
   mark(0);
   for (int q = 0; q < nq; ++q) {
@@ -618,6 +685,7 @@ hpop_status run_step(hpop_server* S, std::vector<Query*>& batch, std::string& er
     for (const hpop_event_chunk& ch : Q->chunks) {
       if (ch.count == 0) continue;
       int& sg = seg_of_res[ch.resource];
+      const int nlev = ch.resource < ss.n_hosts ? 3 : 2;
       if (sg < 0) {
         sg = (int)seg_count.size();
         seg_count.push_back(0);
@@ -626,9 +694,10 @@ hpop_status run_step(hpop_server* S, std::vector<Query*>& batch, std::string& er
         it.req = q;
         it.seg = sg;
         it.list0 = ss.list_begin + ch.resource * 3;
-        it.nlev = ch.resource < ss.n_hosts ? 3 : 2;
+        it.nlev = nlev;
         it.sid = Q->sid;
         items.push_back(it);
+        level_new.push_back({0, 0, 0});
       }
       ChunkDesc d;
       if (Q->mem_space == HPOP_MEM_HOST) {
@@ -646,205 +715,210 @@ hpop_status run_step(hpop_server* S, std::vector<Query*>& batch, std::string& er
       d.owner = q;
       En.h_chunks.push_back(d);
       seg_count[sg] += ch.count;
-      const int nlev = ch.resource < ss.n_hosts ? 3 : 2;
-      for (int l = d.slot; l < nlev; ++l) level_new[ss.list_begin + ch.resource * 3 + l] += ch.count;
+      for (int l = d.slot; l < nlev; ++l) level_new[sg][l] += ch.count;  // item index = segment index
     }
   }
   mark(1);  // payload copies
-  hpop_tuning tun{};
-  hpop_status rc = En.assemble_plan(tun, seg_count, seg_host, std::max(1, nq), 0, err);
-  if (rc != HPOP_OK) return rc;
   // ---- list capacity: a list grows by at most its level's new records. A list
   // that outgrows its place moves to the end of the heap (at least doubling);
   // when the heap is full, every list moves into a new heap four times the live
   // size. All moves of a step are one kernel; the host tables change only
   // once it is enqueued.
   const size_t nl = S->lists.size();
-  std::vector<long long> n_off(nl), n_cap(nl);
+  const int ni = (int)items.size();
+  struct Place {
+    size_t list;
+    long long off, cap;
+  };
+  std::vector<Place> grown;
   long long grow = 0;
-  for (size_t i = 0; i < nl; ++i) {
-    const ListHost& L = S->lists[i];
-    n_off[i] = L.off;
-    n_cap[i] = L.cap;
-    if (!level_new[i]) continue;
-    const long long need = L.len + level_new[i] + 1;
-    if (need <= L.cap) continue;
-    n_cap[i] = (std::max({need, 2 * L.cap, 1024ll}) + 63) & ~63ll;
-    n_off[i] = -1;  // placed below
-    grow += n_cap[i];
-  }
+  for (int i = 0; i < ni; ++i)
+    for (int l = 0; l < items[i].nlev; ++l) {
+      if (!level_new[i][l]) continue;
+      const size_t at = (size_t)items[i].list0 + l;
+      const ListHost& L = S->lists[at];
+      const long long need = L.len + level_new[i][l] + 1;
+      if (need <= L.cap) continue;
+      grown.push_back({at, 0, (std::max({need, 2 * L.cap, 1024ll}) + 63) & ~63ll});
+      grow += grown.back().cap;
+    }
   std::vector<ListMove> moves;
   DevBuf new_heap;
   long long new_heap_cap = S->heap_cap, new_used = S->heap_used;
   if (grow) {
     Comp* old_base = (Comp*)S->heap.ptr;
-    if (S->heap_used + grow <= S->heap_cap) {
-      for (size_t i = 0; i < nl; ++i)
-        if (n_off[i] < 0) {
-          n_off[i] = new_used;
-          new_used += n_cap[i];
-          if (S->lists[i].len) moves.push_back({old_base + S->lists[i].off, old_base + n_off[i], S->lists[i].len});
-        }
-    } else {
+    Comp* base = old_base;
+    if (S->heap_used + grow > S->heap_cap) {
+      // every list, the grown ones at their new size
+      std::vector<Place> all(nl);
+      for (size_t i = 0; i < nl; ++i) all[i] = {i, 0, S->lists[i].cap};
+      for (const Place& g : grown) all[g.list].cap = g.cap;
+      grown.swap(all);
       long long live = 0;
-      for (size_t i = 0; i < nl; ++i) live += n_cap[i];
+      for (const Place& g : grown) live += g.cap;
       new_heap_cap = std::max(4 * live, 1ll << 16);  // 4x: few compactions while sessions grow
       if (!new_heap.reserve(A, (size_t)new_heap_cap * sizeof(Comp), false)) {
         err = "device allocation for the session lists failed";
         return HPOP_E_OOM;
       }
-      Comp* nb = (Comp*)new_heap.ptr;
+      base = (Comp*)new_heap.ptr;
       new_used = 0;
-      for (size_t i = 0; i < nl; ++i) {
-        if (S->lists[i].len) moves.push_back({old_base + S->lists[i].off, nb + new_used, S->lists[i].len});
-        n_off[i] = new_used;
-        new_used += n_cap[i];
+    }
+    for (Place& g : grown) {
+      g.off = new_used;
+      new_used += g.cap;
+      const ListHost& L = S->lists[g.list];
+      moves.push_back({old_base + L.off, base + g.off, L.len, g.cap, (long long)g.list});
+    }
+  }
+  // ---- the build's plan, with the step's tables behind its descriptors
+  auto pad = [](size_t n) { return (n + 63) & ~size_t(63); };
+  const size_t o_items = pad(sizeof(ServCtl)), o_reqs = o_items + pad(items.size() * sizeof(ServItem)),
+               o_moves = o_reqs + pad(reqs.size() * sizeof(ServReq)),
+               n_extra = o_moves + pad(moves.size() * sizeof(ListMove)), b_trees = 2 * (size_t)nq * sizeof(Tree),
+               // results: control words, trees, lists, error flags
+      r_trees = pad(sizeof(ServOut)), r_lists = r_trees + pad(b_trees),
+               r_err = r_lists + pad(3 * (size_t)ni * sizeof(ListOut)), n_out = r_err + pad(4 * (size_t)nq);
+  long long total_rec = 0;
+  for (long long c : seg_count) total_rec += c;
+  const long long want_pool = std::max<long long>(1 << 20, 4 * total_rec + 4096);
+  En.ws.extra_bytes = n_extra;
+  En.h_extra.assign(n_extra, 0);
+  hpop_tuning tun{};
+  hpop_status rc = En.assemble_plan(tun, seg_count, seg_host, std::max(1, nq), 0, err);
+  if (rc == HPOP_OK && want_pool > S->pool_cap) {
+    S->d_pool.release(A);
+    S->pool_cap = 0;
+    if (ensure(S->d_pool, A, (size_t)want_pool * sizeof(Elem))) {
+      S->pool_cap = (long long)(S->d_pool.bytes / sizeof(Elem));
+    } else {
+      err = "scratch pool allocation failed";
+      rc = HPOP_E_OOM;
+    }
+  }
+  if (rc == HPOP_OK && !S->h_out.reserve(n_out)) {
+    err = "pinned host allocation failed";
+    rc = HPOP_E_OOM;
+  }
+  if (rc == HPOP_OK && S->d_lists_n != nl) {
+    // a session opened: the whole table again, from the host's
+    if (!ensure(S->d_lists, A, nl * sizeof(ListDev) + 64) || !S->h_lists.reserve(nl * sizeof(ListDev) + 64)) {
+      err = "device allocation for a serving step failed";
+      rc = HPOP_E_OOM;
+    } else {
+      ListDev* h = (ListDev*)S->h_lists.ptr;
+      for (size_t i = 0; i < nl; ++i)
+        h[i] = ListDev{(Comp*)S->heap.ptr + S->lists[i].off, S->lists[i].len, S->lists[i].total, S->lists[i].cap};
+      const hipError_t e = timed(HPOP_CALL_TABLES, [&] {
+        return hipMemcpyAsync(S->d_lists.ptr, h, nl * sizeof(ListDev), hipMemcpyHostToDevice, st);
+      });
+      if (e != hipSuccess) {
+        err = std::string("list table: ") + hipGetErrorString(e);
+        rc = HPOP_E_HIP;
+      } else {
+        S->d_lists_n = nl;
       }
     }
   }
-  if (!moves.empty() && !ensure(S->d_moves, A, moves.size() * sizeof(ListMove) + 64)) {
+  if (rc != HPOP_OK) {
     new_heap.release(A);
-    err = "device allocation for a serving step failed";
-    return HPOP_E_OOM;
+    return rc;
   }
-  Comp* heap_base = (Comp*)(new_heap.ptr ? new_heap.ptr : S->heap.ptr);
-  std::vector<ListDev> ld(nl);
-  for (size_t i = 0; i < nl; ++i) {
-    ld[i].base = heap_base + n_off[i];
-    ld[i].len = S->lists[i].len;
-    ld[i].total = S->lists[i].total;
-    ld[i].cap = n_cap[i];
-  }
-  const int ni = (int)items.size();
-  const size_t b_lists = ld.size() * sizeof(ListDev), b_items = items.size() * sizeof(ServItem),
-               b_reqs = reqs.size() * sizeof(ServReq), b_trees = 2 * (size_t)nq * sizeof(Tree),
-               b_moves = moves.size() * sizeof(ListMove);
-  if (!ensure(S->d_lists, A, b_lists + 64) || !ensure(S->d_items, A, b_items + 64) ||
-      !ensure(S->d_reqs, A, b_reqs + 64) || !ensure(S->d_ctl, A, sizeof(ServCtl)) ||
-      !ensure(S->d_trees, A, b_trees + 64) ||
-      // pinned layout: lists, items, requests, moves (uploads), then control, trees, lists, error flags
-      !S->h_out.reserve(b_lists + b_items + b_reqs + b_moves + sizeof(ServCtl) + b_trees + b_lists + 4 * (size_t)nq +
-                        256)) {
-    new_heap.release(A);
-    err = "device allocation for a serving step failed";
-    return HPOP_E_OOM;
-  }
-  // ---- list moves, then the new placement becomes the server's
-  if (!moves.empty()) {
-    char* hm = (char*)S->h_out.ptr + b_lists + b_items + b_reqs;
-    memcpy(hm, moves.data(), b_moves);
-    hipError_t e = timed(HPOP_CALL_MOVE, [&] {
-      hipError_t r = hipMemcpyAsync(S->d_moves.ptr, hm, b_moves, hipMemcpyHostToDevice, st);
-      if (r == hipSuccess) {
-        hipLaunchKernelGGL(k_list_move, dim3((unsigned)moves.size(), 8), dim3(256), 0, st,
-                           (const ListMove*)S->d_moves.ptr);
-        r = hipGetLastError();
-      }
-      return r;
+  char* const hout = (char*)S->h_out.ptr;
+  ServOut* const out = (ServOut*)hout;
+  memset(out, 0, sizeof *out);
+  ListOut* const lo = (ListOut*)(hout + r_lists);
+  for (int i = 0; i < 3 * ni; ++i) lo[i].len = -1;
+  En.ws.plan.ts = out->ts;
+  const ServCtl ctl{0, (unsigned long long)S->pool_cap, 0, 0};
+  memcpy(En.h_extra.data(), &ctl, sizeof ctl);
+  if (ni) memcpy(En.h_extra.data() + o_items, items.data(), items.size() * sizeof(ServItem));
+  memcpy(En.h_extra.data() + o_reqs, reqs.data(), reqs.size() * sizeof(ServReq));
+  if (!moves.empty()) memcpy(En.h_extra.data() + o_moves, moves.data(), moves.size() * sizeof(ListMove));
+  char* const dx = En.ws.d_extra;
+  ServCtl* const d_ctl = (ServCtl*)dx;
+  ServItem* const d_items = (ServItem*)(dx + o_items);
+  const ServReq* const d_reqs = (const ServReq*)(dx + o_reqs);
+  ListDev* const d_lists = (ListDev*)S->d_lists.ptr;
+  // ---- the upload and the list moves, then the new placement becomes the server's
+  (void)timed(HPOP_CALL_BUILD, [&] {
+    rc = En.upload(err);
+    return hipSuccess;
+  });
+  if (rc == HPOP_OK && !moves.empty()) {
+    const hipError_t e = timed(HPOP_CALL_MOVE, [&] {
+      hipLaunchKernelGGL(k_list_move, dim3((unsigned)moves.size(), 8), dim3(256), 0, st,
+                         (const ListMove*)(dx + o_moves), d_lists, out->ts);
+      return hipGetLastError();
     });
     if (e != hipSuccess) {
-      (void)hipStreamSynchronize(st);
-      new_heap.release(A);
       err = std::string("list move: ") + hipGetErrorString(e);
-      return HPOP_E_HIP;
+      rc = HPOP_E_HIP;
     }
   }
-  mark(2);  // list moves
+  if (rc != HPOP_OK) {
+    (void)hipStreamSynchronize(st);
+    new_heap.release(A);
+    return rc;
+  }
   if (new_heap.ptr) {
     S->heap.release(A);  // stream-ordered: after the moves out of it
     S->heap = new_heap;
     S->heap_cap = new_heap_cap;
   }
   S->heap_used = new_used;
-  for (size_t i = 0; i < nl; ++i) {
-    S->lists[i].off = n_off[i];
-    S->lists[i].cap = n_cap[i];
-  }
-  long long total_rec = 0;
-  for (long long c : seg_count) total_rec += c;
-  const long long want_pool = std::max<long long>(1 << 20, 4 * total_rec + 4096);
-  if (want_pool > S->pool_cap) {
-    S->d_pool.release(A);
-    if (!ensure(S->d_pool, A, (size_t)want_pool * sizeof(Elem))) {
-      err = "scratch pool allocation failed";
-      return HPOP_E_OOM;
-    }
-    S->pool_cap = (long long)(S->d_pool.bytes / sizeof(Elem));
+  for (const Place& g : grown) {
+    S->lists[g.list].off = g.off;
+    S->lists[g.list].cap = g.cap;
   }
   // ---- the build of the step's records (no regions: the trees come from the lists)
-  if (!En.ws.pinned.reserve(64)) {
-    err = "pinned host allocation failed";
-    return HPOP_E_OOM;
-  }
   (void)timed(HPOP_CALL_BUILD, [&] {
-    rc = En.upload(err);
-    if (rc == HPOP_OK) rc = En.enqueue(true, false, err);
+    rc = En.enqueue(true, false, err);
     return hipSuccess;
   });
   if (rc != HPOP_OK) return rc;
-  mark(3);  // build of the new records
-  char* h = (char*)S->h_out.ptr;
-  memcpy(h, ld.data(), b_lists);
-  memcpy(h + b_lists, items.data(), b_items);
-  memcpy(h + b_lists + b_items, reqs.data(), b_reqs);
-  char* hres = h + b_lists + b_items + b_reqs + b_moves;
-  hipError_t e = timed(HPOP_CALL_TABLES, [&] {
-    hipError_t r = hipSuccess;
-    if (b_lists) r = hipMemcpyAsync(S->d_lists.ptr, h, b_lists, hipMemcpyHostToDevice, st);
-    if (r == hipSuccess && b_items) r = hipMemcpyAsync(S->d_items.ptr, h + b_lists, b_items, hipMemcpyHostToDevice, st);
-    if (r == hipSuccess) r = hipMemcpyAsync(S->d_reqs.ptr, h + b_lists + b_items, b_reqs, hipMemcpyHostToDevice, st);
-    return r;
-  });
-  if (e != hipSuccess) return err = hipGetErrorString(e), HPOP_E_HIP;
   const Plan& P = En.ws.plan;
-  char* o = hres + sizeof(ServCtl);  // results: trees, lists, error flags
+  int max_res = 1;
+  for (const ServReq& r : reqs) max_res = std::max(max_res, r.n_hosts + r.n_devices);
+  const unsigned region_threads = (unsigned)std::min(1024, (8 * max_res + 63) & ~63);
   // one synchronisation per step: the scratch check travels back with the results
   for (int attempt = 0; attempt < 4; ++attempt) {
-    ServCtl ctl{0, (unsigned long long)S->pool_cap, 0, 0};
-    memcpy(hres, &ctl, sizeof ctl);
-    e = timed(HPOP_CALL_CONTROL,
-              [&] { return hipMemcpyAsync(S->d_ctl.ptr, hres, sizeof ctl, hipMemcpyHostToDevice, st); });
-    if (e != hipSuccess) return err = hipGetErrorString(e), HPOP_E_HIP;
+    hipError_t e = hipSuccess;
+    if (attempt > 0) {
+      const ServCtl again{0, (unsigned long long)S->pool_cap, 0, 0};
+      out->ctl = again;
+      e = timed(HPOP_CALL_CONTROL,
+                [&] { return hipMemcpyAsync(d_ctl, &out->ctl, sizeof again, hipMemcpyHostToDevice, st); });
+      if (e != hipSuccess) return err = hipGetErrorString(e), HPOP_E_HIP;
+    }
     if (ni > 0) {
       (void)timed(HPOP_CALL_SPLICE, [&] {
-        hipLaunchKernelGGL(k_serv_prep, dim3((unsigned)((3 * ni + 63) / 64)), dim3(64), 0, st,
-                           (ServItem*)S->d_items.ptr, ni, P, (const ListDev*)S->d_lists.ptr,
-                           (long long*)S->d_frontier.ptr, (ServCtl*)S->d_ctl.ptr);
+        hipLaunchKernelGGL(k_serv_prep, dim3((unsigned)((3 * ni + 3) / 4)), dim3(256), 0, st, d_items, ni, P,
+                           (const ListDev*)d_lists, (long long*)S->d_frontier.ptr, d_ctl);
         hipLaunchKernelGGL(k_serv_splice, dim3((unsigned)(3 * ni)), dim3(kServThreads), 0, st,
-                           (const ServItem*)S->d_items.ptr, P, (ListDev*)S->d_lists.ptr, (Elem*)S->d_pool.ptr,
-                           (const ServCtl*)S->d_ctl.ptr);
+                           (const ServItem*)d_items, P, d_lists, (Elem*)S->d_pool.ptr, (const ServCtl*)d_ctl, lo);
         return hipSuccess;
       });
     }
-    mark(4);  // prep and splice
     // on a scratch overflow no list was written and these trees are discarded
     e = timed(HPOP_CALL_REGION, [&] {
-      hipLaunchKernelGGL(k_serv_region, dim3((unsigned)(2 * nq)), dim3(256), 0, st, (const ServReq*)S->d_reqs.ptr,
-                         (const ListDev*)S->d_lists.ptr, (const long long*)S->d_frontier.ptr, (Tree*)S->d_trees.ptr);
+      hipLaunchKernelGGL(k_serv_region, dim3((unsigned)(2 * nq)), dim3(region_threads), 0, st, d_reqs, nq, P,
+                         (const ListDev*)d_lists, (const long long*)S->d_frontier.ptr, (const ServCtl*)d_ctl,
+                         (Tree*)(hout + r_trees), out, (unsigned int*)(hout + r_err));
       return hipGetLastError();
     });
-    if (e == hipSuccess)
-      e = timed(HPOP_CALL_RESULTS, [&] {
-        hipError_t r = hipMemcpyAsync(hres, S->d_ctl.ptr, sizeof(ServCtl), hipMemcpyDeviceToHost, st);
-        if (r == hipSuccess) r = hipMemcpyAsync(o, S->d_trees.ptr, b_trees, hipMemcpyDeviceToHost, st);
-        if (r == hipSuccess && b_lists)
-          r = hipMemcpyAsync(o + b_trees, S->d_lists.ptr, b_lists, hipMemcpyDeviceToHost, st);
-        if (r == hipSuccess) r = hipMemcpyAsync(o + b_trees + b_lists, P.owner_err, nq * 4, hipMemcpyDeviceToHost, st);
-        return r;
-      });
-    mark(5);  // region trees and result copies
     const auto t_sync = std::chrono::steady_clock::now();
     if (attempt == 0) S->step_prep_us = std::chrono::duration<double, std::micro>(t_sync - t_start).count();
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     S->step_wait_us +=
         std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now() - t_sync).count();
     if (e != hipSuccess) return err = std::string("serving step: ") + hipGetErrorString(e), HPOP_E_HIP;
-    ServCtl got;
-    memcpy(&got, hres, sizeof got);
+    const ServCtl got = out->ctl;
     if (!got.pool_overflow) break;
     // a long overlap needed more scratch: grow the pool and redo prep, splice and region
     const long long np = (long long)(got.pool_used + got.pool_overflow + 4096) * 2;
     S->d_pool.release(A);
+    S->pool_cap = 0;
     if (!ensure(S->d_pool, A, (size_t)np * sizeof(Elem))) {
       err = "scratch pool allocation failed";
       return HPOP_E_OOM;
@@ -855,38 +929,47 @@ hpop_status run_step(hpop_server* S, std::vector<Query*>& batch, std::string& er
       return HPOP_E_OOM;
     }
   }
-  if (S->have_events) {
-    for (int i = 0; i < 5; ++i) {
-      float ms = 0.f;
-      if (hipEventElapsedTime(&ms, S->ev[i], S->ev[i + 1]) == hipSuccess) {
-        S->max_phase_us[i] = std::max(S->max_phase_us[i], 1e3 * (double)ms);
-        S->sum_phase_us[i] += 1e3 * (double)ms;
-      }
-    }
+  // phases by the device clock, each up to the next one's first kernel; the
+  // payload copies by events
+  double us[5] = {0, 0, 0, 0, 0};
+  const unsigned long long* ts = out->ts;
+  float ms = 0.f;
+  if (host_bytes && S->have_events && hipEventElapsedTime(&ms, S->ev[0], S->ev[1]) == hipSuccess) us[0] = 1e3 * ms;
+  auto span = [&](int from, int to) {
+    return ts[from] && ts[to] > ts[from] ? S->us_per_tick * (double)(ts[to] - ts[from]) : 0.0;
+  };
+  const int after_build = ni > 0 ? kTsSplice : kTsRegion;
+  us[1] = span(kTsMove, kTsBuild);
+  us[2] = span(kTsBuild, after_build);
+  us[3] = span(kTsSplice, kTsRegion);
+  us[4] = span(kTsRegion, kTsEnd);
+  for (int i = 0; i < 5; ++i) {
+    S->max_phase_us[i] = std::max(S->max_phase_us[i], us[i]);
+    S->sum_phase_us[i] += us[i];
   }
-  unsigned long long slot_over;
-  memcpy(&slot_over, (const char*)En.ws.pinned.ptr + 16, 8);
-  if (slot_over && !En.exact_forced) {
+  if (out->slot_over && !En.exact_forced) {
     // a bucket outgrew its scatter slots: no list was touched; redo with exact counts
     En.exact_forced = true;
     rc = run_step(S, batch, err);
     En.exact_forced = false;
     return rc;
   }
-  const ListDev* lo = (const ListDev*)(o + b_trees);
-  for (size_t i = 0; i < S->lists.size(); ++i) {
-    S->lists[i].len = lo[i].len;
-    S->lists[i].total = lo[i].total;
-  }
-  const unsigned int* re = (const unsigned int*)(o + b_trees + b_lists);
+  for (int i = 0; i < ni; ++i)
+    for (int l = 0; l < 3; ++l)
+      if (lo[3 * i + l].len >= 0) {
+        ListHost& L = S->lists[(size_t)items[i].list0 + l];
+        L.len = lo[3 * i + l].len;
+        L.total = lo[3 * i + l].total;
+      }
+  const unsigned int* re = (const unsigned int*)(hout + r_err);
   for (int q = 0; q < nq; ++q) {
     Query* Q = batch[q];
     if (re[q]) {
       Q->status = HPOP_E_BAD_INTERVAL;
       Q->error = "a record of this query violates 0 <= start <= end < 2^62; the query was not applied";
     } else {
-      memcpy(&Q->region, o + (2 * q) * sizeof(Tree), sizeof(Tree));
-      memcpy(&Q->global, o + (2 * q + 1) * sizeof(Tree), sizeof(Tree));
+      memcpy(&Q->region, hout + r_trees + (2 * q) * sizeof(Tree), sizeof(Tree));
+      memcpy(&Q->global, hout + r_trees + (2 * q + 1) * sizeof(Tree), sizeof(Tree));
     }
   }
   return HPOP_OK;
@@ -1016,6 +1099,10 @@ hpop_status hpop_server_create(const hpop_server_config* cfg, hpop_server** out)
       delete S;
       return srv_fail(nullptr, HPOP_E_OOM, "page-locked staging allocation failed");
     }
+    int khz = 0;
+    if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, S->device) == hipSuccess && khz > 0)
+      S->us_per_tick = 1e3 / (double)khz;
+    (void)hipGetLastError();
     S->have_events = true;
     for (hipEvent_t& e : S->ev)
       if (hipEventCreate(&e) != hipSuccess) S->have_events = false;
@@ -1055,13 +1142,12 @@ hpop_status hpop_server_destroy(hpop_server* S) {
   (void)hipStreamSynchronize(S->stream);
   S->heap.release(S->alloc);
   S->engine.release();
-  for (DevBuf* b : {&S->d_lists, &S->d_items, &S->d_reqs, &S->d_pool, &S->d_frontier, &S->d_ctl, &S->d_trees,
-                    &S->d_stage, &S->d_moves})
-    b->release(S->alloc);
+  for (DevBuf* b : {&S->d_lists, &S->d_pool, &S->d_frontier, &S->d_stage}) b->release(S->alloc);
   S->staging.release();
   for (hipEvent_t e : S->ev)
     if (e) (void)hipEventDestroy(e);
   S->h_out.release();
+  S->h_lists.release();
   (void)hipStreamSynchronize(S->stream);
   (void)hipStreamDestroy(S->stream);
   for (auto& kv : S->tickets) delete kv.second;
