@@ -228,33 +228,71 @@ __device__ __forceinline__ long long wave_reduce_i64(long long x, long long id) 
   return total;
 }
 
-// Block-wide exclusive scan of K int64 lanes per thread (thread order), with totals.
+// The code below runs on groups of THREADS threads: a workgroup, or with 64 one
+// wave of any workgroup (its waves then work apart from one another).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+template <int THREADS>
+__device__ __forceinline__ int group_thread() {
+  return THREADS == 64 ? (int)(threadIdx.x & 63) : (int)threadIdx.x;
+}
+template <int THREADS>
+__device__ __forceinline__ int group_wave() {
+  return THREADS == 64 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+}
+template <int THREADS>
+__device__ __forceinline__ void group_sync() {
+  if (THREADS == 64) wave_sync();
+  else __syncthreads();
+}
+template <int THREADS>
+__device__ __forceinline__ bool group_any(bool x) {
+  if (THREADS == 64) {
+    wave_sync();
+    return __ballot(x) != 0;
+  }
+  return __syncthreads_or(x);
+}
+
+// Group-wide exclusive scan of K int64 lanes per thread (thread order), with totals.
 // `lds` holds NW*K int64. Contains barriers: call from uniform control flow.
 template <int THREADS, int K, class Op>
 __device__ __forceinline__ void block_excl_scan(const long long (&v)[K], long long (&excl)[K],
                                                 long long (&total)[K], long long ident, long long* lds) {
   constexpr int NW = THREADS / 64;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  static_assert(NW <= 16, "the waves' totals are scanned within a row of 16 lanes");
+  const int lane = threadIdx.x & 63, wave = group_wave<THREADS>();
   long long ex[K];
 #pragma unroll
   for (int k = 0; k < K; ++k) {
     long long tot;
     ex[k] = wave_excl_scan_dpp<Op>(v[k], ident, tot);
-    if (lane == 0) lds[wave * K + k] = tot;
+    if constexpr (NW == 1) {
+      excl[k] = ex[k];
+      total[k] = tot;
+    } else if (lane == 0) {
+      lds[wave * K + k] = tot;
+    }
   }
-  __syncthreads();
+  if constexpr (NW == 1) return;
+  group_sync<THREADS>();
 #pragma unroll
   for (int k = 0; k < K; ++k) {
-    long long pre = ident, tot = ident;
-    for (int w = 0; w < NW; ++w) {
-      const long long t = lds[w * K + k];
-      if (w < wave) pre = Op::apply(pre, t);
-      tot = Op::apply(tot, t);
-    }
+    // lane w holds wave w's total: scanned across lanes, as reading all of them
+    // in every thread takes 2 NW K registers (and spills)
+    long long t = lane < NW ? lds[lane * K + k] : ident;
+    if (NW > 1) t = Op::apply(t, dpp64<kDppRowShr1, 0xf, 0xf>(ident, t));
+    if (NW > 2) t = Op::apply(t, dpp64<kDppRowShr2, 0xf, 0xf>(ident, t));
+    if (NW > 4) t = Op::apply(t, dpp64<kDppRowShr4, 0xf, 0xf>(ident, t));
+    if (NW > 8) t = Op::apply(t, dpp64<kDppRowShr8, 0xf, 0xf>(ident, t));
+    const long long pre = wave > 0 ? readlane64(t, wave - 1) : ident;
     excl[k] = Op::apply(pre, ex[k]);
-    total[k] = tot;
+    total[k] = readlane64(t, NW - 1);
   }
-  __syncthreads();
+  group_sync<THREADS>();
 }
 
 // One stable LSD pass on 8 bits of (start - lo) >> sh over the positions
@@ -336,26 +374,37 @@ struct FlatState {
   long long R[3];  // components written in this bucket
 };
 
-// Flatten one sorted tile: positions 0..n-1 in order ord (or identity).
-// Writes components of each level at comp[l][off + R], or in the narrow form
-// relative to `nlo` at compn[l][off + R] when compn is given; advances `st`.
-template <int THREADS>
+// Flatten one sorted tile of n <= THREADS * MAXI records: positions 0..n-1 in
+// order ord (or identity). Writes components of each level at comp[l][R], or in
+// the narrow form relative to `nlo` at compn[l][R] when compn is given;
+// advances `st`. A thread's records are read once, into registers (the three
+// sweeps read each of them from LDS through ord before, one after another).
+template <int THREADS, int MAXI>
 __device__ __forceinline__ void flatten_tile(const Elem* E, const unsigned short* ord, int n, int nlev,
-                                             long long off, Comp* const* comp, CompN* const* compn, long long nlo,
-                                             FlatState& st, long long* lds_scan, long long* lds_bc) {
+                                             Comp* const* comp, CompN* const* compn, long long nlo, FlatState& st,
+                                             long long* lds_scan) {
   const int ipt = (n + THREADS - 1) / THREADS;
-  const int p0 = threadIdx.x * ipt;
-  const int p1 = min(n, p0 + ipt);
-  const long long EMASK = (1ll << kSlotShift) - 1;
+  const int p0 = group_thread<THREADS>() * ipt;
+  constexpr long long EMASK = (1ll << kSlotShift) - 1;
+  // past the tile: a record of no level
+  long long s[MAXI], e[MAXI];
+  int slot[MAXI];
+#pragma unroll
+  for (int j = 0; j < MAXI; ++j) {
+    const int q = p0 + j;
+    const bool in = j < ipt && q < n;
+    const Elem el = E[in ? (ord ? (int)ord[q] : q) : 0];
+    s[j] = el.s;
+    e[j] = el.e_slot & EMASK;
+    slot[j] = in ? (int)((unsigned long long)el.e_slot >> kSlotShift) : 3;
+  }
   // phase A: exclusive max-scan of ends per level
   long long tmax[3] = {LLONG_MIN, LLONG_MIN, LLONG_MIN};
-  for (int q = p0; q < p1; ++q) {
-    const Elem el = E[ord ? ord[q] : q];
-    const int slot = (int)((unsigned long long)el.e_slot >> kSlotShift);
-    const long long e = el.e_slot & EMASK;
+#pragma unroll
+  for (int j = 0; j < MAXI; ++j) {
 #pragma unroll
     for (int l = 0; l < 3; ++l)
-      if (slot <= l && e > tmax[l]) tmax[l] = e;
+      if (slot[j] <= l && e[j] > tmax[l]) tmax[l] = e[j];
   }
   long long exm[3], totm[3];
   block_excl_scan<THREADS, 3, OpMax>(tmax, exm, totm, LLONG_MIN, lds_scan);
@@ -366,18 +415,15 @@ __device__ __forceinline__ void flatten_tile(const Elem* E, const unsigned short
   long long acc[6] = {0, 0, 0, 0, 0, 0};
   {
     long long Mb[3] = {M[0], M[1], M[2]};
-    for (int q = p0; q < p1; ++q) {
-      const Elem el = E[ord ? ord[q] : q];
-      const int slot = (int)((unsigned long long)el.e_slot >> kSlotShift);
-      const long long e = el.e_slot & EMASK;
-      const long long s = el.s;
+#pragma unroll
+    for (int j = 0; j < MAXI; ++j) {
 #pragma unroll
       for (int l = 0; l < 3; ++l) {
-        if (l < nlev && slot <= l) {
-          const long long lo = s > Mb[l] ? s : Mb[l];
-          if (e > lo) acc[l] += e - lo;
-          if (s > Mb[l]) acc[3 + l] += 1;
-          if (e > Mb[l]) Mb[l] = e;
+        if (l < nlev && slot[j] <= l) {
+          const long long lo = s[j] > Mb[l] ? s[j] : Mb[l];
+          if (e[j] > lo) acc[l] += e[j] - lo;
+          if (s[j] > Mb[l]) acc[3 + l] += 1;
+          if (e[j] > Mb[l]) Mb[l] = e[j];
         }
       }
     }
@@ -385,39 +431,29 @@ __device__ __forceinline__ void flatten_tile(const Elem* E, const unsigned short
   long long exa[6], tota[6];
   block_excl_scan<THREADS, 6, OpSum>(acc, exa, tota, 0, lds_scan);
   // phase C: write components
-  {
-    long long P[3], R[3];
 #pragma unroll
-    for (int l = 0; l < 3; ++l) {
-      P[l] = st.P[l] + exa[l];
-      R[l] = st.R[l] + exa[3 + l];
-    }
-    for (int q = p0; q < p1; ++q) {
-      const Elem el = E[ord ? ord[q] : q];
-      const int slot = (int)((unsigned long long)el.e_slot >> kSlotShift);
-      const long long e = el.e_slot & EMASK;
-      const long long s = el.s;
+  for (int l = 0; l < 3; ++l) {
+    long long P = st.P[l] + exa[l], R = st.R[l] + exa[3 + l], Ml = M[l];
 #pragma unroll
-      for (int l = 0; l < 3; ++l) {
-        if (l < nlev && slot <= l) {
-          if (s > M[l]) {
-            if (compn) {
-              CompN c;
-              c.cs = (uint32_t)(s - nlo);
-              c.pl = (uint32_t)P[l];
-              compn[l][off + R[l]] = c;
-            } else {
-              Comp c;
-              c.cs = s;
-              c.pl = P[l];
-              comp[l][off + R[l]] = c;
-            }
-            R[l] += 1;
+    for (int j = 0; j < MAXI; ++j) {
+      if (l < nlev && slot[j] <= l) {
+        if (s[j] > Ml) {
+          if (compn) {
+            CompN c;
+            c.cs = (uint32_t)(s[j] - nlo);
+            c.pl = (uint32_t)P;
+            compn[l][R] = c;
+          } else {
+            Comp c;
+            c.cs = s[j];
+            c.pl = P;
+            comp[l][R] = c;
           }
-          const long long lo = s > M[l] ? s : M[l];
-          if (e > lo) P[l] += e - lo;
-          if (e > M[l]) M[l] = e;
+          R += 1;
         }
+        const long long lo = s[j] > Ml ? s[j] : Ml;
+        if (e[j] > lo) P += e[j] - lo;
+        if (e[j] > Ml) Ml = e[j];
       }
     }
   }
@@ -427,7 +463,6 @@ __device__ __forceinline__ void flatten_tile(const Elem* E, const unsigned short
     st.P[l] += tota[l];
     st.R[l] += tota[3 + l];
   }
-  (void)lds_bc;
 }
 
 __device__ __forceinline__ double ratio(long long num, long long den, int bit, unsigned int& mask) {
@@ -446,9 +481,9 @@ struct SortSmem {
   Elem E[CAP];
   unsigned short ordA[CAP];
   unsigned short ordB[CAP];
-  unsigned int whist[NW * 256];
-  unsigned int dstart[256];
-  unsigned int dcount[256];
+  unsigned int whist[THREADS < 256 ? 1 : NW * 256];  // the radix passes' (a thread per digit)
+  unsigned int dstart[THREADS < 256 ? 1 : 256];
+  unsigned int dcount[THREADS < 256 ? 1 : 256];
   long long lds_scan[NW * 6];
   unsigned long long red[2][NW];
 };
@@ -479,30 +514,193 @@ __device__ __forceinline__ unsigned long long block_vary(unsigned long long kor,
   return kor ^ kand;
 }
 
-// Sort sm.E[0..n) (n <= CAP, already in LDS and visible to the block) by
-// start - lo. Returns the sorted order, or nullptr when E is already in an
-// acceptable order (all starts equal). Only the bits that vary are sorted.
+// Group-wide minimum and maximum of per-thread keys.
+template <int THREADS>
+__device__ __forceinline__ void block_range(unsigned long long& mn, unsigned long long& mx,
+                                            unsigned long long (*red)[THREADS / 64]) {
+  constexpr int NW = THREADS / 64;
+  mn = wave_red_minu(mn);
+  mx = wave_red_maxu(mx);
+  const int lane = threadIdx.x & 63, wave = group_wave<THREADS>();
+  if (lane == 0) {
+    red[0][wave] = mn;
+    red[1][wave] = mx;
+  }
+  group_sync<THREADS>();
+  for (int w = 0; w < NW; ++w) {
+    mn = red[0][w] < mn ? red[0][w] : mn;
+    mx = red[1][w] > mx ? red[1][w] : mx;
+  }
+}
+
+// The place of a key inside its sub-bin of 2^sh keys, as a fraction of 2^32.
+__device__ __forceinline__ unsigned int bin_fraction(unsigned long long key, int sh) {
+  const unsigned long long low = key & ((1ull << sh) - 1ull);
+  return sh >= 32 ? (unsigned int)(low >> (sh - 32)) : (unsigned int)(low << (32 - sh));
+}
+
+// Order of sm.E[0..n) (n <= CAP, already in LDS and visible to the group) by
+// start - lo, in ord: nullptr where E is already in an acceptable order (all
+// starts equal). False, with nothing in ord: a sub-bin is crowded.
+//
+// A counting sort over about one sub-bin per record, between the smallest and
+// the largest start, then an insertion sort in each sub-bin of two or more.
+// Where starts lie in a few places (a sub-bin of more than kBinRefine
+// records) a second count first splits every sub-bin into as many parts as it
+// holds records. A sub-bin that is crowded even then (many equal starts) is
+// left to the radix sort of sort_lds, which alone took five passes of eight
+// barriers for a wide bucket.
+constexpr unsigned int kBinRefine = 8, kBinCrowd = 32;
+
 template <int THREADS, int CAP>
-__device__ const unsigned short* sort_lds(SortSmem<THREADS, CAP>& sm, int n, long long lo) {
+__device__ __forceinline__ bool sort_bins(SortSmem<THREADS, CAP>& sm, int n, long long lo, const unsigned short*& ord) {
   constexpr int MAXR = CAP / THREADS;
-  unsigned long long kor = 0, kand = ~0ull;
-  for (int i = threadIdx.x; i < n; i += THREADS) {
+  const int tid = group_thread<THREADS>();
+  ord = nullptr;
+  unsigned long long mn = ~0ull, mx = 0;
+  for (int i = tid; i < n; i += THREADS) {
     const unsigned long long k = (unsigned long long)(sm.E[i].s - lo);
-    kor |= k;
-    kand &= k;
+    mn = k < mn ? k : mn;
+    mx = k > mx ? k : mx;
   }
-  const unsigned long long vary = block_vary<THREADS>(kor, kand, sm.red);
-  if (!vary) return nullptr;
-  const int lb = __ffsll((long long)vary) - 1;
-  const int hb = bitlen64(vary);
-  const int passes = (hb - lb + 7) >> 3;
-  const unsigned short* in = nullptr;  // identity for the first pass
-  for (int ps = 0; ps < passes; ++ps) {
-    unsigned short* out = (ps & 1) ? sm.ordB : sm.ordA;
-    radix_pass<THREADS, MAXR>(sm.E, in, out, n, lo, lb + 8 * ps, sm.whist, sm.dstart, sm.lds_scan);
-    in = out;
+  block_range<THREADS>(mn, mx, sm.red);
+  if (mn == mx) return true;
+  // 2 THREADS sub-bins at least (a thread scans one word or more), CAP at most
+  int bits = bitlen64(2 * THREADS - 1);
+  while ((1 << bits) < n) ++bits;
+  const int words = 1 << (bits - 1);  // two 16-bit counters (then sub-bin starts) per word
+  const int hb = bitlen64(mx - mn), sh = hb > bits ? hb - bits : 0;
+  unsigned int* bins = (unsigned int*)sm.ordB;
+  auto start_of = [&](unsigned int d) { return (bins[d >> 1] >> (16u * (d & 1u))) & 0xFFFFu; };
+  auto stop_of = [&](unsigned int d) { return (d + 1) >> 1 < (unsigned int)words ? start_of(d + 1) : (unsigned int)n; };
+  unsigned int bin[MAXR], rk[MAXR];
+#pragma unroll
+  for (int r = 0; r < MAXR; ++r) {
+    const int i = tid + r * THREADS;
+    bin[r] = i < n ? (unsigned int)(((unsigned long long)(sm.E[i].s - lo) - mn) >> sh) : 0u;
+    rk[r] = 0;
   }
-  return in;
+  // ranks within the sub-bins bin[], and the sub-bins' starts; true if one holds more than `most`
+  auto count = [&](unsigned int most) -> bool {
+    for (int w = tid; w < words; w += THREADS) bins[w] = 0;
+    group_sync<THREADS>();
+    bool over = false;
+#pragma unroll
+    for (int r = 0; r < MAXR; ++r) {
+      if (tid + r * THREADS < n) {
+        const unsigned int half = 16u * (bin[r] & 1u);
+        rk[r] = (atomicAdd(&bins[bin[r] >> 1], 1u << half) >> half) & 0xFFFFu;
+        over |= rk[r] >= most;
+      }
+    }
+    group_sync<THREADS>();
+    const int per = words / THREADS, w0 = tid * per;
+    long long v[1] = {0}, ex[1], all[1];
+    for (int j = 0; j < per; ++j) v[0] += (bins[w0 + j] & 0xFFFFu) + (bins[w0 + j] >> 16);
+    block_excl_scan<THREADS, 1, OpSum>(v, ex, all, 0, sm.lds_scan);
+    unsigned int run = (unsigned int)ex[0];
+    for (int j = 0; j < per; ++j) {
+      const unsigned int c = bins[w0 + j], mid = run + (c & 0xFFFFu);
+      bins[w0 + j] = run | (mid << 16);
+      run = mid + (c >> 16);
+    }
+    return group_any<THREADS>(over);
+  };
+  if (count(kBinRefine) && sh > 0) {
+#pragma unroll
+    for (int r = 0; r < MAXR; ++r) {
+      const int i = tid + r * THREADS;
+      if (i < n) {
+        const unsigned int st = start_of(bin[r]), c = stop_of(bin[r]) - st;
+        bin[r] = st + __umulhi(bin_fraction((unsigned long long)(sm.E[i].s - lo) - mn, sh), c);
+      }
+    }
+    group_sync<THREADS>();
+    (void)count(kBinRefine);
+  }
+#pragma unroll
+  for (int r = 0; r < MAXR; ++r) {
+    const int i = tid + r * THREADS;
+    if (i < n) sm.ordA[start_of(bin[r]) + rk[r]] = (unsigned short)i;
+  }
+  group_sync<THREADS>();
+  bool crowded = false;
+  if (sh > 0) {
+    // the thread that placed a sub-bin's second record puts it in order
+#pragma unroll
+    for (int r = 0; r < MAXR; ++r) {
+      if (tid + r * THREADS < n && rk[r] == 1) {
+        const unsigned int st = start_of(bin[r]), c = stop_of(bin[r]) - st;
+        if (c > kBinCrowd) {
+          crowded = true;
+          continue;
+        }
+        unsigned short* o = sm.ordA + st;
+        for (int a = 1; a < (int)c; ++a) {
+          const unsigned short x = o[a];
+          const long long s = sm.E[x].s;
+          int b = a - 1;
+          while (b >= 0 && sm.E[o[b]].s > s) {
+            o[b + 1] = o[b];
+            --b;
+          }
+          o[b + 1] = x;
+        }
+      }
+    }
+  }
+  if (group_any<THREADS>(crowded)) return false;
+  ord = sm.ordA;
+  return true;
+}
+
+// The same order for every case. Where a sub-bin is crowded: an LSD radix sort
+// of 8 of the varying bits per pass, or by one wave a bitonic sort.
+template <int THREADS, int CAP>
+__device__ __forceinline__ const unsigned short* sort_lds(SortSmem<THREADS, CAP>& sm, int n, long long lo) {
+  const unsigned short* ord;
+  if (sort_bins<THREADS, CAP>(sm, n, lo, ord)) return ord;
+  if constexpr (THREADS < 256) {
+    // places past the records hold the largest key: none of them moves before one
+    const int tid = group_thread<THREADS>();
+    int size = 2;
+    while (size < n) size <<= 1;
+    for (int i = tid; i < size; i += THREADS) sm.ordA[i] = (unsigned short)i;
+    group_sync<THREADS>();
+    auto key = [&](int i) { return i < n ? sm.E[i].s : LLONG_MAX; };
+    for (int k = 2; k <= size; k <<= 1) {
+      for (int j = k >> 1; j > 0; j >>= 1) {
+        for (int i = tid; i < size / 2; i += THREADS) {
+          const int a = ((i & ~(j - 1)) << 1) | (i & (j - 1)), b = a | j;
+          const unsigned short x = sm.ordA[a], y = sm.ordA[b];
+          if ((key(x) > key(y)) == ((a & k) == 0)) {
+            sm.ordA[a] = y;
+            sm.ordA[b] = x;
+          }
+        }
+        group_sync<THREADS>();
+      }
+    }
+    return sm.ordA;
+  } else {
+    constexpr int MAXR = CAP / THREADS;
+    unsigned long long kor = 0, kand = ~0ull;
+    for (int i = threadIdx.x; i < n; i += THREADS) {
+      const unsigned long long k = (unsigned long long)(sm.E[i].s - lo);
+      kor |= k;
+      kand &= k;
+    }
+    const unsigned long long vary = block_vary<THREADS>(kor, kand, sm.red);
+    const int lb = __ffsll((long long)vary) - 1;
+    const int passes = (bitlen64(vary) - lb + 7) >> 3;
+    const unsigned short* in = nullptr;  // identity for the first pass
+    for (int ps = 0; ps < passes; ++ps) {
+      unsigned short* out = (ps & 1) ? sm.ordB : sm.ordA;
+      radix_pass<THREADS, MAXR>(sm.E, in, out, n, lo, lb + 8 * ps, sm.whist, sm.dstart, sm.lds_scan);
+      in = out;
+    }
+    return in;
+  }
 }
 
 // Stable LSD sort of n records in global memory by start - lo, CAP records of

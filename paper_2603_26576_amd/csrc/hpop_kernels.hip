@@ -92,6 +92,7 @@ __global__ void k_reset(Plan p) {
     p.oversized[1] = 0;
   }
   if (tid < 4) p.ticket[tid] = 0;
+  for (long long i = tid; i < 2 * kQueues * kQueuePad; i += stride) p.qlen[i] = 0;
   if (tid == 0 && p.ts) p.ts[kTsBuild] = __builtin_amdgcn_s_memrealtime();
   for (long long i = tid; i < p.n_owners; i += stride) p.owner_err[i] = 0;
   for (long long i = tid; i < kRaccWords * p.n_racc; i += stride) p.racc[i] = 0;
@@ -1150,21 +1151,31 @@ __global__ __launch_bounds__(THREADS) void k_base_grouped(Plan p) {
 // merge: per bucket, sort by start in LDS and flatten each level
 // ----------------------------------------------------------------------------
 
-// Block path: one workgroup flattens bucket gb (LDS radix sort up to CAP
-// records, global-memory radix sort beyond).
+// n items by the group, the loads of four rounds issued together.
+template <int THREADS, class Load, class Put>
+__device__ __forceinline__ void group_copy(int n, Load load, Put put) {
+  constexpr int U = 4;
+  for (int i0 = group_thread<THREADS>(); i0 < n; i0 += U * THREADS) {
+    decltype(load(0)) x[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) x[u] = load(min(i0 + u * THREADS, n - 1));
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (i0 + u * THREADS < n) put(i0 + u * THREADS, x[u]);
+  }
+}
+
+// One group flattens bucket gb: sorted in LDS up to CAP records; beyond, by a
+// workgroup's radix sort in global memory. A single wave takes buckets of at
+// most CAP records only.
 template <int THREADS, int CAP>
-__device__ void merge_bucket_block(const Plan& p, long long gb, SortSmem<THREADS, CAP>& sm, int* s_seg) {
-  if (threadIdx.x == 0) *s_seg = p.bucket_seg[gb];
-  __syncthreads();
-  const int seg = *s_seg;
-  const SegDesc sd = p.segs[seg];
-  const Geom g = seg_geom(p, seg);
-  const long long bl = gb - sd.bucket_begin;
+__device__ __forceinline__ void merge_bucket(const Plan& p, long long gb, SortSmem<THREADS, CAP>& sm) {
+  constexpr int MAXI = CAP / THREADS;
+  const int tid = group_thread<THREADS>();
   const BucketRecs br = bucket_recs(p, gb);
-  // a slot overflow makes the host redo the build: write an empty bucket
-  const long long n = br.overflow ? 0 : (long long)br.n8 + br.n16;
+  const int seg = p.bucket_seg[gb];
   const long long off = (long long)p.offsets[gb];
-  const int nlev = sd.n_levels;
+  const unsigned long long mx[3] = {p.maxend[gb * 3], p.maxend[gb * 3 + 1], p.maxend[gb * 3 + 2]};
   FlatState st;
 #pragma unroll
   for (int l = 0; l < 3; ++l) {
@@ -1172,6 +1183,12 @@ __device__ void merge_bucket_block(const Plan& p, long long gb, SortSmem<THREADS
     st.P[l] = 0;
     st.R[l] = 0;
   }
+  const SegDesc sd = p.segs[seg];
+  const Geom g = seg_geom(p, seg);
+  const long long bl = gb - sd.bucket_begin;
+  // a slot overflow makes the host redo the build: write an empty bucket
+  const long long n = br.overflow ? 0 : (long long)br.n8 + br.n16;
+  const int nlev = sd.n_levels;
   Comp* comp[3] = {p.comp[0] + off, p.comp[1] + off, p.comp[2] + off};
   CompN* compn_b[3] = {p.compn[0] + off, p.compn[1] + off, p.compn[2] + off};
   CompN* const* compn = seg_narrow(g) ? compn_b : nullptr;
@@ -1179,67 +1196,70 @@ __device__ void merge_bucket_block(const Plan& p, long long gb, SortSmem<THREADS
     const long long lo = bucket_lo(g, bl);
     if (n <= CAP) {
       const int ni = (int)n;
-      const unsigned long long* mx = p.maxend + gb * 3;
-      for (int i = threadIdx.x; i < br.n8; i += THREADS) sm.E[i] = widen(br.narrow[i], lo, mx);
-      for (int i = threadIdx.x; i < br.n16; i += THREADS) sm.E[br.n8 + i] = br.wide[i];
-      __syncthreads();
+      group_copy<THREADS>(br.n8, [&](int i) { return br.narrow[i]; },
+                          [&](int i, uint2 x) { sm.E[i] = widen(x, lo, mx); });
+      group_copy<THREADS>(br.n16, [&](int i) { return br.wide[i]; }, [&](int i, Elem x) { sm.E[br.n8 + i] = x; });
+      group_sync<THREADS>();
       const unsigned short* ord = sort_lds<THREADS, CAP>(sm, ni, lo);
-      flatten_tile<THREADS>(sm.E, ord, ni, nlev, 0, comp, compn, lo, st, sm.lds_scan, nullptr);
-    } else {
+      flatten_tile<THREADS, MAXI>(sm.E, ord, ni, nlev, comp, compn, lo, st, sm.lds_scan);
+    } else if constexpr (THREADS >= 256) {
       // oversized bucket (exact offsets only): every record in the 16 B form
       // into the scratch copy, a stable LSD sort between it and the bucket's
       // own region (16 B per record), then flatten CAP records at a time,
       // carrying the running state across tiles
       Elem* a = p.elems2 + off;
-      const unsigned long long* mx = p.maxend + gb * 3;
-      for (long long i = threadIdx.x; i < br.n8; i += THREADS) a[i] = widen(br.narrow[i], lo, mx);
-      for (long long i = threadIdx.x; i < br.n16; i += THREADS) a[br.n8 + i] = br.wide[i];
+      for (long long i = tid; i < br.n8; i += THREADS) a[i] = widen(br.narrow[i], lo, mx);
+      for (long long i = tid; i < br.n16; i += THREADS) a[br.n8 + i] = br.wide[i];
       __threadfence_block();
       __syncthreads();
       const Elem* src = sort_global<THREADS, CAP>(sm, a, p.elems + off, n, lo);
       for (long long t0 = 0; t0 < n; t0 += CAP) {
         const int cnt = (int)min((long long)CAP, n - t0);
-        for (int i = threadIdx.x; i < cnt; i += THREADS) sm.E[i] = src[t0 + i];
+        for (int i = tid; i < cnt; i += THREADS) sm.E[i] = src[t0 + i];
         __syncthreads();
-        flatten_tile<THREADS>(sm.E, nullptr, cnt, nlev, 0, comp, compn, lo, st, sm.lds_scan, nullptr);
+        flatten_tile<THREADS, MAXI>(sm.E, nullptr, cnt, nlev, comp, compn, lo, st, sm.lds_scan);
         __syncthreads();
       }
     }
   }
-  if (threadIdx.x == 0) {
+  if (tid == 0) {
 #pragma unroll
     for (int l = 0; l < 3; ++l) {
       p.bsum[gb * 3 + l] = st.P[l];
       p.ncomp[gb * 3 + l] = (unsigned int)st.R[l];
     }
   }
-  __syncthreads();
+  group_sync<THREADS>();
 }
 
-// Buckets the wave path handed over (ticket[2] of them in p.queue): one per
-// workgroup by index when they are at most as many as the workgroups, else
-// taken by persistent workgroups from a shared counter (ticket[1]), every
-// workgroup leaving once the counter passes the queue length.
-template <int THREADS, int CAP>
-__global__ __launch_bounds__(THREADS) void k_merge_block(Plan p) {
-  __shared__ SortSmem<THREADS, CAP> sm;
-  __shared__ int s_seg;
-  __shared__ unsigned int s_idx;
-  const unsigned int qlen = __hip_atomic_load(&p.ticket[2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (qlen <= gridDim.x) {
-    // at most one bucket per workgroup: taken by index, so the workgroups
-    // without one leave at once instead of queueing on the shared counter
-    if (blockIdx.x < qlen) merge_bucket_block<THREADS, CAP>(p, (long long)p.queue[blockIdx.x], sm, &s_seg);
-    return;
+// The buckets of list set `set` (kQueues lists taken as one): workgroup b takes
+// every gridDim.x-th from the b-th on.
+struct QueueView {
+  const unsigned int* queue;
+  long long cap;
+  unsigned int len, first, total;  // per lane < kQueues: a list's length, and its first place among all
+  __device__ __forceinline__ long long at(unsigned int idx) const {
+    // the last list that starts at or before idx and is not empty
+    const int q = 63 - __clzll((long long)__ballot(len > 0 && first <= idx));
+    return (long long)queue[q * cap + (idx - (unsigned int)__builtin_amdgcn_readlane((int)first, q))];
   }
-  while (true) {
-    if (threadIdx.x == 0) s_idx = atomicAdd(&p.ticket[1], 1u);
-    __syncthreads();
-    const unsigned int idx = s_idx;
-    __syncthreads();
-    if (idx >= qlen) break;
-    merge_bucket_block<THREADS, CAP>(p, (long long)p.queue[idx], sm, &s_seg);
-  }
+};
+__device__ __forceinline__ QueueView queue_view(const Plan& p, int set) {
+  QueueView v;
+  const int lane = threadIdx.x & 63;
+  v.queue = p.queue + (long long)set * kQueues * p.queue_cap;
+  v.cap = p.queue_cap;
+  v.len = lane < kQueues ? __hip_atomic_load(&p.qlen[(set * kQueues + lane) * kQueuePad], __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT)
+                         : 0u;
+  v.first = wave_excl_scan_u32<OpSumU>(v.len, 0u, v.total);
+  return v;
+}
+
+// Appends bucket gb (one lane calls) to its list of list set `set`.
+__device__ __forceinline__ void queue_push(const Plan& p, int set, long long gb) {
+  const long long l = set * kQueues + ((gb >> 2) & (kQueues - 1));
+  p.queue[l * p.queue_cap + atomicAdd(&p.qlen[l * kQueuePad], 1u)] = (unsigned int)gb;
 }
 
 // Wave path: each wave sorts and flattens one bucket of at most kWaveCap
@@ -1261,12 +1281,6 @@ struct alignas(16) WaveSmem {
   unsigned int end[kWaveCap];        // ends of the sorted records
   unsigned int bins[kWaveBins / 2];  // two 16-bit counters (then sub-bin starts) per word
 };
-
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // N consecutive LDS words from a position that is a multiple of N: 16-byte
 // reads when N is a multiple of 4, 8-byte reads when it is even, else words
@@ -1436,19 +1450,109 @@ __device__ __forceinline__ void wave_flatten(const Plan& p, WaveSmem& W, long lo
 // bucket's count (fixed slots only).
 constexpr int kWavePre = 4;
 
+// The most records of a sub-bin that the wave path's insertion sort takes. A
+// bucket with more in one (starts in a few places, as where phases of work lie
+// between idle stretches) is handed over, and sorted with a second count
+// (wave_split) by a wave of k_merge_rest. The split is not made in the wave
+// kernel: its registers and code cost every bucket (large trace: 640 us for the
+// merge instead of 508, 600 with the split in a called function). The line at
+// 12: a trace of 32 + 32 resources in phases of 20 ms every 330 ms (4e6 records)
+// takes 24 + 73 us in the two kernels at 8, 49 + 70 at 16, 83 + 48 at 24, and
+// took 110 + 141 with sub-bins of up to 32 sorted by insertion and the others
+// by the block path; but at 8 a few buckets of evenly spread records go the
+// long way too (small trace: 3.4 -> 8.9 us for k_merge_rest).
+constexpr int kWaveFix = 12, kWaveFixSplit = 32;
+
+// The second count: each sub-bin is split into as many parts as it holds
+// records, and the records' places come from counting the parts' starts up.
+// W.bins holds the sub-bins' starts, kr and er the records; leaves W.key and
+// W.end sorted, or returns true in a lane that found a part of more than
+// kWaveFixSplit records.
+template <int IPL, int NBINS>
+__device__ __forceinline__ bool wave_split(WaveSmem& W, int ni, int ksh, const unsigned int (&kr)[IPL],
+                                            const unsigned int (&er)[IPL]) {
+  constexpr int wpl = NBINS >> 7;
+  const int lane = threadIdx.x & 63;
+  auto half = [&](unsigned int d) { return (W.bins[d >> 1] >> (16u * (d & 1u))) & 0xFFFFu; };
+  unsigned int part[IPL];
+#pragma unroll
+  for (int r = 0; r < IPL; ++r) {
+    const unsigned int d = kr[r] >> ksh, st = half(d);
+    const unsigned int stop = (int)d + 1 < NBINS ? half(d + 1) : (unsigned int)ni;
+    part[r] = st + __umulhi(kr[r] << (32 - ksh), stop - st);  // below ni <= NBINS; past the bucket: not used
+  }
+  wave_sync();
+  unsigned int bw[wpl];
+#pragma unroll
+  for (int j = 0; j < wpl; ++j) bw[j] = 0;
+  lds_store<wpl>(W.bins + lane * wpl, bw);
+  wave_sync();
+#pragma unroll
+  for (int r = 0; r < IPL; ++r)
+    if (lane + 64 * r < ni) atomicAdd(&W.bins[part[r] >> 1], 1u << (16u * (part[r] & 1u)));
+  wave_sync();
+  lds_load<wpl>(W.bins + lane * wpl, bw);
+  unsigned int tot = 0, all;
+#pragma unroll
+  for (int j = 0; j < wpl; ++j) tot += (bw[j] & 0xFFFFu) + (bw[j] >> 16);
+  unsigned int run = wave_excl_scan_u32<OpSumU>(tot, 0u, all);
+#pragma unroll
+  for (int j = 0; j < wpl; ++j) {
+    const unsigned int a = run, b = run + (bw[j] & 0xFFFFu);
+    run = b + (bw[j] >> 16);
+    bw[j] = a | (b << 16);
+  }
+  lds_store<wpl>(W.bins + lane * wpl, bw);
+  wave_sync();
+#pragma unroll
+  for (int r = 0; r < IPL; ++r) {
+    // a position past the bucket stores to its own index
+    unsigned int q = (unsigned int)(lane + 64 * r);
+    if ((int)q < ni) {
+      const unsigned int sh = 16u * (part[r] & 1u);
+      q = (atomicAdd(&W.bins[part[r] >> 1], 1u << sh) >> sh) & 0xFFFFu;
+    }
+    W.key[q] = kr[r];
+    W.end[q] = er[r];
+  }
+  wave_sync();
+  // the parts' starts have become their stops: order inside each part
+  bool crowded = false;
+  for (int d = lane; d < ni; d += 64) {
+    const int st = d ? (int)half((unsigned int)d - 1u) : 0, c = (int)half((unsigned int)d) - st;
+    if (c > kWaveFixSplit) crowded = true;
+    if (c < 2 || c > kWaveFixSplit) continue;
+    unsigned int* ko = W.key + st;
+    unsigned int* eo = W.end + st;
+    for (int a = 1; a < c; ++a) {
+      const unsigned int kx = ko[a], ex = eo[a];
+      int b = a - 1;
+      while (b >= 0 && ko[b] > kx) {
+        ko[b + 1] = ko[b];
+        eo[b + 1] = eo[b];
+        --b;
+      }
+      ko[b + 1] = kx;
+      eo[b + 1] = ex;
+    }
+  }
+  return crowded;
+}
+
 // Sort of one bucket of 64*(IPL-1) < ni <= 64*IPL records into W, then its
 // flatten: every round but the last is full, so only the last one tests for
 // positions past the bucket. With fixed slots (kSlots) the first kWavePre
 // rounds come loaded in `pre` (read before the count was known, so past the
-// end of a bucket of fewer records: places its slots hold). Returns false
-// (nothing written) when the bucket must take the block path.
-template <int IPL, bool kSlots>
+// end of a bucket of fewer records: places its slots hold). kSplit: with the
+// second count, and any ni <= 64*IPL. Returns false (nothing written) when the
+// bucket must be handed over.
+template <int IPL, bool kSlots, bool kSplit = false>
 __device__ __forceinline__ bool wave_bucket(const Plan& p, WaveSmem& W, long long gb, long long off, int ni,
                                             const uint2* rec, const uint2 (&pre)[kWavePre], long long lo, int nlev,
                                             const long long (&carry)[3], const long long (&maxe)[3]) {
   const int lane = threadIdx.x & 63;
   // round r holds position lane + 64 r; rounds before the last are inside the bucket
-  auto in_bucket = [&](int r) { return r < IPL - 1 || lane + 64 * r < ni; };
+  auto in_bucket = [&](int r) { return (!kSplit && r < IPL - 1) || lane + 64 * r < ni; };
   unsigned int kr[IPL], er[IPL], rk[IPL];
   // every lane loads every round, from a position clamped into the bucket
   // (ni >= 1): the loads issue back to back instead of one masked block (and
@@ -1462,7 +1566,7 @@ __device__ __forceinline__ bool wave_bucket(const Plan& p, WaveSmem& W, long lon
     }
     // a 32-bit byte offset from the wave-uniform base (ni <= kWaveCap); the
     // last round clamps into the bucket, so it reads no lines past its end
-    const unsigned int i = (unsigned int)(r < IPL - 1 ? lane + 64 * r : min(lane + 64 * r, ni - 1));
+    const unsigned int i = (unsigned int)(!kSplit && r < IPL - 1 ? lane + 64 * r : min(lane + 64 * r, ni - 1));
     x[r] = *(const uint2*)((const char*)rec + 8u * i);  // relative to lo: (start - lo) << 2 | slot, end - lo + 1
   }
   // a position past the bucket keeps the padding pair of the flatten: key 2
@@ -1517,6 +1621,15 @@ __device__ __forceinline__ bool wave_bucket(const Plan& p, WaveSmem& W, long lon
   }
   lds_store<wpl>(W.bins + lane * wpl, bw);
   wave_sync();
+  bool crowded = false;
+  if constexpr (kSplit) {
+    crowded = wave_split<IPL, nbins>(W, ni, ksh, kr, er);
+    if (__ballot(crowded)) return false;
+    wave_sync();
+    if (nlev == 2) wave_flatten<IPL, 2>(p, W, gb, off, ni, lo, carry, maxe);
+    else wave_flatten<IPL, 3>(p, W, gb, off, ni, lo, carry, maxe);
+    return true;
+  }
   unsigned int fix = 0;  // bit r: the record of round r is the second one of its sub-bin
   constexpr int G = IPL < 4 ? IPL : 4;  // rounds placed together (bounds the live registers)
 #pragma unroll
@@ -1545,13 +1658,12 @@ __device__ __forceinline__ bool wave_bucket(const Plan& p, WaveSmem& W, long lon
   }
   wave_sync();
   // order inside each sub-bin by the full key, where it holds two or more
-  // records: an insertion sort per such sub-bin (c > 32 records: block path)
-  bool crowded = false;
+  // records: an insertion sort per such sub-bin
   auto fix_sub_bin = [&](unsigned int d) {
     const int st0 = (int)((W.bins[d >> 1] >> (16u * (d & 1u))) & 0xFFFFu);
     const int st1 = (int)d + 1 < nbins ? (int)((W.bins[(d + 1) >> 1] >> (16u * ((d + 1) & 1u))) & 0xFFFFu) : ni;
     const int c = st1 - st0;
-    if (c > 32) {
+    if (c > kWaveFix) {
       crowded = true;
       return;
     }
@@ -1687,7 +1799,55 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
   if (br.n16 == 0 && n <= kWaveCap)  // only 8 B records (so the segment is narrow: buckets at most 2^30 ns wide)
     done = wave_merge<kSlots>(p, W, gb, off, (int)n, br.narrow, pre, bucket_lo(g, gb - sd.bucket_begin), sd.n_levels,
                               carry, maxe);
-  if (!done && lane == 0) p.queue[atomicAdd(&p.ticket[2], 1u)] = (unsigned int)gb;
+  if (!done && lane == 0) queue_push(p, n <= kWaveCap ? 0 : 1, gb);
+}
+
+// The buckets the wave path handed over. Those of more than kWaveCap records
+// take a workgroup each. The others take a wave each: 8 B records with crowded
+// sub-bins the wave path's code with its second count, 16 B records (64-bit
+// keys) and equal starts the workgroup's code. Waves count from the last
+// workgroup down, so those without a large bucket take the small ones first.
+// A build of 2.9e3 wide buckets (16 + 16 resources, 1e6 records over hours):
+// 131 us with a workgroup per bucket and a radix sort, 57 with the counting
+// sort, 27 so. A few buckets take 17 us, which is one bucket's chain of
+// dependent reads, barriers and scans.
+template <int THREADS, int CAP>
+__global__ __launch_bounds__(THREADS, CAP == 2048 ? 3 : 1) void k_merge_rest(Plan p) {
+  constexpr int NW = THREADS / 64;
+  __shared__ union {
+    SortSmem<THREADS, CAP> block;
+    SortSmem<64, kWaveCap> one[NW];
+    WaveSmem w[NW];
+  } u;
+  {
+    const QueueView v = queue_view(p, 1);
+    for (unsigned int idx = blockIdx.x; idx < v.total; idx += gridDim.x) merge_bucket<THREADS, CAP>(p, v.at(idx), u.block);
+  }
+  const QueueView v = queue_view(p, 0);
+  const int wave = group_wave<THREADS>();
+  for (unsigned int idx = (gridDim.x - 1 - blockIdx.x) * NW + wave; idx < v.total; idx += gridDim.x * NW) {
+    const long long gb = v.at(idx);
+    const BucketRecs br = bucket_recs(p, gb);
+    bool done = false;
+    if (br.n16 == 0) {
+      const int seg = p.bucket_seg[gb];
+      const long long off = (long long)p.offsets[gb];
+      long long carry[3], maxe[3];
+#pragma unroll
+      for (int l = 0; l < 3; ++l) {
+        carry[l] = p.carry[gb * 3 + l];
+        maxe[l] = (long long)p.maxend[gb * 3 + l];
+      }
+      maxe[1] = max(maxe[0], maxe[1]);
+      maxe[2] = max(maxe[1], maxe[2]);
+      const SegDesc sd = p.segs[seg];
+      const long long lo = bucket_lo(seg_geom(p, seg), gb - sd.bucket_begin);
+      const uint2 pre[kWavePre] = {};
+      done = wave_bucket<8, false, true>(p, u.w[wave], gb, off, br.n8, br.narrow, pre, lo, sd.n_levels, carry, maxe);
+      wave_sync();
+    }
+    if (!done) merge_bucket<64, kWaveCap>(p, gb, u.one[wave]);
+  }
 }
 
 // ----------------------------------------------------------------------------
@@ -1722,7 +1882,6 @@ struct SmallSmem {
   unsigned int off[kSmallBuckets];        // merged-interval offset within the segment
   unsigned int queue[kSmallBuckets];      // buckets for the block path
   unsigned int nq;
-  int seg;
   const int64_t* s[kSmallChunks];
   const int64_t* e[kSmallChunks];
   int first[kSmallChunks];      // segment's record index of the chunk's first record
@@ -1957,6 +2116,9 @@ __global__ __launch_bounds__(kSmallThreads, 4) void k_build_small(Plan p) {
       maxe[2] = max(maxe[1], maxe[2]);
       const long long off = ss.elem0 + (long long)(unsigned int)__builtin_amdgcn_readfirstlane((int)S.off[b]);
       done = wave_merge<true>(p, S.u.w[wave], gb, off, (int)n, rec, pre, bucket_lo(g, b), sd.n_levels, carry, maxe);
+      if (!done)
+        done = wave_bucket<8, false, true>(p, S.u.w[wave], gb, off, (int)n, rec, pre, bucket_lo(g, b), sd.n_levels,
+                                           carry, maxe);
     }
     if (!done && lane == 0) S.queue[atomicAdd(&S.nq, 1u)] = (unsigned int)b;
   }
@@ -1964,7 +2126,7 @@ __global__ __launch_bounds__(kSmallThreads, 4) void k_build_small(Plan p) {
   // the block path, a bucket at a time by the whole workgroup
   const unsigned int nq = S.nq;
   for (unsigned int q = 0; q < nq; ++q)
-    merge_bucket_block<THREADS, 2048>(p, sd.bucket_begin + S.queue[q], S.u.sort, &S.seg);
+    merge_bucket<THREADS, 2048>(p, sd.bucket_begin + S.queue[q], S.u.sort);
   __syncthreads();
   if (wave == 0) base_segment(p, seg, lane);
 }
@@ -1974,7 +2136,7 @@ __global__ __launch_bounds__(kSmallThreads, 4) void k_build_small(Plan p) {
 // ----------------------------------------------------------------------------
 
 // Measure of level l of segment seg before time t.
-__device__ long long measure_before(const Plan& p, int seg, int l, long long t) {
+__device__ __forceinline__ long long measure_before(const Plan& p, int seg, int l, long long t) {
   const SegDesc sd = p.segs[seg];
   const Geom g = seg_geom(p, seg);
   const long long max_e = (long long)p.stats[seg].max_e;
@@ -2324,14 +2486,14 @@ hipError_t launch_merge_wave(const Plan& p, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_merge_block(const Plan& p, int cap, hipStream_t st) {
+hipError_t launch_merge_rest(const Plan& p, int cap, hipStream_t st) {
   if (p.n_buckets == 0) return hipSuccess;
-  // persistent workgroups for the buckets the wave path handed over
-  const unsigned grid = (unsigned)std::min<long long>(p.n_buckets, 1024);
+  // persistent workgroups (as many as fit) for the buckets the wave path handed over
+  const unsigned grid = (unsigned)std::min<long long>(p.n_buckets, 768);
   if (cap == 2048)
-    hipLaunchKernelGGL((k_merge_block<256, 2048>), dim3(grid), dim3(256), 0, st, p);
+    hipLaunchKernelGGL((k_merge_rest<256, 2048>), dim3(grid), dim3(256), 0, st, p);
   else
-    hipLaunchKernelGGL((k_merge_block<256, 4096>), dim3(grid), dim3(256), 0, st, p);
+    hipLaunchKernelGGL((k_merge_rest<256, 4096>), dim3(grid), dim3(256), 0, st, p);
   return hipGetLastError();
 }
 

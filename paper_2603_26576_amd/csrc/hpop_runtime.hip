@@ -184,11 +184,15 @@ hpop_status Workspace::prepare(Alloc& a, long long n_chunks, long long n_tiles, 
   small += carve_bytes(n_buckets + 1, sizeof(unsigned long long));
   small += carve_bytes(n_buckets, sizeof(unsigned long long));
   small += carve_bytes(3 * n_buckets, sizeof(unsigned long long));
-  small += carve_bytes(3 * n_buckets, sizeof(long long)) * 3;
+  small += carve_bytes(3 * n_buckets, sizeof(long long)) * 2;
+  // the measures before each bucket come last, so their place holds the block path's lists until then
+  const long long queue_cap = 4 * (n_buckets / (4 * kQueues) + 1);
+  const long long queue_words = 2 * kQueues * (queue_cap + kQueuePad);
+  const long long base_words = std::max(3 * n_buckets, (queue_words + 1) / 2);
+  small += carve_bytes(base_words, sizeof(long long));
   small += carve_bytes(3 * n_buckets, sizeof(unsigned int));
   small += carve_bytes(3 * n_segs, sizeof(long long));
   small += carve_bytes(1, 8) + carve_bytes(nscan, 8) + carve_bytes(4, 4) + carve_bytes(2, 8);
-  small += carve_bytes(n_buckets, sizeof(unsigned int));
   small += carve_bytes(n_owners, sizeof(unsigned int));
   small += carve_bytes(n_regions, sizeof(RegionDesc)) + carve_bytes(n_regions * sizeof(Tree) + kStatusBytes, 1);
   small += carve_bytes(kRaccWords * n_regions, sizeof(unsigned long long));
@@ -272,12 +276,14 @@ hpop_status Workspace::prepare(Alloc& a, long long n_chunks, long long n_tiles, 
   p.maxend = carve<unsigned long long>(cur, 3 * n_buckets);
   p.carry = carve<long long>(cur, 3 * n_buckets);
   p.bsum = carve<long long>(cur, 3 * n_buckets);
-  p.base = carve<long long>(cur, 3 * n_buckets);
+  p.base = carve<long long>(cur, base_words);
+  p.qlen = (unsigned int*)p.base;
+  p.queue = p.qlen + 2 * kQueues * kQueuePad;
+  p.queue_cap = queue_cap;
   p.ncomp = carve<unsigned int>(cur, 3 * n_buckets);
   p.seg_total = carve<long long>(cur, 3 * n_segs);
   p.scan_state = carve<unsigned long long>(cur, nscan);
   p.ticket = carve<unsigned int>(cur, 4);
-  p.queue = carve<unsigned int>(cur, n_buckets);
   p.n_owners = (int32_t)n_owners;
   p.seg_group = 1;
   d_trees = (Tree*)carve<char>(cur, n_regions * sizeof(Tree) + kStatusBytes);
@@ -636,7 +642,7 @@ hpop_status Engine::enqueue(bool build, bool with_timing, std::string& err) {
     HPOP_HIP(launch_merge_wave(p, st), "k_merge_wave");
     HPOP_HIP(mark("merge_wave"), "hipEventRecord");
     HPOP_HIP(pre("merge_block"), "hipEventRecord");
-    HPOP_HIP(launch_merge_block(p, p.cap, st), "k_merge_block");
+    HPOP_HIP(launch_merge_rest(p, p.cap, st), "k_merge_rest");
     HPOP_HIP(mark("merge_block"), "hipEventRecord");
     HPOP_HIP(pre("base"), "hipEventRecord");
     HPOP_HIP(launch_base(p, st), "k_base");
