@@ -72,3 +72,14 @@ def test_many_wide_buckets():
     n = 30_000
     st = np.sort(rng.integers(0, n << 28, size=n))
     check(trace(st, rng, 1 << 28), {"bucket_target": 16})
+
+
+@pytest.mark.parametrize("extra", [0, 1])
+def test_tile_size_changes_with_the_records(extra):
+    """The most records of a build with the smallest tiles, and one more (three resources, the last ones of a tile each)."""
+    n = (128 << 10) // 3
+    rng = np.random.default_rng(extra)
+    tr = trace(np.sort(rng.integers(0, n * 60_000, size=n)), rng, 60_000)
+    more = (128 << 10) - 3 * n + extra
+    tr.chunks += [tg.Chunk(1, tg.DEV_KERNEL, tg.T0 + np.arange(more), tg.T0 + np.arange(more) + 5)]
+    check(tr, {})
