@@ -65,6 +65,13 @@ __host__ __device__ inline int bucket_of_start(const Geom& g, long long s) {
   return (int)geom_div(g, (unsigned int)((unsigned long long)(s - g.min_s) >> g.s0));
 }
 
+// whether a start lies in the range its segment's buckets cover (always, where
+// that is the range of all of its records)
+__host__ __device__ inline bool start_in_range(const Geom& g, long long s) {
+  // nb * wx <= 2^31 + nb: 32 bits
+  return ((unsigned long long)(s - g.min_s) >> g.s0) < (unsigned long long)(g.empty ? 0u : (unsigned int)g.nb * g.wx);
+}
+
 // buckets at most 2^kNarrowShift ns wide: records and components fit the 8 B forms
 __host__ __device__ inline bool seg_narrow(const Geom& g) {
   return ((unsigned long long)g.wx << g.s0) <= (1ull << kNarrowShift);

@@ -63,6 +63,16 @@ constexpr int kSmallChunks = 128;    // chunks of such a segment at most
 constexpr int kSmallRecords = 4096;  // records
 constexpr int kSmallBuckets = 64;    // buckets
 
+// Sampled start ranges (k_range): kRangeSample starts of each chunk, half from
+// its front and half from its back (records arrive roughly in time order), and
+// 1 / 2^kRangePad of what they span on either side. Records in any order pass
+// too: the chance that one of a segment lies outside is below 3e-7. Plans with
+// a segment of more than kRangeChunks chunks read every start.
+constexpr int kRangeSample = 2048;
+constexpr int kRangePad = 7;
+constexpr int kRangeChunks = 64;
+constexpr unsigned long long kRangeMiss = 1ull << 62;
+
 // Chunks smaller than half a tile share tiles: consecutive ones (in the
 // chunk table) fill a tile with at most this many chunks and tile_elems records.
 constexpr int kTileChunks = 32;
@@ -178,6 +188,9 @@ struct Plan {
   int32_t pad1;
   const SegDesc* segs;
   const SmallSeg* sseg;              // [n_segs] when every segment is small, else null
+  const int32_t* seg_first;          // [n_segs + 1] the segments' places in seg_chunk; null: their start ranges
+                                     // are read from every record
+  const int32_t* seg_chunk;          // [n_chunks] chunks by segment
   SegStats* stats;
   SegGeom* geom;                     // [n_segs] bucket geometry (filled by the geometry kernel)
   int64_t n_buckets;
@@ -202,7 +215,8 @@ struct Plan {
   unsigned int* queue;               // [2][kQueues][queue_cap] buckets the wave path handed over (in base's memory)
   unsigned int* qlen;                // [2][kQueues], kQueuePad words apart: their counts
   int64_t queue_cap;
-  unsigned long long* oversized;     // [0] buckets above the on-chip capacity, [1] buckets above slot_cap
+  unsigned long long* oversized;     // [0] buckets above the on-chip capacity, [1] buckets above slot_cap, and
+                                     // kRangeMiss if a start lay outside its segment's sampled range
   unsigned int* owner_err;           // [n_owners] set when an owner has an invalid record
   unsigned long long* racc;          // [n_racc][kRaccWords] per region: six sums, three maxima, slices added;
                                      // zero between launches

@@ -23,6 +23,7 @@ hipError_t launch_gather(const CopyChunk* chunks, int n, hipStream_t st);  // ho
 
 hipError_t launch_build_small(const Plan& p, hipStream_t st);  // a plan with p.sseg: the whole build
 hipError_t launch_reset(const Plan& p, hipStream_t st);
+hipError_t launch_range(const Plan& p, bool reset, hipStream_t st);  // sampled start ranges (p.seg_first); reset: that pass too
 hipError_t launch_stats(const Plan& p, hipStream_t st);
 hipError_t launch_hist(const Plan& p, hipStream_t st);
 hipError_t launch_scan(const Plan& p, hipStream_t st);
@@ -33,7 +34,7 @@ hipError_t launch_merge_wave(const Plan& p, hipStream_t st);
 hipError_t launch_merge_rest(const Plan& p, int cap, hipStream_t st);
 hipError_t launch_base(const Plan& p, hipStream_t st);
 // Regions (n_plain of them [t0, t1), the rest per resource) and the status
-// words {first bad record, oversized buckets, slot overflows}. trees and
+// words {first bad record, oversized buckets, slot overflows (and kRangeMiss)}. trees and
 // status: device or page-locked host memory. reset: the build's own status
 // words go back to their identities once they are stored.
 hipError_t launch_region(const Plan& p, const RegionDesc* regions, int n_regions, int n_plain, int max_res, Tree* trees,

@@ -70,15 +70,9 @@ __global__ __launch_bounds__(256) void k_gather(GatherArgs g) {
 // reset: per-build counters to their identities
 // ----------------------------------------------------------------------------
 
-__global__ void k_reset(Plan p) {
+__device__ __forceinline__ void reset_counters(const Plan& p) {
   const long long tid = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   const long long stride = (long long)gridDim.x * blockDim.x;
-  for (long long i = tid; i < p.n_segs; i += stride) {
-    p.stats[i].min_s = ULLONG_MAX;
-    p.stats[i].max_s = 0;
-    p.stats[i].max_e = 0;
-    p.stats[i].pad = 0;
-  }
   for (long long i = tid; i < p.n_buckets; i += stride) {
     p.counts[i] = 0;
     p.cursor[i] = 0;
@@ -96,6 +90,17 @@ __global__ void k_reset(Plan p) {
   if (tid == 0 && p.ts) p.ts[kTsBuild] = __builtin_amdgcn_s_memrealtime();
   for (long long i = tid; i < p.n_owners; i += stride) p.owner_err[i] = 0;
   for (long long i = tid; i < kRaccWords * p.n_racc; i += stride) p.racc[i] = 0;
+}
+
+__global__ void k_reset(Plan p) {
+  reset_counters(p);
+  const long long stride = (long long)gridDim.x * blockDim.x;
+  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < p.n_segs; i += stride) {
+    p.stats[i].min_s = ULLONG_MAX;
+    p.stats[i].max_s = 0;
+    p.stats[i].max_e = 0;
+    p.stats[i].pad = 0;
+  }
 }
 
 // ----------------------------------------------------------------------------
@@ -298,7 +303,7 @@ __device__ __forceinline__ void scatter_shared(const Plan& p, long long tile, Sh
   sh_load<true>(p, tile, T);
   const int n = T.off[T.n];
   int jj[IPT], gbk[IPT];
-  bool nr[IPT];
+  bool nr[IPT], miss = false;
   unsigned int kx[IPT], ex[IPT];
   {
     long long svs[IPT], evs[IPT];
@@ -318,6 +323,8 @@ __device__ __forceinline__ void scatter_shared(const Plan& p, long long tile, Sh
           const ChunkDesc& cd = p.chunks[T.first + j];
           atomicMin(p.err, ((unsigned long long)cd.chunk_id << 40) | (unsigned long long)(x - T.off[j]));
           p.owner_err[cd.owner] = 1u;
+        } else if (sv < ev && !start_in_range(T.g[j], sv)) {
+          miss = true;
         } else if (sv < ev) {
           const Geom& g = T.g[j];
           const int b = bucket_of(sv, g);
@@ -330,6 +337,7 @@ __device__ __forceinline__ void scatter_shared(const Plan& p, long long tile, Sh
       }
     }
   }
+  if (miss) atomicOr(&p.oversized[1], kRangeMiss);
   int bmin = INT_MAX, bmax = -1;
 #pragma unroll
   for (int k = 0; k < IPT; ++k) {
@@ -575,6 +583,84 @@ __global__ __launch_bounds__(256) void k_stats_small(Plan p) {
   }
 }
 
+// Start range and bucket geometry of each segment (a workgroup per segment)
+// from a sample of its starts, with the reset pass on the side if asked: the
+// scatter checks every start against the range, and a build with one outside
+// is redone with the pass over all starts. That pass reads 8 of the 24 B per
+// record that the build's first half moves. With its reset and geometry
+// kernels it took 178 us of the large trace's 1370, 28 of the mid trace's 232,
+// 75 of the streams' 660 and 66 of 440 on a batch of 128 traces; this takes 13,
+// 9, 17 and 37. What bounds it is four dependent reads, so a wave takes a
+// quarter of a chunk's sample, not a chunk (mid: 11 us).
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void k_range(Plan p, bool reset) {
+  constexpr int NW = THREADS / 64, K = 8;
+  __shared__ unsigned long long red[2][NW];
+  __shared__ const int64_t* s_at[kRangeChunks];
+  __shared__ int64_t s_count[kRangeChunks];
+  if (reset) reset_counters(p);
+  const int seg = blockIdx.x;
+  if (seg >= p.n_segs) return;
+  const int c0 = p.seg_first[seg], nch = p.seg_first[seg + 1] - c0;
+  bool all = true;  // the sample holds every record
+  for (int j = threadIdx.x; j < nch; j += THREADS) {
+    const ChunkDesc& cd = p.chunks[p.seg_chunk[c0 + j]];
+    s_at[j] = cd.s;
+    s_count[j] = cd.count;
+  }
+  __syncthreads();
+  unsigned long long mn = ULLONG_MAX, mx = 0;
+  for (int j = 0; j < nch; ++j) all = all && s_count[j] <= kRangeSample;
+  // a wave per quarter of a chunk's sample, K loads in flight per lane
+  constexpr int kParts = kRangeSample / (64 * K);
+  const int lane = threadIdx.x & 63;
+  for (int u = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); u < nch * kParts; u += NW) {
+    const int j = u / kParts, i0 = (u % kParts) * 64 * K;
+    const int64_t* s = s_at[j];
+    const long long n = s_count[j];
+    const int m = (int)min(n, (long long)kRangeSample);
+    if (i0 >= m) continue;
+    unsigned long long x[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const int i = min(i0 + 64 * k + lane, m - 1);
+      x[k] = (unsigned long long)s[i < kRangeSample / 2 ? (long long)i : n - m + i];
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      if (x[k] < (unsigned long long)kTimeLimit) {  // other starts belong to invalid records
+        mn = x[k] < mn ? x[k] : mn;
+        mx = x[k] > mx ? x[k] : mx;
+      }
+    }
+  }
+  mn = wave_red_minu(mn);
+  mx = wave_red_maxu(mx);
+  if ((threadIdx.x & 63) == 0) {
+    red[0][threadIdx.x >> 6] = mn;
+    red[1][threadIdx.x >> 6] = mx;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < NW; ++w) {
+      mn = red[0][w] < mn ? red[0][w] : mn;
+      mx = red[1][w] > mx ? red[1][w] : mx;
+    }
+    if (mn <= mx && !all) {
+      const unsigned long long pad = ((mx - mn) >> kRangePad) + 1;
+      mn = mn > pad ? mn - pad : 0;
+      mx = min(mx + pad, (unsigned long long)kTimeLimit - 1);
+    }
+    SegStats st;
+    st.min_s = mn;
+    st.max_s = mx;
+    st.max_e = 0;
+    st.pad = 0;
+    p.stats[seg] = st;
+    p.geom[seg] = make_geom(st, p.segs[seg]);
+  }
+}
+
 // The bucket geometry of every segment from its start range (one thread per
 // segment, after the start-range pass).
 __global__ void k_geom(Plan p) {
@@ -770,7 +856,7 @@ __global__ __launch_bounds__(THREADS) void k_scatter(Plan p) {
   // per record: bucket (-1: none), form, and the 8 B form itself; a record in
   // the 16 B form is read again where it is needed (rare)
   int bk[IPT];
-  bool nr[IPT];
+  bool nr[IPT], miss = false;
   unsigned int kx[IPT], ex[IPT];
   int bmin = INT_MAX, bmax = -1;
   // the loads of all rounds first, from positions clamped into the tile
@@ -797,6 +883,8 @@ __global__ __launch_bounds__(THREADS) void k_scatter(Plan p) {
         // first bad record of the build: chunk << 40 | index (rare path)
         atomicMin(p.err, ((unsigned long long)cd.chunk_id << 40) | (unsigned long long)i);
         p.owner_err[cd.owner] = 1u;
+      } else if (sv < ev && !start_in_range(g, sv)) {
+        miss = true;
       } else if (sv < ev) {
         bk[k] = bucket_of(sv, g);
         const long long lo = bucket_lo(g, bk[k]);
@@ -808,6 +896,7 @@ __global__ __launch_bounds__(THREADS) void k_scatter(Plan p) {
       }
     }
   }
+  if (miss) atomicOr(&p.oversized[1], kRangeMiss);
   bmin = wave_reduce_i32<OpMinI>(bmin, INT_MAX);
   bmax = wave_reduce_i32<OpMaxI>(bmax, -1);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -2387,6 +2476,20 @@ hipError_t launch_reset(const Plan& p, hipStream_t st) {
   const long long work = max(3 * p.n_buckets + p.n_segs, p.n_tiles) + 64;
   int blocks = (int)min(2048ll, (work + 255) / 256);
   hipLaunchKernelGGL(k_reset, dim3(blocks), dim3(256), 0, st, p);
+  return hipGetLastError();
+}
+
+hipError_t launch_range(const Plan& p, bool reset, hipStream_t st) {
+  // many segments (a batch of small traces: 1.6e4) hold few records each, so a
+  // wave takes one (37 us, 44 with two waves); the reset pass wants a workgroup
+  // per few hundred buckets
+  const bool many = p.n_segs >= 2048;
+  long long blocks = p.n_segs;
+  if (reset) blocks = max(blocks, min(1024ll, (3 * p.n_buckets + 511) / 512));
+  if (many)
+    hipLaunchKernelGGL(k_range<64>, dim3((unsigned)blocks), dim3(64), 0, st, p, reset);
+  else
+    hipLaunchKernelGGL(k_range<512>, dim3((unsigned)blocks), dim3(512), 0, st, p, reset);
   return hipGetLastError();
 }
 

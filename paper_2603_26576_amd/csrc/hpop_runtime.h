@@ -72,6 +72,8 @@ struct Workspace {
   ChunkDesc* d_chunks = nullptr;
   SegDesc* d_segs = nullptr;
   SmallSeg* d_sseg = nullptr;
+  int32_t* d_seg_first = nullptr;
+  int32_t* d_seg_chunk = nullptr;
   char* d_extra = nullptr;       // a caller's own tables, uploaded with the descriptors
   size_t extra_bytes = 0;        // their size (set before the plan is made)
   RegionDesc* d_regions = nullptr;
@@ -91,7 +93,7 @@ struct Workspace {
   hpop_status prepare(Alloc& a, long long n_chunks, long long n_tiles, long long n_segs, long long n_buckets,
                       long long n_elems,
                       long long n_slots, long long n_regions, long long n_times, long long n_owners,
-                      long long n_ivls, bool small, std::string& err);
+                      long long n_ivls, bool small, bool sampled, std::string& err);
   void release(Alloc& a);
 };
 
@@ -103,6 +105,9 @@ struct Engine {
   std::vector<int32_t> h_tile_chunk;  // [n_tiles] chunk of each streaming tile (see Plan::tile_chunk)
   std::vector<SegDesc> h_segs;
   std::vector<SmallSeg> h_sseg;       // not empty: every segment is small (see k_build_small)
+  std::vector<int32_t> h_seg_first;   // not empty: start ranges from a sample (see k_range), with
+  std::vector<int32_t> h_seg_chunk;   // the chunks by segment
+  bool exact_range = false;           // a start lay outside a sampled range: read every start from then on
   bool staged = false;                // the plan keeps the build's passes apart (their times are wanted)
   bool keep_status = false;           // only builds are enqueued: the caller's kernels read what they leave
   int plan_passes = 0;                // builds run with the current plan
@@ -137,6 +142,7 @@ struct Engine {
   hpop_status assemble_plan(const hpop_tuning& tun, const std::vector<long long>& seg_count,
                             const std::vector<char>& seg_host, int n_owners, long long times, std::string& err);
   bool plan_small(const std::vector<long long>& seg_count, int slots, int cap);
+  void plan_range(int n_segs, int slots);
   hpop_status prepare_plan(long long tiles, long long own_tiles, long long n_segs, long long buckets, long long elems,
                            int slots, int cap, int tile, int n_owners, long long times, std::string& err);
   hpop_status upload(std::string& err);

@@ -172,12 +172,13 @@ static size_t carve_bytes(size_t n, size_t sz) { return (n * sz + 255) & ~size_t
 hpop_status Workspace::prepare(Alloc& a, long long n_chunks, long long n_tiles, long long n_segs,
                                long long n_buckets, long long n_elems, long long n_slots, long long n_regions,
                                long long n_times, long long n_owners, long long n_ivls, bool small_segs,
-                               std::string& err) {
+                               bool sampled, std::string& err) {
   const size_t nscan = (size_t)((n_buckets + kScanTile - 1) / kScanTile + 1);
   size_t small = 0;
   small += carve_bytes(n_chunks, sizeof(ChunkDesc));
   small += carve_bytes(n_tiles, sizeof(int32_t));
   small += carve_bytes(n_segs, sizeof(SegDesc)) + carve_bytes(small_segs ? n_segs : 0, sizeof(SmallSeg));
+  if (sampled) small += carve_bytes(n_segs + 1, sizeof(int32_t)) + carve_bytes(n_chunks, sizeof(int32_t));
   small += carve_bytes(n_segs, sizeof(SegStats));
   small += carve_bytes(n_segs, sizeof(SegGeom));
   small += carve_bytes(n_buckets, sizeof(unsigned int)) * 2;
@@ -260,6 +261,11 @@ hpop_status Workspace::prepare(Alloc& a, long long n_chunks, long long n_tiles, 
   d_ivls = carve<IvlDesc>(cur, n_ivls);
   d_sseg = carve<SmallSeg>(cur, small_segs ? n_segs : 0);
   p.sseg = small_segs ? d_sseg : nullptr;
+  p.seg_first = p.seg_chunk = d_seg_first = d_seg_chunk = nullptr;
+  if (sampled) {
+    p.seg_first = d_seg_first = carve<int32_t>(cur, n_segs + 1);
+    p.seg_chunk = d_seg_chunk = carve<int32_t>(cur, n_chunks);
+  }
   d_extra = carve<char>(cur, extra_bytes);
   p.err = carve<unsigned long long>(cur, 1);
   p.oversized = carve<unsigned long long>(cur, 2);
@@ -446,6 +452,7 @@ hpop_status Engine::assemble_plan(const hpop_tuning& tun, const std::vector<long
   if (plan_small(seg_count, slots, cap)) {
     for (const auto& d : h_chunks) elems += d.count;
     h_tile_chunk.clear();
+    h_seg_first.clear();
     return prepare_plan(0, 0, n_segs, buckets, elems, slots, cap, tile, n_owners, times, err);
   }
   // Streaming tiles. A chunk of fewer than half a tile of records would leave
@@ -493,7 +500,25 @@ hpop_status Engine::assemble_plan(const hpop_tuning& tun, const std::vector<long
     while (c + 1 < nc && h_chunks[(size_t)c + 1].tile_begin <= t) ++c;
     h_tile_chunk[(size_t)t] = (int32_t)c;
   }
+  plan_range((int)n_segs, slots);
   return prepare_plan(tiles, own_tiles, n_segs, buckets, elems, slots, cap, tile, n_owners, times, err);
+}
+
+// Whether the segments' start ranges come from a sample, and the chunks by
+// segment for it. Fixed slots only: an exact build is the one whose records
+// already had their way with a guess. A caller that takes over the build's
+// results (keep_status) reads the ranges themselves.
+void Engine::plan_range(int n_segs, int slots) {
+  h_seg_first.clear();
+  if (slots == 0 || exact_range || keep_status) return;
+  std::vector<int32_t> first((size_t)n_segs + 1, 0);
+  for (const ChunkDesc& d : h_chunks)
+    if (++first[(size_t)d.seg + 1] > kRangeChunks) return;
+  for (int r = 0; r < n_segs; ++r) first[(size_t)r + 1] += first[(size_t)r];
+  h_seg_chunk.resize(h_chunks.size());
+  std::vector<int32_t> fill(first.begin(), first.end() - 1);
+  for (size_t c = 0; c < h_chunks.size(); ++c) h_seg_chunk[(size_t)fill[(size_t)h_chunks[c].seg]++] = (int32_t)c;
+  h_seg_first.swap(first);
 }
 
 // Whether every segment is small enough for k_build_small; then its chunks are
@@ -532,7 +557,8 @@ hpop_status Engine::prepare_plan(long long tiles, long long own_tiles, long long
                                  std::string& err) {
   hpop_status st = ws.prepare(alloc, (long long)h_chunks.size(), tiles, n_segs, buckets, elems,
                               slots > 0 ? buckets * (long long)slots : 0, (long long)h_regions.size(), times,
-                              std::max(1, n_owners), (long long)h_ivls.size(), !h_sseg.empty(), err);
+                              std::max(1, n_owners), (long long)h_ivls.size(), !h_sseg.empty(),
+                              !h_seg_first.empty(), err);
   if (st != HPOP_OK) return st;
   ws.plan.n_tiles = tiles;
   ws.plan.n_own_tiles = own_tiles;
@@ -577,6 +603,10 @@ hpop_status Engine::upload(std::string& err) {
   put(ws.d_regions, h_regions.data(), h_regions.size() * sizeof(RegionDesc));
   put(ws.d_ivls, h_ivls.data(), h_ivls.size() * sizeof(IvlDesc));
   put(ws.d_sseg, h_sseg.data(), h_sseg.size() * sizeof(SmallSeg));
+  if (ws.plan.seg_first) {
+    put(ws.d_seg_first, h_seg_first.data(), h_seg_first.size() * sizeof(int32_t));
+    put(ws.d_seg_chunk, h_seg_chunk.data(), h_seg_chunk.size() * sizeof(int32_t));
+  }
   put(ws.d_extra, h_extra.data(), ws.extra_bytes);
   // the status words and accumulators start at their identities (a build of
   // small segments has no reset pass: its last kernel puts them back)
@@ -619,11 +649,14 @@ hpop_status Engine::enqueue(bool build, bool with_timing, std::string& err) {
   if (build && p.sseg) {
     HPOP_HIP(launch_build_small(p, st), "k_build_small");
   } else if (build) {
+    // a sampled range takes the reset along, unless that pass's own time is wanted
+    const bool with_reset = p.seg_first && !staged;
     HPOP_HIP(pre("reset"), "hipEventRecord");
-    HPOP_HIP(launch_reset(p, st), "k_reset");
+    if (!with_reset) HPOP_HIP(launch_reset(p, st), "k_reset");
     HPOP_HIP(mark("reset"), "hipEventRecord");
     HPOP_HIP(pre("stats"), "hipEventRecord");
-    HPOP_HIP(launch_stats(p, st), "k_stats");
+    if (p.seg_first) HPOP_HIP(launch_range(p, with_reset, st), "k_range");
+    else HPOP_HIP(launch_stats(p, st), "k_stats");
     HPOP_HIP(mark("stats"), "hipEventRecord");
     if (p.slot_cap == 0) {  // exact offsets: count, then scan, then scatter, then carry
       HPOP_HIP(pre("hist"), "hipEventRecord");
@@ -786,6 +819,12 @@ hpop_status Engine::run(hpop_session* const* ss, int k, uint32_t flags, hpop_met
   memcpy(&over, h + bt + 8, 8);
   memcpy(&slot_over, h + bt + 16, 8);
   if (build) last_oversized = (long long)over;
+  if (build && bad == ULLONG_MAX && (slot_over & kRangeMiss)) {
+    // a start outside its segment's sampled range: redo this plan with every start read
+    exact_range = true;
+    key_sessions.clear();
+    return run(ss, k, flags | HPOP_FORCE_REBUILD, out, timing, err);
+  }
   if (build && bad == ULLONG_MAX && ws.plan.slot_cap > 0 && slot_over > 0) {
     // a bucket outgrew its fixed slots: redo this plan with exact offsets
     exact_forced = true;

@@ -182,10 +182,10 @@ extern "C" hpop_status hpop_metrics_compute_static(int32_t n_hosts, int32_t n_de
     std::lock_guard<std::mutex> g(d->mu);
     Engine& E = d->engine;
     E.alloc.stream = (hipStream_t)stream;
-    E.exact_forced = false;
+    E.exact_forced = E.exact_range = false;
     const size_t bt = (size_t)n_regions * sizeof(Tree);
     std::string err;
-    for (int attempt = 0; attempt < 2; ++attempt) {
+    for (int attempt = 0; attempt < 3; ++attempt) {
       st = plan(*d, n_hosts, n_devices, chunks, n_chunks, region_t0, region_t1, n_regions, err);
       if (st != HPOP_OK) return fail(st, err);
       d->result.assign(bt + 24, 0);
@@ -203,6 +203,11 @@ extern "C" hpop_status hpop_metrics_compute_static(int32_t n_hosts, int32_t n_de
         const int ci = cid < d->chunk_index.size() ? d->chunk_index[cid] : -1;
         return fail(HPOP_E_BAD_INTERVAL, "invalid record: chunk " + std::to_string(ci) + ", index " +
                                              std::to_string(idx) + " (need 0 <= start <= end < 2^62)");
+      }
+      if (slot_over & kRangeMiss) {
+        // a start outside its resource's sampled range: the same call with every start read
+        E.exact_range = true;
+        continue;
       }
       if (slot_over > 0 && E.ws.plan.slot_cap > 0) {
         // a bucket outgrew its fixed slots: the same call with exact offsets
