@@ -25,9 +25,11 @@ namespace hpop {
 // kGatherPiece records of both arrays. A few hundred copies of some ten
 // thousand bytes are bound by what enqueueing each costs the host (about 4 us
 // per copy, two copies per chunk); one launch per 80 chunks took the add and
-// build of 264 chunks (9e5 records) from 1049 to 232 us.
+// build of 264 chunks (9e5 records) from 1049 to 232 us. Pieces of 1024 records:
+// 80 chunks of 8191 take 6.0 us, 7.9 with pieces of 2048 and 11.4 with 4096,
+// which left most CUs without a workgroup.
 constexpr int kGatherChunks = 80;
-constexpr int kGatherPiece = 4096;
+constexpr int kGatherPiece = 1024;
 struct GatherArgs {
   CopyChunk c[kGatherChunks];
   unsigned int first[kGatherChunks + 1];
@@ -36,18 +38,15 @@ struct GatherArgs {
 static_assert(sizeof(GatherArgs) <= 4000, "kernel arguments");
 
 // n words from src to dst (256 B aligned) by the workgroup: pairs of words
-// when src is 16 B aligned, with four loads in flight per thread.
+// when src is 16 B aligned, with all of a thread's loads in flight.
 __device__ __forceinline__ void copy_words(const int64_t* src, int64_t* dst, int n) {
   if ((((uintptr_t)src) & 15) == 0 && n == kGatherPiece) {
     const longlong2* a = (const longlong2*)src;
     longlong2* b = (longlong2*)dst;
-    for (int i = threadIdx.x; i < kGatherPiece / 2; i += 4 * 256) {
-      const longlong2 x0 = a[i], x1 = a[i + 256], x2 = a[i + 512], x3 = a[i + 768];
-      b[i] = x0;
-      b[i + 256] = x1;
-      b[i + 512] = x2;
-      b[i + 768] = x3;
-    }
+    static_assert(kGatherPiece == 4 * 256, "two pairs per thread");
+    const longlong2 x0 = a[threadIdx.x], x1 = a[threadIdx.x + 256];
+    b[threadIdx.x] = x0;
+    b[threadIdx.x + 256] = x1;
   } else {
     for (int i = threadIdx.x; i < n; i += 256) dst[i] = src[i];
   }
