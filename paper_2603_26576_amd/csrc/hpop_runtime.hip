@@ -706,8 +706,9 @@ hpop_status Engine::enqueue(bool build, bool with_timing, std::string& err) {
   HPOP_HIP(mark("region"), "hipEventRecord");
   n_marks = ev;
   if (result_host)
-    HPOP_HIP(hipMemcpyAsync(result_host, ws.d_trees, (size_t)nreg * sizeof(Tree) + kStatusBytes, hipMemcpyDeviceToHost,
-                            st),
+    HPOP_HIP(hipMemcpyAsync(result_host, ws.d_trees,
+                            result_times ? times_offset() + 32 * (size_t)n_times : (size_t)nreg * sizeof(Tree) + kStatusBytes,
+                            hipMemcpyDeviceToHost, st),
              "copy results");
   return HPOP_OK;
 }

@@ -188,7 +188,11 @@ extern "C" hpop_status hpop_metrics_compute_static(int32_t n_hosts, int32_t n_de
     for (int attempt = 0; attempt < 3; ++attempt) {
       st = plan(*d, n_hosts, n_devices, chunks, n_chunks, region_t0, region_t1, n_regions, err);
       if (st != HPOP_OK) return fail(st, err);
-      d->result.assign(bt + 24, 0);
+      // the state times lie behind the trees: up to a MiB they come along with
+      // them (a copy of its own costs the call 10 us), more go straight to the caller
+      const size_t btimes = (size_t)n_regions * (size_t)(n_hosts + n_devices) * 32;
+      E.result_times = times_out && btimes && btimes <= (1u << 20);
+      d->result.resize(E.result_times ? E.times_offset() + btimes : bt + 24);
       E.result_host = d->result.data();
       st = E.upload(err);
       if (st == HPOP_OK) st = E.enqueue(true, false, err);
@@ -215,8 +219,9 @@ extern "C" hpop_status hpop_metrics_compute_static(int32_t n_hosts, int32_t n_de
         continue;
       }
       if (bt) memcpy(out, d->result.data(), bt);
-      const size_t btimes = (size_t)n_regions * (size_t)(n_hosts + n_devices) * 32;
-      if (times_out && btimes) {
+      if (E.result_times) {
+        memcpy(times_out, d->result.data() + E.times_offset(), btimes);
+      } else if (times_out && btimes) {
         e = hipMemcpy(times_out, E.ws.d_times, btimes, hipMemcpyDeviceToHost);
         if (e != hipSuccess) return fail(HPOP_E_HIP, std::string("hipMemcpy: ") + hipGetErrorString(e));
       }
