@@ -16,7 +16,8 @@ namespace hpop {
 __device__ __forceinline__ int bitlen64(unsigned long long x) { return x ? 64 - __clzll((long long)x) : 0; }
 
 __device__ __forceinline__ bool rec_valid(long long s, long long e) {
-  return s >= 0 && s <= e && e < kTimeLimit;
+  // 0 <= s <= e < 2^62: a negative one is above every other as an unsigned word
+  return (unsigned long long)s <= (unsigned long long)e && (unsigned long long)e < (unsigned long long)kTimeLimit;
 }
 
 __device__ __forceinline__ Geom seg_geom(const Plan& p, long long seg) { return p.geom[seg]; }
@@ -149,6 +150,11 @@ __device__ __forceinline__ long long dpp64(long long old, long long v) {
   const int lo = __builtin_amdgcn_update_dpp((int)old, (int)v, CTRL, ROW_MASK, BANK_MASK, false);
   const int hi = __builtin_amdgcn_update_dpp((int)(old >> 32), (int)(v >> 32), CTRL, ROW_MASK, BANK_MASK, false);
   return (long long)(((unsigned long long)(unsigned int)hi << 32) | (unsigned long long)(unsigned int)lo);
+}
+
+// lanes of m below this one
+__device__ __forceinline__ unsigned int lanes_below(unsigned long long m) {
+  return __builtin_amdgcn_mbcnt_hi((unsigned int)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)m, 0u));
 }
 
 __device__ __forceinline__ long long readlane64(long long v, int lane) {

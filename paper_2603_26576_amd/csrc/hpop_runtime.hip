@@ -352,12 +352,13 @@ static void tuned(const hpop_tuning& t, long long records, int& target, int& cap
   target = t.bucket_target > 0 ? std::min(4096, std::max(16, t.bucket_target)) : 352;
   cap = t.bucket_cap == 4096 ? 4096 : 2048;
   tile = t.tile_elems == 512 || t.tile_elems == 2048 || t.tile_elems == 8192 ? t.tile_elems : 4096;
-  // unless a size is asked for, tiles shrink with the records so that the
-  // streaming passes still spread over the 256 CUs: whole rebuilds with tiles
-  // of 512 / 2048 / 4096 took 65 / 68 / 69 us for 8e4 records, 73 / 69 / 76 for
-  // 3e5, 116 / 97 / 99 for 1e6 (8 resources each), 174 / 142 / 147 for 4e6 and
-  // 390 / 252 / 245 for 1.2e7 (32 resources)
-  if (t.tile_elems == 0 && records <= (6ll << 20)) tile = records <= (128ll << 10) ? 512 : 2048;
+  // unless a size is asked for: 2048 records (four per thread and 44 registers,
+  // so 32 waves per CU; the scatter of 1.25e8 records takes 504 us, 564 with
+  // 4096-record tiles at 24 waves, and 60 against 62 for 1.25e7), and 512 in
+  // builds of few records, so that the streaming passes still spread over the
+  // 256 CUs (whole rebuilds with tiles of 512 / 2048 / 4096: 65 / 68 / 69 us for
+  // 8e4 records, 73 / 69 / 76 for 3e5, 116 / 97 / 99 for 1e6)
+  if (t.tile_elems == 0 && records < LLONG_MAX) tile = records <= (128ll << 10) ? 512 : 2048;
   // single-pass scatter slots: 4x the mean bucket, within the on-chip capacity
   if (t.scatter_slots < 0) slots = 0;
   else if (t.scatter_slots > 0) slots = std::min(cap, pow2ceil(std::max(64, t.scatter_slots)));
@@ -1354,7 +1355,7 @@ hpop_status hpop_session_set_tuning(hpop_session* s, const hpop_tuning* t) {
 hpop_status hpop_session_get_tuning(const hpop_session* s, hpop_tuning* out) {
   if (!s || !out) return HPOP_E_ARG;
   int target, cap, tile, slots;
-  tuned(s->tuning, LLONG_MAX, target, cap, tile, slots);  // the tile size of a large build
+  tuned(s->tuning, LLONG_MAX, target, cap, tile, slots);  // the tile size asked for (4096: none was)
   out->bucket_target = target;
   out->bucket_cap = cap;
   out->tile_elems = tile;
