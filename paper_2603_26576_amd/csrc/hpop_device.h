@@ -380,15 +380,16 @@ struct FlatState {
   long long R[3];  // components written in this bucket
 };
 
-// Flatten one sorted tile of n <= THREADS * MAXI records: positions 0..n-1 in
-// order ord (or identity). Writes components of each level at comp[l][R], or in
-// the narrow form relative to `nlo` at compn[l][R] when compn is given;
-// advances `st`. A thread's records are read once, into registers (the three
-// sweeps read each of them from LDS through ord before, one after another).
-template <int THREADS, int MAXI>
-__device__ __forceinline__ void flatten_tile(const Elem* E, const unsigned short* ord, int n, int nlev,
-                                             Comp* const* comp, CompN* const* compn, long long nlo, FlatState& st,
-                                             long long* lds_scan) {
+// Flatten the NLEV levels of one sorted tile of n <= THREADS * MAXI records:
+// positions 0..n-1 in order ord (or identity). Writes components of each level
+// at comp[l][R], or in the narrow form relative to `nlo` at compn[l][R] when
+// compn is given; advances `st`. A thread's records are read once, into
+// registers, and the levels' break counts (at most 2^12 each) share one scan:
+// a wave's 64-bit scans are most of its instructions.
+template <int THREADS, int MAXI, int NLEV>
+__device__ __forceinline__ void flatten_tile(const Elem* E, const unsigned short* ord, int n, Comp* const* comp,
+                                             CompN* const* compn, long long nlo, FlatState& st, long long* lds_scan) {
+  static_assert(THREADS * MAXI <= 1 << 12 && NLEV <= 3, "break counts take 20 bits per level");
   const int ipt = (n + THREADS - 1) / THREADS;
   const int p0 = group_thread<THREADS>() * ipt;
   constexpr long long EMASK = (1ll << kSlotShift) - 1;
@@ -405,44 +406,45 @@ __device__ __forceinline__ void flatten_tile(const Elem* E, const unsigned short
     slot[j] = in ? (int)((unsigned long long)el.e_slot >> kSlotShift) : 3;
   }
   // phase A: exclusive max-scan of ends per level
-  long long tmax[3] = {LLONG_MIN, LLONG_MIN, LLONG_MIN};
+  long long tmax[NLEV];
 #pragma unroll
-  for (int j = 0; j < MAXI; ++j) {
+  for (int l = 0; l < NLEV; ++l) {
+    tmax[l] = LLONG_MIN;
 #pragma unroll
-    for (int l = 0; l < 3; ++l)
+    for (int j = 0; j < MAXI; ++j)
       if (slot[j] <= l && e[j] > tmax[l]) tmax[l] = e[j];
   }
-  long long exm[3], totm[3];
-  block_excl_scan<THREADS, 3, OpMax>(tmax, exm, totm, LLONG_MIN, lds_scan);
-  long long M[3];
+  long long M[NLEV], totm[NLEV];
+  block_excl_scan<THREADS, NLEV, OpMax>(tmax, M, totm, LLONG_MIN, lds_scan);
+  // phase B: per-thread measure per level, and break counts in fields of 20 bits
+  long long acc[NLEV + 1];
+  acc[NLEV] = 0;
 #pragma unroll
-  for (int l = 0; l < 3; ++l) M[l] = exm[l] > st.M[l] ? exm[l] : st.M[l];
-  // phase B: per-thread measure and break counts
-  long long acc[6] = {0, 0, 0, 0, 0, 0};
-  {
-    long long Mb[3] = {M[0], M[1], M[2]};
+  for (int l = 0; l < NLEV; ++l) {
+    M[l] = M[l] > st.M[l] ? M[l] : st.M[l];
+    long long Mb = M[l], a = 0;
+    int breaks = 0;
 #pragma unroll
     for (int j = 0; j < MAXI; ++j) {
-#pragma unroll
-      for (int l = 0; l < 3; ++l) {
-        if (l < nlev && slot[j] <= l) {
-          const long long lo = s[j] > Mb[l] ? s[j] : Mb[l];
-          if (e[j] > lo) acc[l] += e[j] - lo;
-          if (s[j] > Mb[l]) acc[3 + l] += 1;
-          if (e[j] > Mb[l]) Mb[l] = e[j];
-        }
+      if (slot[j] <= l) {
+        const long long lo = s[j] > Mb ? s[j] : Mb;
+        if (e[j] > lo) a += e[j] - lo;
+        if (s[j] > Mb) ++breaks;
+        if (e[j] > Mb) Mb = e[j];
       }
     }
+    acc[l] = a;
+    acc[NLEV] |= (long long)breaks << (20 * l);
   }
-  long long exa[6], tota[6];
-  block_excl_scan<THREADS, 6, OpSum>(acc, exa, tota, 0, lds_scan);
+  long long exa[NLEV + 1], tota[NLEV + 1];
+  block_excl_scan<THREADS, NLEV + 1, OpSum>(acc, exa, tota, 0, lds_scan);
   // phase C: write components
 #pragma unroll
-  for (int l = 0; l < 3; ++l) {
-    long long P = st.P[l] + exa[l], R = st.R[l] + exa[3 + l], Ml = M[l];
+  for (int l = 0; l < NLEV; ++l) {
+    long long P = st.P[l] + exa[l], R = st.R[l] + ((exa[NLEV] >> (20 * l)) & 0xFFFFF), Ml = M[l];
 #pragma unroll
     for (int j = 0; j < MAXI; ++j) {
-      if (l < nlev && slot[j] <= l) {
+      if (slot[j] <= l) {
         if (s[j] > Ml) {
           if (compn) {
             CompN c;
@@ -462,12 +464,9 @@ __device__ __forceinline__ void flatten_tile(const Elem* E, const unsigned short
         if (e[j] > Ml) Ml = e[j];
       }
     }
-  }
-#pragma unroll
-  for (int l = 0; l < 3; ++l) {
     st.M[l] = totm[l] > st.M[l] ? totm[l] : st.M[l];
     st.P[l] += tota[l];
-    st.R[l] += tota[3 + l];
+    st.R[l] += (tota[NLEV] >> (20 * l)) & 0xFFFFF;
   }
 }
 

@@ -1359,7 +1359,8 @@ __device__ __forceinline__ void merge_bucket(const Plan& p, long long gb, SortSm
       group_copy<THREADS>(br.n16, [&](int i) { return br.wide[i]; }, [&](int i, Elem x) { sm.E[br.n8 + i] = x; });
       group_sync<THREADS>();
       const unsigned short* ord = sort_lds<THREADS, CAP>(sm, ni, lo);
-      flatten_tile<THREADS, MAXI>(sm.E, ord, ni, nlev, comp, compn, lo, st, sm.lds_scan);
+      if (nlev == 2) flatten_tile<THREADS, MAXI, 2>(sm.E, ord, ni, comp, compn, lo, st, sm.lds_scan);
+      else flatten_tile<THREADS, MAXI, 3>(sm.E, ord, ni, comp, compn, lo, st, sm.lds_scan);
     } else if constexpr (THREADS >= 256) {
       // oversized bucket (exact offsets only): every record in the 16 B form
       // into the scratch copy, a stable LSD sort between it and the bucket's
@@ -1375,7 +1376,8 @@ __device__ __forceinline__ void merge_bucket(const Plan& p, long long gb, SortSm
         const int cnt = (int)min((long long)CAP, n - t0);
         for (int i = tid; i < cnt; i += THREADS) sm.E[i] = src[t0 + i];
         __syncthreads();
-        flatten_tile<THREADS, MAXI>(sm.E, nullptr, cnt, nlev, comp, compn, lo, st, sm.lds_scan);
+        if (nlev == 2) flatten_tile<THREADS, MAXI, 2>(sm.E, nullptr, cnt, comp, compn, lo, st, sm.lds_scan);
+        else flatten_tile<THREADS, MAXI, 3>(sm.E, nullptr, cnt, comp, compn, lo, st, sm.lds_scan);
         __syncthreads();
       }
     }
@@ -1614,12 +1616,13 @@ constexpr int kWavePre = 4;
 // (wave_split) by a wave of k_merge_rest. The split is not made in the wave
 // kernel: its registers and code cost every bucket (large trace: 640 us for the
 // merge instead of 508, 600 with the split in a called function). The line at
-// 12: a trace of 32 + 32 resources in phases of 20 ms every 330 ms (4e6 records)
+// 16: a trace of 32 + 32 resources in phases of 20 ms every 330 ms (4e6 records)
 // takes 24 + 73 us in the two kernels at 8, 49 + 70 at 16, 83 + 48 at 24, and
 // took 110 + 141 with sub-bins of up to 32 sorted by insertion and the others
-// by the block path; but at 8 a few buckets of evenly spread records go the
-// long way too (small trace: 3.4 -> 8.9 us for k_merge_rest).
-constexpr int kWaveFix = 12, kWaveFixSplit = 32;
+// by the block path; but at 8, and on some traces at 12, a few buckets of evenly
+// spread records go the long way too, and one such bucket costs the build 12 us
+// (small trace at 8: 3.4 -> 8.9 us for k_merge_rest).
+constexpr int kWaveFix = 16, kWaveFixSplit = 32;
 
 // The second count: each sub-bin is split into as many parts as it holds
 // records, and the records' places come from counting the parts' starts up.
@@ -2028,11 +2031,13 @@ __global__ __launch_bounds__(THREADS, CAP == 2048 ? 3 : 1) void k_merge_rest(Pla
 // CU per segment runs out of VALU beyond: with 1e4 records per segment 51 us
 // against 49, with 3e4 105 against 64. 512 threads: two workgroups per CU.
 constexpr int kSmallThreads = 512;
+constexpr int kSmallSort = 4;  // waves that sort buckets with 64-bit keys (their LDS: 10 KB each)
 
 struct SmallSmem {
   union {
     WaveSmem w[kSmallThreads / 64];
     SortSmem<kSmallThreads, 2048> sort;
+    SortSmem<64, kWaveCap> one[kSmallSort];
   } u;
   unsigned long long cnt[kSmallBuckets];  // 8 B records | 16 B records << 32
   unsigned long long maxe[kSmallBuckets * 3];
@@ -2281,10 +2286,25 @@ __global__ __launch_bounds__(kSmallThreads, 4) void k_build_small(Plan p) {
     if (!done && lane == 0) S.queue[atomicAdd(&S.nq, 1u)] = (unsigned int)b;
   }
   __syncthreads();
-  // the block path, a bucket at a time by the whole workgroup
+  // what is left, as k_merge_rest does it: buckets of at most kWaveCap records
+  // by a wave each, kSmallSort at a time (a segment of wide buckets has all of
+  // its here), then the larger ones by the workgroup
   const unsigned int nq = S.nq;
-  for (unsigned int q = 0; q < nq; ++q)
-    merge_bucket<THREADS, 2048>(p, sd.bucket_begin + S.queue[q], S.u.sort);
+  if (wave < kSmallSort) {
+    for (unsigned int q = wave; q < nq; q += kSmallSort) {
+      const unsigned int b = (unsigned int)__builtin_amdgcn_readfirstlane((int)S.queue[q]);
+      const unsigned long long cu = (unsigned long long)readlane64((long long)S.cnt[b], 0);
+      if ((cu & 0xFFFFFFFFull) + (cu >> 32) <= (unsigned long long)kWaveCap)
+        merge_bucket<64, kWaveCap>(p, sd.bucket_begin + b, S.u.one[wave]);
+    }
+  }
+  __syncthreads();
+  for (unsigned int q = 0; q < nq; ++q) {
+    const unsigned int b = S.queue[q];
+    const unsigned long long cu = S.cnt[b];
+    if ((cu & 0xFFFFFFFFull) + (cu >> 32) > (unsigned long long)kWaveCap)
+      merge_bucket<THREADS, 2048>(p, sd.bucket_begin + b, S.u.sort);
+  }
   __syncthreads();
   if (wave == 0) base_segment(p, seg, lane);
 }

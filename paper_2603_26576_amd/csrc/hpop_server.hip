@@ -286,14 +286,14 @@ __global__ __launch_bounds__(kServThreads) void k_serv_splice(const ServItem* it
     if (in_lds) {
       const int ni = (int)cnt;
       const unsigned short* ord = sort_lds<kServThreads, kServCap>(sm, ni, lo);
-      flatten_tile<kServThreads, kServCap / kServThreads>(sm.E, ord, ni, 1, out, nullptr, 0, st, sm.lds_scan);
+      flatten_tile<kServThreads, kServCap / kServThreads, 1>(sm.E, ord, ni, out, nullptr, 0, st, sm.lds_scan);
     } else if (cnt > 0) {
       const Elem* src = sort_global<kServThreads, kServCap>(sm, A, A + total, cnt, lo);
       for (long long t0 = 0; t0 < cnt; t0 += kServCap) {
         const int c = (int)min((long long)kServCap, cnt - t0);
         for (int i = threadIdx.x; i < c; i += kServThreads) sm.E[i] = src[t0 + i];
         __syncthreads();
-        flatten_tile<kServThreads, kServCap / kServThreads>(sm.E, nullptr, c, 1, out, nullptr, 0, st, sm.lds_scan);
+        flatten_tile<kServThreads, kServCap / kServThreads, 1>(sm.E, nullptr, c, out, nullptr, 0, st, sm.lds_scan);
         __syncthreads();
       }
     }
