@@ -112,7 +112,8 @@ typedef struct {
 /* Tuning of the reduction kernels (see hpop_autotune). Zero fields keep defaults. */
 typedef struct {
     int32_t bucket_target;  /* records per time bucket of a resource, before rounding the bucket
-                               count up to a power of two (16 .. 4096) */
+                               count up to a power of two (16 .. 4096); 0 = chosen by the build's
+                               records (reported as 352) */
     int32_t bucket_cap;     /* records a bucket may hold for the on-chip sort: 2048 or 4096 */
     int32_t tile_elems;     /* records per workgroup in the streaming passes: 512, 2048, 4096 or 8192;
                                0 = chosen by the build's records (reported as 4096) */

@@ -350,6 +350,14 @@ static int pow2ceil(int x) {
 
 static void tuned(const hpop_tuning& t, long long records, int& target, int& cap, int& tile, int& slots) {
   target = t.bucket_target > 0 ? std::min(4096, std::max(16, t.bucket_target)) : 352;
+  // 320 up to 32 Mi records, unless a target is asked for: with 352 a few in ten
+  // thousand buckets hold more than the 512 records of the wave path, and one of
+  // them costs the build 12 us in k_merge_rest (1.25e7 records: 195 us against
+  // 182; 9e5: 110 against 97; a batch of 128 traces 381 against 372). Larger
+  // builds have some whatever the target, and more buckets cost them more (1.25e8:
+  // 1125 against 1137 us), as do wide buckets, a wave of that kernel each (1e6
+  // records over hours: 103 against 117)
+  if (t.bucket_target == 0 && records <= (32ll << 20)) target = 320;
   cap = t.bucket_cap == 4096 ? 4096 : 2048;
   tile = t.tile_elems == 512 || t.tile_elems == 2048 || t.tile_elems == 8192 ? t.tile_elems : 4096;
   // unless a size is asked for: 2048 records (four per thread and 44 registers,

@@ -154,7 +154,11 @@ hpop_status plan(StaticDevice& d, int32_t n_hosts, int32_t n_devices, const hpop
     rd.ivl_begin = 0;
     E.h_regions.push_back(rd);
   }
-  const hpop_tuning defaults{};
+  // a build near the scratch's limits takes the larger buckets, of which it needs fewer
+  hpop_tuning defaults{};
+  long long records = 0;
+  for (long long n : seg_count) records += n;
+  if (records > (1ll << 20)) defaults.bucket_target = 352;
   hpop_status st = E.assemble_plan(defaults, seg_count, seg_host, 1, (long long)n_regions * R, err);
   if (st == HPOP_E_ARG && E.ws.fixed_needed > E.ws.fixed_bytes && !E.exact_forced) {
     // fixed scatter slots do not fit: exact offsets need less room
