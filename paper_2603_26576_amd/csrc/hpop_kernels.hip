@@ -785,26 +785,38 @@ __device__ __forceinline__ void scan_tile(const Plan& p) {
   }
   long long v[1] = {tsum}, ex[1], tot[1];
   block_excl_scan<THREADS, 1, OpSum>(v, ex, tot, 0, lds);
+  // The counts of all earlier tiles: the first wave reads 64 predecessors at
+  // once, nearest first (lane i: tile j - i), up to one whose inclusive sum is
+  // known. One at a time, the last of 9 tiles waited for 8 round trips: with tiles
+  // of 4096 buckets the launch took 12.8 us on the mid trace, 16 on 256 devices
+  // with their streams and 6 on the small trace; with 1024 it takes 5.9, 9 and
+  // 3.4. Tickets are taken in order, so every predecessor runs or has run.
   constexpr unsigned long long FLAG_AGG = 1ull << 62, FLAG_INC = 2ull << 62, VMASK = (1ull << 62) - 1;
-  if (threadIdx.x == 0) {
+  if (threadIdx.x < 64) {
     unsigned long long* st = p.scan_state;
-    if (bid == 0) {
-      __hip_atomic_store(&st[0], FLAG_INC | (unsigned long long)tot[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      s_excl = 0;
-    } else {
-      __hip_atomic_store(&st[bid], FLAG_AGG | (unsigned long long)tot[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      unsigned long long acc = 0;
-      long long j = bid - 1;
-      while (j >= 0) {
-        unsigned long long w = __hip_atomic_load(&st[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const unsigned long long f = w & ~VMASK;
-        if (f == 0) { __builtin_amdgcn_s_sleep(1); continue; }
-        acc += w & VMASK;
-        if (f == FLAG_INC) break;
-        --j;
-      }
-      __hip_atomic_store(&st[bid], FLAG_INC | (acc + (unsigned long long)tot[0]), __ATOMIC_RELAXED,
+    const int lane = threadIdx.x;
+    if (lane == 0)
+      __hip_atomic_store(&st[bid], (bid == 0 ? FLAG_INC : FLAG_AGG) | (unsigned long long)tot[0], __ATOMIC_RELAXED,
                          __HIP_MEMORY_SCOPE_AGENT);
+    unsigned long long acc = 0;
+    for (long long j = bid - 1; j >= 0;) {
+      const unsigned long long w =
+          j >= lane ? __hip_atomic_load(&st[j - lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : FLAG_INC;
+      const unsigned long long none = __ballot((w & ~VMASK) == 0), inc = __ballot((w & ~VMASK) == FLAG_INC);
+      // lanes up to the nearest inclusive sum (past tile 0 they hold an empty one)
+      const unsigned long long use = inc ? (inc & (0ull - inc)) | ((inc & (0ull - inc)) - 1ull) : ~0ull;
+      if (none & use) {
+        __builtin_amdgcn_s_sleep(1);
+        continue;
+      }
+      acc += (unsigned long long)wave_reduce_i64<OpSum>((use >> lane) & 1 ? (long long)(w & VMASK) : 0ll, 0ll);
+      if (inc) break;
+      j -= 64;
+    }
+    if (lane == 0) {
+      if (bid > 0)
+        __hip_atomic_store(&st[bid], FLAG_INC | (acc + (unsigned long long)tot[0]), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
       s_excl = acc;
     }
   }
@@ -1146,6 +1158,85 @@ __device__ __forceinline__ void carry_segment(const Plan& p, long long seg, int 
   if (lane == 0) p.stats[seg].max_e = (unsigned long long)(run[2] > init ? run[2] : (init + 1 > 0 ? init + 1 : 0));
 }
 
+// Segments of many buckets (128 and more on average): a workgroup each. A wave
+// scans 64 buckets at a time, row after row: segments of 700 buckets took the
+// carry pass 16 us and the base pass 13. A workgroup takes 4 x 256 per round,
+// all loads first: 11 and 10 (segments of 300: 7 and 5.5, now 5.5 and 5.3).
+constexpr int kBigRows = 4;
+
+__device__ __forceinline__ void carry_segment_big(const Plan& p, long long seg) {
+  __shared__ long long lds[4 * 3];
+  const SegDesc sd = p.segs[seg];
+  const SegStats st = p.stats[seg];
+  const long long nb = sd.nb;
+  const long long init = st.min_s > st.max_s ? -1 : (long long)st.min_s - 1;
+  long long run[3] = {init, init, init};
+  for (long long c0 = 0; c0 < nb; c0 += 256 * kBigRows) {
+    unsigned long long m[kBigRows][3];
+#pragma unroll
+    for (int j = 0; j < kBigRows; ++j) {
+      const long long b = c0 + 256 * j + threadIdx.x;
+      m[j][0] = m[j][1] = m[j][2] = 0;
+      if (b < nb) {
+        p.bucket_seg[sd.bucket_begin + b] = (int32_t)seg;
+        const unsigned long long* q = p.maxend + (sd.bucket_begin + b) * 3;
+        m[j][0] = q[0];
+        m[j][1] = q[1];
+        m[j][2] = q[2];
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < kBigRows; ++j) {
+      if (c0 + 256 * j >= nb) break;  // uniform
+      const long long b = c0 + 256 * j + threadIdx.x;
+      long long v[3], ex[3], all[3];
+      v[0] = m[j][0] ? (long long)m[j][0] : LLONG_MIN;
+      const long long m1 = m[j][1] ? (long long)m[j][1] : LLONG_MIN;
+      const long long m2 = m[j][2] ? (long long)m[j][2] : LLONG_MIN;
+      v[1] = m1 > v[0] ? m1 : v[0];
+      v[2] = m2 > v[1] ? m2 : v[1];
+      block_excl_scan<256, 3, OpMax>(v, ex, all, LLONG_MIN, lds);
+#pragma unroll
+      for (int l = 0; l < 3; ++l) {
+        if (b < nb) p.carry[(sd.bucket_begin + b) * 3 + l] = ex[l] > run[l] ? ex[l] : run[l];
+        run[l] = all[l] > run[l] ? all[l] : run[l];
+      }
+    }
+  }
+  if (threadIdx.x == 0)
+    p.stats[seg].max_e = (unsigned long long)(run[2] > init ? run[2] : (init + 1 > 0 ? init + 1 : 0));
+}
+
+__global__ __launch_bounds__(256) void k_base_big(Plan p) {
+  __shared__ long long lds[4 * 3];
+  const long long seg = blockIdx.x;
+  const SegDesc sd = p.segs[seg];
+  const long long nb = sd.nb;
+  long long run[3] = {0, 0, 0};
+  for (long long c0 = 0; c0 < nb; c0 += 256 * kBigRows) {
+    long long v[kBigRows][3];
+#pragma unroll
+    for (int j = 0; j < kBigRows; ++j) {
+      const long long b = c0 + 256 * j + threadIdx.x;
+#pragma unroll
+      for (int l = 0; l < 3; ++l) v[j][l] = b < nb ? p.bsum[(sd.bucket_begin + b) * 3 + l] : 0;
+    }
+#pragma unroll
+    for (int j = 0; j < kBigRows; ++j) {
+      if (c0 + 256 * j >= nb) break;  // uniform
+      const long long b = c0 + 256 * j + threadIdx.x;
+      long long ex[3], all[3];
+      block_excl_scan<256, 3, OpSum>(v[j], ex, all, 0, lds);
+#pragma unroll
+      for (int l = 0; l < 3; ++l) {
+        if (b < nb) p.base[(sd.bucket_begin + b) * 3 + l] = run[l] + ex[l];
+        run[l] += all[l];
+      }
+    }
+  }
+  if (threadIdx.x < 3) p.seg_total[seg * 3 + threadIdx.x] = threadIdx.x == 0 ? run[0] : (threadIdx.x == 1 ? run[1] : run[2]);
+}
+
 template <int THREADS>
 __global__ __launch_bounds__(THREADS) void k_carry(Plan p) {
   const int lane = threadIdx.x & 63;
@@ -1262,11 +1353,15 @@ __global__ __launch_bounds__(THREADS) void k_carry_grouped(Plan p) {
 // Fixed slots: the bucket scan and the carry pass read only what the scatter
 // wrote, so one launch does both: workgroups [0, scan_blocks) scan (tiles in
 // ticket order), the ones after give each wave a segment (or a group of
-// kSegGroup segments).
-template <bool kGrouped>
+// kSegGroup segments), or take a segment themselves (kBig).
+template <bool kGrouped, bool kBig = false>
 __global__ __launch_bounds__(256) void k_scan_carry(Plan p, int scan_blocks) {
   if ((int)blockIdx.x < scan_blocks) {
     scan_tile<256>(p);
+    return;
+  }
+  if constexpr (kBig) {
+    carry_segment_big(p, blockIdx.x - scan_blocks);
     return;
   }
   const int lane = threadIdx.x & 63;
@@ -2647,6 +2742,9 @@ hipError_t launch_scatter(const Plan& p, hipStream_t st) {
   return hipGetLastError();
 }
 
+// many buckets per segment: the per-segment passes take a workgroup for each
+static bool big_segments(const Plan& p) { return p.n_buckets >= 128 * (int64_t)p.n_segs; }
+
 hipError_t launch_carry(const Plan& p, hipStream_t st) {
   if (p.n_segs == 0) return hipSuccess;
   if (p.seg_group > 1)
@@ -2661,6 +2759,11 @@ hipError_t launch_scan_carry(const Plan& p, hipStream_t st) {
   const long long waves = p.seg_group > 1 ? (p.n_segs + kSegGroup - 1) / kSegGroup : p.n_segs;
   const long long blocks = scan_blocks + (waves + 3) / 4;
   if (blocks == 0) return hipSuccess;
+  if (big_segments(p)) {
+    hipLaunchKernelGGL((k_scan_carry<false, true>), dim3((unsigned)(scan_blocks + p.n_segs)), dim3(256), 0, st, p,
+                       (int)scan_blocks);
+    return hipGetLastError();
+  }
   if (p.seg_group > 1)
     hipLaunchKernelGGL(k_scan_carry<true>, dim3((unsigned)blocks), dim3(256), 0, st, p, (int)scan_blocks);
   else
@@ -2691,6 +2794,10 @@ hipError_t launch_merge_rest(const Plan& p, int cap, hipStream_t st) {
 
 hipError_t launch_base(const Plan& p, hipStream_t st) {
   if (p.n_segs == 0) return hipSuccess;
+  if (big_segments(p)) {
+    hipLaunchKernelGGL(k_base_big, dim3((unsigned)p.n_segs), dim3(256), 0, st, p);
+    return hipGetLastError();
+  }
   if (p.seg_group > 1)
     hipLaunchKernelGGL(k_base_grouped<64>, dim3((unsigned)((p.n_segs + kSegGroup - 1) / kSegGroup)), dim3(64), 0, st, p);
   else

@@ -83,3 +83,16 @@ def test_tile_size_changes_with_the_records(extra):
     more = (128 << 10) - 3 * n + extra
     tr.chunks += [tg.Chunk(1, tg.DEV_KERNEL, tg.T0 + np.arange(more), tg.T0 + np.arange(more) + 5)]
     check(tr, {})
+
+
+@pytest.mark.parametrize("devices,buckets", [(1, 127), (1, 129), (2, 341), (2, 342), (1, 1025), (0, 66_000), (300, 64)])
+def test_bucket_counts(devices, buckets):
+    """Edges of the bucket passes: workgroup per segment or wave, one tile of 1024 buckets and more, over 64 tiles."""
+    rng = np.random.default_rng(devices + buckets)
+    n = 16 * buckets
+    chunks = []
+    for r in range(1 + devices):
+        s = tg.T0 + np.sort(rng.integers(0, n * 1000, size=n))
+        chunks.append(tg.Chunk(r, 2 if r == 0 else 3, s, s + rng.integers(0, 1500, size=n)))
+    regions = [(tg.T0, tg.T0 + n * 1000), (tg.T0 + n * 300, tg.T0 + n * 700 + 1)]
+    check(tg.Trace(1, devices, chunks, regions), {"bucket_target": 16})
