@@ -121,6 +121,10 @@ struct IvlDesc {
   int32_t region;
   int32_t resource;  // within the region's session
   int64_t a, b;
+  // filled with the plan, so that a thread has all it needs in one read
+  int32_t seg;       // the resource's segment
+  int32_t n_levels;  // 2 for devices, 3 for hosts
+  int64_t row;       // its row in the times array (and the accumulators)
 };
 
 struct Tree {  // identical layout to hpop_metric_tree

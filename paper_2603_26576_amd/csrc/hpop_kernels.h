@@ -36,9 +36,10 @@ hipError_t launch_base(const Plan& p, hipStream_t st);
 // Regions (n_plain of them [t0, t1), the rest per resource) and the status
 // words {first bad record, oversized buckets, slot overflows (and kRangeMiss)}. trees and
 // status: device or page-locked host memory. reset: the build's own status
-// words go back to their identities once they are stored.
+// words go back to their identities once they are stored. clear_macc: the
+// intervals' accumulators are cleared first (every pass leaves them clear).
 hipError_t launch_region(const Plan& p, const RegionDesc* regions, int n_regions, int n_plain, int max_res, Tree* trees,
                          unsigned long long* status, bool reset, long long* times, const IvlDesc* ivls,
-                         long long n_ivls, long long* macc, hipStream_t st);
+                         long long n_ivls, long long* macc, bool clear_macc, hipStream_t st);
 
 }  // namespace hpop

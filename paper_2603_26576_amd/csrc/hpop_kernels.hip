@@ -2538,13 +2538,18 @@ __global__ __launch_bounds__(256) void k_region(Plan p, const RegionDesc* region
 }
 
 // Regions given as per-resource interval lists (a region entered repeatedly,
-// each resource on its own clock). Part 1 clears the accumulators of their
-// resources; part 2 adds, per (interval, level, end of the interval), the
-// level's measure before that end (the start with a minus sign) and each
-// interval's length; part 3 turns them into state times (the remainder
-// completes the resource's own time in the region) and the tree, with E the
-// largest host in-region time (eq. 1), or the largest device one when no host
-// process is in the region.
+// each resource on its own clock). The first part adds, per (interval, level,
+// end of the interval), the level's measure before that end (the start with a
+// minus sign) and each interval's length; the second turns them into state
+// times (the remainder completes the resource's own time in the region) and
+// the tree, with E the largest host in-region time (eq. 1), or the largest
+// device one when no host process is in the region, and leaves the
+// accumulators clear for the next pass (k_ivl_zero clears a new plan's).
+//
+// The first part is a chain of cache misses (16 regions x 128 resources x 32
+// entries fit the GPU at once), so what a thread needs to start lies in its
+// interval: 29 -> 26 us there, and with two launches fewer (the status words and
+// the clearing) a pass takes 49 us instead of 56.
 __global__ __launch_bounds__(256) void k_ivl_zero(const RegionDesc* regions, long long* macc) {
   const RegionDesc rd = regions[blockIdx.x];
   if (rd.n_ivl == 0) return;
@@ -2552,30 +2557,30 @@ __global__ __launch_bounds__(256) void k_ivl_zero(const RegionDesc* regions, lon
   for (int i = threadIdx.x; i < 4 * R; i += 256) macc[rd.times_off * 4 + i] = 0;
 }
 
-__global__ __launch_bounds__(256) void k_ivl_acc(Plan p, const RegionDesc* regions, const IvlDesc* ivls,
-                                                 long long n_ivls, long long* macc) {
+__global__ __launch_bounds__(256) void k_ivl_acc(Plan p, const IvlDesc* ivls, long long n_ivls, long long* macc) {
   const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
   const long long i = t >> 3;
   if (i >= n_ivls) return;
   const int l = (int)((t >> 1) & 3), ep = (int)(t & 1);
   const IvlDesc iv = ivls[i];
-  const RegionDesc rd = regions[iv.region];
-  unsigned long long* acc = (unsigned long long*)(macc + (rd.times_off + iv.resource) * 4);
+  unsigned long long* acc = (unsigned long long*)(macc + iv.row * 4);
   if (l == 3) {
     if (ep) atomicAdd(acc + 3, (unsigned long long)(iv.b - iv.a));
     return;
   }
-  if (l >= (iv.resource < rd.n_hosts ? 3 : 2)) return;
-  const long long v = measure_before(p, rd.seg_begin + iv.resource, l, ep ? iv.b : iv.a);
+  if (l >= iv.n_levels) return;
+  const long long v = measure_before(p, iv.seg, l, ep ? iv.b : iv.a);
   atomicAdd(acc + l, (unsigned long long)(ep ? v : -v));  // two's complement: the sum is exact
 }
 
 template <int THREADS>
-__global__ __launch_bounds__(THREADS) void k_region_multi(const RegionDesc* regions, const long long* macc, Tree* trees,
-                                                          long long* times) {
+__global__ __launch_bounds__(THREADS) void k_region_multi(Plan p, const RegionDesc* regions, long long* macc,
+                                                          Tree* trees, long long* times, unsigned long long* status,
+                                                          bool reset) {
   __shared__ long long lds[THREADS / 64 * 10];
   __shared__ Tree tree;
   __shared__ long long semax[2][THREADS / 64];
+  if (status && blockIdx.x == 0) put_status(p, status, reset);
   const RegionDesc rd = regions[blockIdx.x];
   if (rd.n_ivl == 0) return;
   const int R = rd.n_hosts + rd.n_devices;
@@ -2583,8 +2588,9 @@ __global__ __launch_bounds__(THREADS) void k_region_multi(const RegionDesc* regi
   long long v[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
   long long eh = 0, ed = 0;
   for (int r = threadIdx.x; r < R; r += THREADS) {
-    const long long* a = macc + (rd.times_off + r) * 4;
+    long long* a = macc + (rd.times_off + r) * 4;
     const long long D[3] = {a[0], a[1], a[2]}, Er = a[3];
+    a[0] = a[1] = a[2] = a[3] = 0;
     const bool host = r < rd.n_hosts;
     add_times(host, D, Er, times + (rd.times_off + r) * 4, v);
     if (host) eh = Er > eh ? Er : eh;
@@ -2807,21 +2813,22 @@ hipError_t launch_base(const Plan& p, hipStream_t st) {
 
 hipError_t launch_region(const Plan& p, const RegionDesc* regions, int n_regions, int n_plain, int max_res, Tree* trees,
                          unsigned long long* status, bool reset, long long* times, const IvlDesc* ivls,
-                         long long n_ivls, long long* macc, hipStream_t st) {
-  if (n_plain == 0) {
+                         long long n_ivls, long long* macc, bool clear_macc, hipStream_t st) {
+  // the status words go with the last kernel (of plain regions, or of those by
+  // intervals), or alone
+  if (n_plain == 0 && n_ivls == 0) {
     hipLaunchKernelGGL(k_status, dim3(1), dim3(64), 0, st, p, status, reset);
-  } else {
+  } else if (n_plain > 0) {
     const int slice = max_res <= 16 || (long long)n_plain * max_res <= 8192 ? 8 : 32;
     const unsigned slices = (unsigned)std::max(1, (max_res + slice - 1) / slice);
     hipLaunchKernelGGL(k_region, dim3((unsigned)n_regions, slices), dim3(8 * slice), 0, st, p, regions, times, trees,
                        status, reset);
   }
   if (n_ivls > 0) {
-    hipLaunchKernelGGL(k_ivl_zero, dim3((unsigned)n_regions), dim3(256), 0, st, regions, macc);
-    hipLaunchKernelGGL(k_ivl_acc, dim3((unsigned)((8 * n_ivls + 255) / 256)), dim3(256), 0, st, p, regions, ivls,
-                       n_ivls, macc);
-    hipLaunchKernelGGL(k_region_multi<256>, dim3((unsigned)n_regions), dim3(256), 0, st, regions,
-                       (const long long*)macc, trees, times);
+    if (clear_macc) hipLaunchKernelGGL(k_ivl_zero, dim3((unsigned)n_regions), dim3(256), 0, st, regions, macc);
+    hipLaunchKernelGGL(k_ivl_acc, dim3((unsigned)((8 * n_ivls + 255) / 256)), dim3(256), 0, st, p, ivls, n_ivls, macc);
+    hipLaunchKernelGGL(k_region_multi<256>, dim3((unsigned)n_regions), dim3(256), 0, st, p, regions, macc, trees, times,
+                       n_plain == 0 ? status : nullptr, reset);
   }
   return hipGetLastError();
 }

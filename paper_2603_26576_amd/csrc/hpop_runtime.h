@@ -129,6 +129,7 @@ struct Engine {
   int graph_replays = 0;
   long long last_oversized = 0;
   char* result_host = nullptr;  // set: enqueue copies the results here; else kernels store them in ws.pinned
+  bool macc_clear = false;      // the last pass of this plan left the interval accumulators at zero
   bool result_times = false;    // with result_host: the state times too, at times_offset()
   size_t times_offset() const { return (size_t)((const char*)ws.d_times - (const char*)ws.d_trees); }
   // timing

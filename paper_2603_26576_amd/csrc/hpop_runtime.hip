@@ -423,6 +423,9 @@ hpop_status Engine::assemble(hpop_session* const* ss, int k, std::string& err) {
       rd.ivl_begin = (int64_t)h_ivls.size();
       for (IvlDesc iv : s->region_ivls[g]) {
         iv.region = (int32_t)h_regions.size();
+        iv.seg = seg_base + iv.resource;
+        iv.n_levels = iv.resource < s->n_hosts ? 3 : 2;
+        iv.row = times + iv.resource;
         h_ivls.push_back(iv);
       }
       times += R;
@@ -591,6 +594,7 @@ hpop_status Engine::prepare_plan(long long tiles, long long own_tiles, long long
   ws.plan.pad1 = 0;
   n_times = times;
   plan_passes = 0;
+  macc_clear = false;
   return HPOP_OK;
 }
 
@@ -721,8 +725,9 @@ hpop_status Engine::enqueue(bool build, bool with_timing, std::string& err) {
   Tree* trees = result_host ? ws.d_trees : (Tree*)ws.pinned.ptr;
   HPOP_HIP(pre("region"), "hipEventRecord");
   HPOP_HIP(launch_region(p, ws.d_regions, nreg, n_plain, max_res, trees, (unsigned long long*)(trees + nreg),
-                         true, ws.d_times, ws.d_ivls, (long long)h_ivls.size(), ws.d_macc, st),
+                         true, ws.d_times, ws.d_ivls, (long long)h_ivls.size(), ws.d_macc, !macc_clear, st),
            "k_region");
+  macc_clear = true;
   HPOP_HIP(mark("region"), "hipEventRecord");
   n_marks = ev;
   if (result_host)
