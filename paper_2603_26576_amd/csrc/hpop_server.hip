@@ -1123,6 +1123,10 @@ hpop_status hpop_server_create(const hpop_server_config* cfg, hpop_server** out)
     S->engine.alloc = S->alloc;
     S->engine.use_graphs = false;
     S->engine.keep_status = true;  // the splice kernels read them after the build
+    // page-locked memory for the tables and results of usual steps (a step that
+    // needs more grows it, which costs that step some hundred microseconds)
+    (void)S->h_out.reserve(256 << 10);
+    (void)S->engine.ws.pinned_desc.reserve(1 << 20);
     S->worker = std::thread(worker_loop, S);
     *out = S;
     return HPOP_OK;
