@@ -73,7 +73,8 @@ typedef int32_t hpop_status;
 
 /* flags of hpop_metrics_compute_all and hpop_batch_compute */
 #define HPOP_FORCE_REBUILD 1u /* rebuild the merged interval lists even if no record was added */
-#define HPOP_NO_GRAPH 2u      /* launch the kernels one by one instead of replaying the captured HIP graph */
+#define HPOP_NO_GRAPH 2u      /* launch the kernels one by one also where a captured HIP graph is replayed (forced
+                                 rebuilds and repeated plans of up to 256 Ki records) */
 
 typedef struct hpop_session hpop_session;
 typedef struct hpop_server hpop_server;
@@ -261,8 +262,8 @@ hpop_status hpop_metrics_compute_static(int32_t n_hosts, int32_t n_devices, cons
                                         int64_t* times_out);
 
 /* Batched evaluation: the records and regions of k sessions reduced together
- * in one launch sequence (captured once in a HIP graph and replayed while no
- * session changes). out receives every region of every session, session by
+ * in one launch sequence (up to 256 Ki records: captured once in a HIP graph and
+ * replayed while no session changes). out receives every region of every session, session by
  * session, regions in id order. All sessions must use the same HIP device;
  * the work runs on the first session's stream. */
 hpop_status hpop_batch_compute(hpop_session* const* sessions, int32_t k, uint32_t flags,

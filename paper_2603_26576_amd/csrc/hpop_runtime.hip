@@ -801,7 +801,15 @@ hpop_status Engine::run(hpop_session* const* ss, int k, uint32_t flags, hpop_met
     return run(ss, k, flags, out, timing, err);
   }
   built = false;
-  if (build && use_graphs && !timing && !(flags & HPOP_NO_GRAPH) && (plan_passes > 0 || (flags & HPOP_FORCE_REBUILD))) {
+  // A replay of the seven kernels takes 4-16 us longer on the device than their
+  // launches one by one, whose host time hides behind the first kernels: mid
+  // trace 174 against 166 us, 1.25e8 records 1111 against 1102, a batch of 128
+  // traces 379 against 363, 8e4 records 51 against 48. Builds of up to 256 Ki
+  // records keep the replay (and its count), as there the host would be busy
+  // launching for most of the build.
+  constexpr long long kGraphRecords = 256ll << 10;
+  if (build && use_graphs && !timing && !(flags & HPOP_NO_GRAPH) && ws.plan.n_elems <= kGraphRecords &&
+      (plan_passes > 0 || (flags & HPOP_FORCE_REBUILD))) {
     // a plan that comes again, or is said to by a forced rebuild: capture its
     // whole launch sequence once and replay it. The build that new records
     // ask for launches its kernels one by one, which costs less than the
