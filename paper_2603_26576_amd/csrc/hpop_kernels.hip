@@ -2619,7 +2619,7 @@ __global__ __launch_bounds__(THREADS) void k_region_multi(Plan p, const RegionDe
 // ----------------------------------------------------------------------------
 
 hipError_t launch_gather(const CopyChunk* chunks, int n, hipStream_t st) {
-  // a launch holds fewer than 2^31 threads: a chunk past that (1.7e10 records) is cut
+  // a launch holds fewer than 2^31 threads: a chunk past that (4.3e9 records) is cut
   constexpr long long kMaxPieces = 1ll << 22;
   GatherArgs g;
   g.n = 0;

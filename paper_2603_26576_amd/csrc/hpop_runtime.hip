@@ -533,7 +533,7 @@ hpop_status Engine::assemble_plan(const hpop_tuning& tun, const std::vector<long
 // results (keep_status) reads the ranges themselves.
 void Engine::plan_range(int n_segs, int slots) {
   h_seg_first.clear();
-  if (slots == 0 || exact_range || keep_status) return;
+  if (n_segs == 0 || slots == 0 || exact_range || keep_status) return;
   std::vector<int32_t> first((size_t)n_segs + 1, 0);
   for (const ChunkDesc& d : h_chunks)
     if (++first[(size_t)d.seg + 1] > kRangeChunks) return;

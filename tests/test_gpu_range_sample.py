@@ -112,3 +112,23 @@ def test_static_and_batch(outlier):
     finally:
         for s, _ in ss:
             hp.hpop_session_destroy(s)
+
+
+@pytest.mark.parametrize("hosts,devices", [(0, 0), (0, 2), (2, 0)])
+def test_no_resources_or_records(hosts, devices):
+    """Nothing to sample, with the passes apart (timing) and together, alone and in a batch."""
+    tr = tg.Trace(hosts, devices, [], [(tg.T0, tg.T0 + 1000)])
+    want = oracle.compute(tr)
+    full = trace(3000, np.random.default_rng(1))
+    s, _ = new_session(tr)
+    other, keep = new_session(full, device=True)
+    try:
+        for on in (0, 1, 0):
+            assert hp.lib().hpop_session_enable_timing(s, on) == hp.HPOP_OK
+            assert_same(engine_results(s, tr, hp.HPOP_FORCE_REBUILD), want)
+        got = hp.hpop_batch_compute([s, other], hp.HPOP_FORCE_REBUILD)
+        np.testing.assert_array_equal(np.array([hp.tree_sums(got[0])]), want["sums"])
+        np.testing.assert_array_equal(np.array([hp.tree_sums(t) for t in got[1:]]), oracle.compute(full)["sums"])
+    finally:
+        hp.hpop_session_destroy(s)
+        hp.hpop_session_destroy(other)
