@@ -166,8 +166,8 @@ struct Elem {  // one record regrouped by bucket (the 16 B form)
 // both: 8 B records in the low 32 bits, 16 B records in the high 32.
 constexpr int kRaccWords = 10;
 
-// Buckets the wave path hands over, in two sets of lists (to k_merge_rest and
-// to k_merge_block). Bucket b goes to list (b / 4) % kQueues; the lists' counts
+// Buckets the wave path hands over to k_merge_rest, in two sets of lists (for a
+// wave and for a workgroup). Bucket b goes to list (b / 4) % kQueues; the lists' counts
 // lie in cache lines of their own, so appends to different lists don't wait for
 // one another. With one list the wave path of 2.9e3 wide
 // buckets, all handed over, took 35 us instead of 5.

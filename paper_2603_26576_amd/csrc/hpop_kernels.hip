@@ -1530,7 +1530,7 @@ __device__ __forceinline__ void queue_push(const Plan& p, int set, long long gb)
 // their sorted places in LDS, then an insertion sort inside each sub-bin that
 // received two or more records (equal starts may end in any order: the merged
 // result does not depend on it). Other buckets (more records, any record in
-// the 16 B form, a crowded sub-bin) go to the block path's queue.
+// the 16 B form, a crowded sub-bin) go to k_merge_rest's lists.
 struct alignas(16) WaveSmem {
   unsigned int key[kWaveCap];        // sorted keys (then, with end[], the components of one level)
   unsigned int end[kWaveCap];        // ends of the sorted records
@@ -1978,7 +1978,7 @@ __device__ __forceinline__ bool wave_bucket(const Plan& p, WaveSmem& W, long lon
 
 // One bucket of ni records (1 <= ni <= kWaveCap, all in the 8 B form) by one
 // wave, with as many records per lane as it needs: every slot costs the same
-// instructions, filled or not. False: the bucket must take the block path.
+// instructions, filled or not. False: the bucket must be handed over.
 template <bool kSlots>
 __device__ __forceinline__ bool wave_merge(const Plan& p, WaveSmem& W, long long gb, long long off, int ni,
                                            const uint2* rec, const uint2 (&pre)[kWavePre], long long lo, int nlev,
@@ -1994,7 +1994,7 @@ __device__ __forceinline__ bool wave_merge(const Plan& p, WaveSmem& W, long long
 }
 
 // One wave per bucket, 8 waves per SIMD (64 VGPRs). Buckets that need the
-// block path go to its queue. kSlots: fixed slots of at least 128 records
+// k_merge_rest go to its lists. kSlots: fixed slots of at least 128 records
 // (2 slot_cap record places per bucket, whatever its count).
 template <bool kSlots>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_merge_wave(Plan p) {
@@ -2022,7 +2022,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
     br.n16 = (int)(cu >> 32);
     br.overflow = (long long)br.n8 + br.n16 > (long long)p.slot_cap;
     br.narrow = (const uint2*)p.elems + 2 * gb * (long long)p.slot_cap;
-    br.wide = nullptr;  // never read here: such buckets take the block path
+    br.wide = nullptr;  // never read here: such buckets are handed over
   } else {
     br = bucket_recs(p, gb);
   }
@@ -2138,7 +2138,7 @@ struct SmallSmem {
   unsigned long long maxe[kSmallBuckets * 3];
   long long carry[kSmallBuckets * 3];
   unsigned int off[kSmallBuckets];        // merged-interval offset within the segment
-  unsigned int queue[kSmallBuckets];      // buckets for the block path
+  unsigned int queue[kSmallBuckets];      // buckets the wave merges left
   unsigned int nq;
   const int64_t* s[kSmallChunks];
   const int64_t* e[kSmallChunks];

@@ -186,7 +186,7 @@ hpop_status Workspace::prepare(Alloc& a, long long n_chunks, long long n_tiles, 
   small += carve_bytes(n_buckets, sizeof(unsigned long long));
   small += carve_bytes(3 * n_buckets, sizeof(unsigned long long));
   small += carve_bytes(3 * n_buckets, sizeof(long long)) * 2;
-  // the measures before each bucket come last, so their place holds the block path's lists until then
+  // the measures before each bucket come last, so their place holds k_merge_rest's lists until then
   const long long queue_cap = 4 * (n_buckets / (4 * kQueues) + 1);
   const long long queue_words = 2 * kQueues * (queue_cap + kQueuePad);
   const long long base_words = std::max(3 * n_buckets, (queue_words + 1) / 2);
@@ -549,7 +549,7 @@ void Engine::plan_range(int n_segs, int slots) {
 bool Engine::plan_small(const std::vector<long long>& seg_count, int slots, int cap) {
   h_sseg.clear();
   // the passes' own times are wanted; a merge of fixed slots needs 128 of
-  // them, and the workgroup's block path holds 2048 records
+  // them, and what they leave is sorted 2048 records at a time
   if (staged || slots < 128 || cap != 2048 || seg_count.empty()) return false;
   for (size_t r = 0; r < seg_count.size(); ++r)
     if (seg_count[r] > kSmallRecords || h_segs[r].nb > kSmallBuckets) return false;
