@@ -105,3 +105,8 @@ def test_invalid_record_is_named_and_dropped():
         assert_same(engine_results(s, tr), oracle.compute(tr), "after the drop")
     finally:
         hp.hpop_session_destroy(s)
+
+
+@pytest.mark.parametrize("devices", [511, 512])
+def test_most_segments_of_the_path_and_one_more(devices):
+    check(trace(70, np.random.default_rng(devices), n_devices=devices))
