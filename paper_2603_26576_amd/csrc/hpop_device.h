@@ -6,6 +6,7 @@
 
 #include "hpop_geom.h"
 #include "hpop_internal.h"
+#include "hpop_lds.h"
 
 namespace hpop {
 
@@ -478,20 +479,6 @@ __device__ __forceinline__ double ratio(long long num, long long den, int bit, u
   return (double)num / (double)den;
 }
 
-
-// LDS of the sorting workgroups (one bucket or one list tile at a time).
-template <int THREADS, int CAP>
-struct SortSmem {
-  static constexpr int NW = THREADS / 64;
-  Elem E[CAP];
-  unsigned short ordA[CAP];
-  unsigned short ordB[CAP];
-  unsigned int whist[THREADS < 256 ? 1 : NW * 256];  // the radix passes' (a thread per digit)
-  unsigned int dstart[THREADS < 256 ? 1 : 256];
-  unsigned int dcount[THREADS < 256 ? 1 : 256];
-  long long lds_scan[NW * 6];
-  unsigned long long red[2][NW];
-};
 
 // Block-wide OR and AND of per-thread key accumulators: the bits in which keys differ.
 template <int THREADS>

@@ -8,8 +8,6 @@ namespace hpop {
 
 constexpr int kScanTile = 1024;  // bucket counts per workgroup of the offset scan
 constexpr int kHistWin = 512;    // LDS bucket window of one streaming tile
-constexpr int kWaveCap = 512;    // records one wave sorts and flattens on its own
-constexpr int kWaveBins = 512;   // sub-bins of the wave path's counting sort (at most)
 
 // One add call's chunk to copy into the record arena: `count` starts to dst_s, ends to dst_e.
 struct CopyChunk {

@@ -1531,11 +1531,6 @@ __device__ __forceinline__ void queue_push(const Plan& p, int set, long long gb)
 // received two or more records (equal starts may end in any order: the merged
 // result does not depend on it). Other buckets (more records, any record in
 // the 16 B form, a crowded sub-bin) go to k_merge_rest's lists.
-struct alignas(16) WaveSmem {
-  unsigned int key[kWaveCap];        // sorted keys (then, with end[], the components of one level)
-  unsigned int end[kWaveCap];        // ends of the sorted records
-  unsigned int bins[kWaveBins / 2];  // two 16-bit counters (then sub-bin starts) per word
-};
 
 // N consecutive LDS words from a position that is a multiple of N: 16-byte
 // reads when N is a multiple of 4, 8-byte reads when it is even, else words
@@ -2070,11 +2065,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
 template <int THREADS, int CAP>
 __global__ __launch_bounds__(THREADS, CAP == 2048 ? 3 : 1) void k_merge_rest(Plan p) {
   constexpr int NW = THREADS / 64;
-  __shared__ union {
-    SortSmem<THREADS, CAP> block;
-    SortSmem<64, kWaveCap> one[NW];
-    WaveSmem w[NW];
-  } u;
+  __shared__ RestSmem<THREADS, CAP> u;
   {
     const QueueView v = queue_view(p, 1);
     for (unsigned int idx = blockIdx.x; idx < v.total; idx += gridDim.x) merge_bucket<THREADS, CAP>(p, v.at(idx), u.block);
@@ -2099,10 +2090,10 @@ __global__ __launch_bounds__(THREADS, CAP == 2048 ? 3 : 1) void k_merge_rest(Pla
       const SegDesc sd = p.segs[seg];
       const long long lo = bucket_lo(seg_geom(p, seg), gb - sd.bucket_begin);
       const uint2 pre[kWavePre] = {};
-      done = wave_bucket<8, false, true>(p, u.w[wave], gb, off, br.n8, br.narrow, pre, lo, sd.n_levels, carry, maxe);
+      done = wave_bucket<8, false, true>(p, u.wave[wave].w, gb, off, br.n8, br.narrow, pre, lo, sd.n_levels, carry, maxe);
       wave_sync();
     }
-    if (!done) merge_bucket<64, kWaveCap>(p, gb, u.one[wave]);
+    if (!done) merge_bucket<64, kWaveCap>(p, gb, u.wave[wave].one);
   }
 }
 
