@@ -66,10 +66,12 @@ __host__ __device__ inline int bucket_of_start(const Geom& g, long long s) {
 }
 
 // whether a start lies in the range its segment's buckets cover (always, where
-// that is the range of all of its records)
+// that is the range of all of its records). Past 2^31 units bucket_index gives
+// the last bucket, which with many narrow buckets is not the start's.
 __host__ __device__ inline bool start_in_range(const Geom& g, long long s) {
   // nb * wx <= 2^31 + nb: 32 bits
-  return ((unsigned long long)(s - g.min_s) >> g.s0) < (unsigned long long)(g.empty ? 0u : (unsigned int)g.nb * g.wx);
+  const unsigned int cover = g.empty ? 0u : (unsigned int)g.nb * g.wx;
+  return ((unsigned long long)(s - g.min_s) >> g.s0) < (cover < (1u << 31) ? cover : 1u << 31);
 }
 
 // buckets at most 2^kNarrowShift ns wide: records and components fit the 8 B forms
