@@ -65,9 +65,12 @@ constexpr int kSmallBuckets = 64;    // buckets
 
 // Sampled start ranges (k_range): kRangeSample starts of each chunk, half from
 // its front and half from its back (records arrive roughly in time order), and
-// 1 / 2^kRangePad of what they span on either side. Records in any order pass
-// too: the chance that one of a segment lies outside is below 3e-7. Plans with
-// a segment of more than kRangeChunks chunks read every start.
+// 1 / 2^kRangePad of what they span on either side. A sample does not always
+// hold: records spread evenly over their range pass in any order (a miss has a
+// chance below 3e-7 per segment), a few apart from the rest in the middle of a
+// chunk are outside, and the build is then redone with every start read (see
+// RangeChoice). Plans with a segment of more than kRangeChunks chunks read every
+// start.
 constexpr int kRangeSample = 2048;
 constexpr int kRangePad = 7;
 constexpr int kRangeChunks = 64;

@@ -8,6 +8,7 @@
 
 #include "hpop.h"
 #include "hpop_internal.h"
+#include "hpop_range.h"
 
 namespace hpop {
 
@@ -107,7 +108,8 @@ struct Engine {
   std::vector<SmallSeg> h_sseg;       // not empty: every segment is small (see k_build_small)
   std::vector<int32_t> h_seg_first;   // not empty: start ranges from a sample (see k_range), with
   std::vector<int32_t> h_seg_chunk;   // the chunks by segment
-  bool exact_range = false;           // a start lay outside a sampled range: read every start from then on
+  RangeChoice range;                  // whether they are to come from one
+  std::vector<unsigned long long> range_versions;  // of the sessions whose starts are read in full
   bool staged = false;                // the plan keeps the build's passes apart (their times are wanted)
   bool keep_status = false;           // only builds are enqueued: the caller's kernels read what they leave
   int plan_passes = 0;                // builds run with the current plan

@@ -533,7 +533,7 @@ hpop_status Engine::assemble_plan(const hpop_tuning& tun, const std::vector<long
 // results (keep_status) reads the ranges themselves.
 void Engine::plan_range(int n_segs, int slots) {
   h_seg_first.clear();
-  if (n_segs == 0 || slots == 0 || exact_range || keep_status) return;
+  if (n_segs == 0 || slots == 0 || range.exact || keep_status) return;
   std::vector<int32_t> first((size_t)n_segs + 1, 0);
   for (const ChunkDesc& d : h_chunks)
     if (++first[(size_t)d.seg + 1] > kRangeChunks) return;
@@ -775,6 +775,15 @@ hpop_status Engine::run(hpop_session* const* ss, int k, uint32_t flags, hpop_met
       forced_versions.clear();
     }
   }
+  auto versions = [&] {
+    std::vector<unsigned long long> v;
+    for (int i = 0; i < k; ++i) v.push_back(ss[i]->version);
+    return v;
+  };
+  if (!same && range.exact && versions() != range_versions) {
+    range.new_records();
+    range_versions = versions();
+  }
   const size_t nreg_total = [&] {
     size_t t = 0;
     for (int i = 0; i < k; ++i) t += ss[i]->regions.size();
@@ -859,10 +868,12 @@ hpop_status Engine::run(hpop_session* const* ss, int k, uint32_t flags, hpop_met
   if (build) last_oversized = (long long)over;
   if (build && bad == ULLONG_MAX && (slot_over & kRangeMiss)) {
     // a start outside its segment's sampled range: redo this plan with every start read
-    exact_range = true;
+    range.missed();
+    range_versions = versions();
     key_sessions.clear();
     return run(ss, k, flags | HPOP_FORCE_REBUILD, out, timing, err);
   }
+  if (build && ws.plan.seg_first && !(slot_over & kRangeMiss)) range.held();
   if (build && bad == ULLONG_MAX && ws.plan.slot_cap > 0 && slot_over > 0) {
     // a bucket outgrew its fixed slots: redo this plan with exact offsets
     exact_forced = true;

@@ -186,7 +186,8 @@ extern "C" hpop_status hpop_metrics_compute_static(int32_t n_hosts, int32_t n_de
     std::lock_guard<std::mutex> g(d->mu);
     Engine& E = d->engine;
     E.alloc.stream = (hipStream_t)stream;
-    E.exact_forced = E.exact_range = false;
+    E.exact_forced = false;
+    E.range = RangeChoice{};
     const size_t bt = (size_t)n_regions * sizeof(Tree);
     std::string err;
     for (int attempt = 0; attempt < 3; ++attempt) {
@@ -214,7 +215,7 @@ extern "C" hpop_status hpop_metrics_compute_static(int32_t n_hosts, int32_t n_de
       }
       if (slot_over & kRangeMiss) {
         // a start outside its resource's sampled range: the same call with every start read
-        E.exact_range = true;
+        E.range.missed();
         continue;
       }
       if (slot_over > 0 && E.ws.plan.slot_cap > 0) {
