@@ -108,7 +108,8 @@ struct Engine {
   std::vector<SmallSeg> h_sseg;       // not empty: every segment is small (see k_build_small)
   std::vector<int32_t> h_seg_first;   // not empty: start ranges from a sample (see k_range), with
   std::vector<int32_t> h_seg_chunk;   // the chunks by segment
-  RangeChoice range;                  // whether they are to come from one
+  bool sample_ranges = true;          // they may come from one
+  RangeChoice range;                  // whether the present records' do
   std::vector<unsigned long long> range_versions;  // of the sessions whose starts are read in full
   bool staged = false;                // the plan keeps the build's passes apart (their times are wanted)
   bool keep_status = false;           // only builds are enqueued: the caller's kernels read what they leave

@@ -530,10 +530,11 @@ hpop_status Engine::assemble_plan(const hpop_tuning& tun, const std::vector<long
 // Whether the segments' start ranges come from a sample, and the chunks by
 // segment for it. Fixed slots only: an exact build is the one whose records
 // already had their way with a guess. A caller that takes over the build's
-// results (keep_status) reads the ranges themselves.
+// results (keep_status) reads the ranges themselves, and one whose calls share
+// nothing (the entry point without allocation) would pay for a miss on each.
 void Engine::plan_range(int n_segs, int slots) {
   h_seg_first.clear();
-  if (n_segs == 0 || slots == 0 || range.exact || keep_status) return;
+  if (n_segs == 0 || slots == 0 || !sample_ranges || range.exact || keep_status) return;
   std::vector<int32_t> first((size_t)n_segs + 1, 0);
   for (const ChunkDesc& d : h_chunks)
     if (++first[(size_t)d.seg + 1] > kRangeChunks) return;

@@ -62,6 +62,7 @@ hpop_status device_state(int dev, StaticDevice** out) {
     d->engine.alloc.fn_alloc = refuse_alloc;
     d->engine.alloc.fn_free = ignore_free;
     d->engine.use_graphs = false;
+    d->engine.sample_ranges = false;
     d->engine.ws.fixed = p;
     d->engine.ws.fixed_bytes = kScratchBytes;
     g_devices[dev] = d;
@@ -187,10 +188,9 @@ extern "C" hpop_status hpop_metrics_compute_static(int32_t n_hosts, int32_t n_de
     Engine& E = d->engine;
     E.alloc.stream = (hipStream_t)stream;
     E.exact_forced = false;
-    E.range = RangeChoice{};
     const size_t bt = (size_t)n_regions * sizeof(Tree);
     std::string err;
-    for (int attempt = 0; attempt < 3; ++attempt) {
+    for (int attempt = 0; attempt < 2; ++attempt) {
       st = plan(*d, n_hosts, n_devices, chunks, n_chunks, region_t0, region_t1, n_regions, err);
       if (st != HPOP_OK) return fail(st, err);
       // the state times lie behind the trees: up to a MiB they come along with
@@ -212,11 +212,6 @@ extern "C" hpop_status hpop_metrics_compute_static(int32_t n_hosts, int32_t n_de
         const int ci = cid < d->chunk_index.size() ? d->chunk_index[cid] : -1;
         return fail(HPOP_E_BAD_INTERVAL, "invalid record: chunk " + std::to_string(ci) + ", index " +
                                              std::to_string(idx) + " (need 0 <= start <= end < 2^62)");
-      }
-      if (slot_over & kRangeMiss) {
-        // a start outside its resource's sampled range: the same call with every start read
-        E.range.missed();
-        continue;
       }
       if (slot_over > 0 && E.ws.plan.slot_cap > 0) {
         // a bucket outgrew its fixed slots: the same call with exact offsets

@@ -1,6 +1,8 @@
 """Sets of records with and without a start outside its sampled range, in one
 session and in a batch that goes on: every answer is the oracle's, whichever
 of them are sampled and whichever are read in full."""
+import time
+
 import numpy as np
 import pytest
 import torch  # noqa: F401  (its HIP runtime is loaded before the library's)
@@ -58,3 +60,33 @@ def test_session_and_batch_go_on(row):
     finally:
         for s in ss:
             hp.hpop_session_destroy(s)
+
+
+def test_static_calls_build_once():
+    """Calls that share nothing don't pay for a start apart from the others: with one they take
+    as long as without (1.0-1.1 times; building twice takes 1.8 times as long)."""
+    rng = np.random.default_rng(4)
+    n, R, span = 60_000, 16, 60_000 * 60_000
+    calls, wants = [], []
+    for outlier in (False, True):
+        chunks = []
+        for r in range(R):
+            s = tg.T0 + span // 8 + np.sort(rng.integers(0, span, size=n))
+            if outlier and r == 0:
+                s[n // 2] = tg.T0 + span // 16
+            chunks.append(tg.Chunk(r, tg.DEV_KERNEL, s, s + rng.integers(0, 60_000, size=n)))
+        tr = tg.Trace(0, R, chunks, [(tg.T0, tg.T0 + 2 * span)])
+        dev = [(c.resource, c.kind, torch.from_numpy(c.start).cuda(), torch.from_numpy(c.end).cuda()) for c in chunks]
+        calls.append((dev, tr.regions))
+        wants.append(oracle.compute(tr)["sums"])
+    torch.cuda.synchronize()
+    took = ([], [])
+    for _ in range(41):
+        for k, (dev, regs) in enumerate(calls):
+            t = time.perf_counter()
+            trees = hp.hpop_metrics_compute_static(0, R, dev, regs)
+            took[k].append(time.perf_counter() - t)
+            np.testing.assert_array_equal(np.array([hp.tree_sums(x) for x in trees]), wants[k])
+    plain, odd = (sorted(v)[20] for v in took)
+    print("static: %.1f us, with a start apart %.1f us" % (1e6 * plain, 1e6 * odd), flush=True)
+    assert odd < 1.5 * plain
