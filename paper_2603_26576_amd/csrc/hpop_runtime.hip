@@ -872,7 +872,7 @@ hpop_status Engine::run(hpop_session* const* ss, int k, uint32_t flags, hpop_met
     range.missed();
     range_versions = versions();
     key_sessions.clear();
-    return run(ss, k, flags | HPOP_FORCE_REBUILD, out, timing, err);
+    return run(ss, k, flags, out, timing, err);  // the keys are gone: a new plan, and a build
   }
   if (build && ws.plan.seg_first && !(slot_over & kRangeMiss)) range.held();
   if (build && bad == ULLONG_MAX && ws.plan.slot_cap > 0 && slot_over > 0) {
@@ -882,7 +882,7 @@ hpop_status Engine::run(hpop_session* const* ss, int k, uint32_t flags, hpop_met
     for (int i = 0; i < k; ++i) forced_versions.push_back(ss[i]->version);
     forced_tuning = tuning_key(ss[0]->tuning);
     key_sessions.clear();
-    return run(ss, k, flags | HPOP_FORCE_REBUILD, out, timing, err);
+    return run(ss, k, flags, out, timing, err);  // the keys are gone: a new plan, and a build
   }
   if (bad != ULLONG_MAX) {
     const unsigned long long cid = bad >> 40, idx = bad & ((1ull << 40) - 1);
