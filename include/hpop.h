@@ -274,7 +274,9 @@ hpop_status hpop_session_set_tuning(hpop_session* s, const hpop_tuning* t);
 hpop_status hpop_session_get_tuning(const hpop_session* s, hpop_tuning* out);
 
 /* Per-kernel device time of the last build and clip, measured with HIP
- * events on the session stream when enabled (off by default).
+ * events on the session stream when enabled (off by default). A timed build
+ * always runs as separate passes; an untimed one of up to 512 resources of at
+ * most 4096 records each runs as one kernel, whose time is not their sum.
  * names/ms receive up to `cap` entries; *n_out the number written. */
 hpop_status hpop_session_enable_timing(hpop_session* s, int32_t on);
 hpop_status hpop_session_stage_times(const hpop_session* s, int32_t cap, const char** names,

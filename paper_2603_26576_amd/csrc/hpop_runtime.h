@@ -111,7 +111,8 @@ struct Engine {
   bool sample_ranges = true;          // they may come from one
   RangeChoice range;                  // whether the present records' do
   std::vector<unsigned long long> range_versions;  // of the sessions whose starts are read in full
-  bool staged = false;                // the plan keeps the build's passes apart (their times are wanted)
+  bool staged = false;                // the plan was made for a timed build, which keeps the passes apart
+  bool small_fits = false;            // k_build_small could take the plan's segments (not in a timed build)
   bool keep_status = false;           // only builds are enqueued: the caller's kernels read what they leave
   int plan_passes = 0;                // builds run with the current plan
   std::vector<RegionDesc> h_regions;

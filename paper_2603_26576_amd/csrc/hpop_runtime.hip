@@ -549,9 +549,10 @@ void Engine::plan_range(int n_segs, int slots) {
 // put next to each other in the chunk table (h_sseg).
 bool Engine::plan_small(const std::vector<long long>& seg_count, int slots, int cap) {
   h_sseg.clear();
-  // the passes' own times are wanted; a merge of fixed slots needs 128 of
-  // them, and what they leave is sorted 2048 records at a time
-  if (staged || slots < 128 || cap != 2048 || seg_count.empty()) return false;
+  small_fits = false;
+  // a merge of fixed slots needs 128 of them, and what they leave is sorted
+  // 2048 records at a time
+  if (slots < 128 || cap != 2048 || seg_count.empty()) return false;
   // one round of its workgroups, two per CU: a rebuild of 512 segments of 450
   // records takes 55 us so and 59 by the passes, of 768 61 and 58, of 2048 94
   // and 70 (of 60 records: 52 and 57, 62 and 59, 89 and 67)
@@ -561,6 +562,8 @@ bool Engine::plan_small(const std::vector<long long>& seg_count, int slots, int 
   std::vector<int> n(seg_count.size() + 1, 0);
   for (const ChunkDesc& d : h_chunks)
     if (++n[(size_t)d.seg + 1] > kSmallChunks) return false;
+  small_fits = true;
+  if (staged) return false;  // the passes' own times are wanted
   for (size_t r = 0; r < seg_count.size(); ++r) n[r + 1] += n[r];
   h_sseg.resize(seg_count.size());
   long long elem0 = 0;
@@ -679,7 +682,7 @@ hpop_status Engine::enqueue(bool build, bool with_timing, std::string& err) {
     HPOP_HIP(launch_build_small(p, st), "k_build_small");
   } else if (build) {
     // a sampled range takes the reset along, unless that pass's own time is wanted
-    const bool with_reset = p.seg_first && !staged;
+    const bool with_reset = p.seg_first && !with_timing;
     HPOP_HIP(pre("reset"), "hipEventRecord");
     if (!with_reset) HPOP_HIP(launch_reset(p, st), "k_reset");
     HPOP_HIP(mark("reset"), "hipEventRecord");
@@ -758,13 +761,16 @@ hpop_status Engine::collect_timing(std::string& err) {
 hpop_status Engine::run(hpop_session* const* ss, int k, uint32_t flags, hpop_metric_tree* out, bool timing,
                         std::string& err) {
   // does the current plan still describe these sessions?
-  bool same = (int)key_sessions.size() == k && built && staged == timing;
+  bool same = (int)key_sessions.size() == k && built;
   if (same) {
     for (int i = 0; i < k; ++i)
       if (key_sessions[i] != ss[i] || key_versions[i] != ss[i]->version || key_arena[i] != ss[i]->arena.ptr ||
           key_regions[i] != ss[i]->regions.size() || key_tuning[i] != tuning_key(ss[i]->tuning))
         same = false;
   }
+  // timed builds keep the passes apart: a small plan made for the other kind is
+  // made again, but only for a build (timing switched on or off asks for none)
+  if (same && (flags & HPOP_FORCE_REBUILD) && small_fits && staged != timing) same = false;
   const bool build = !same || (flags & HPOP_FORCE_REBUILD);
   if (!same && exact_forced) {
     // new records, another session set or another tuning (slots follow the
