@@ -110,14 +110,18 @@ typedef struct {
     uint32_t reserved;
 } hpop_metric_tree;
 
-/* Tuning of the reduction kernels (see hpop_autotune). Zero fields keep defaults. */
+/* Tuning of the reduction kernels (see hpop_autotune). Zero fields keep defaults;
+ * hpop_session_get_tuning reports them as a build of the session's present
+ * records takes them. */
 typedef struct {
-    int32_t bucket_target;  /* records per time bucket of a resource, before rounding the bucket
-                               count up to a power of two (16 .. 4096); 0 = chosen by the build's
-                               records (reported as 352) */
+    int32_t bucket_target;  /* records per time bucket of a resource: ceil(records / bucket_target)
+                               buckets (16 .. 4096); 0 = chosen by the build's records: 320 up to
+                               32 Mi, else 352 */
     int32_t bucket_cap;     /* records a bucket may hold for the on-chip sort: 2048 or 4096 */
     int32_t tile_elems;     /* records per workgroup in the streaming passes: 512, 2048, 4096 or 8192;
-                               0 = chosen by the build's records (reported as 4096) */
+                               0 = chosen by the build's records: 512 up to 128 Ki, else 2048.
+                               512 and 2048 asked for always let small batches share a workgroup,
+                               chosen ones only where most batches are small */
     int32_t scatter_slots;  /* records reserved per bucket by the single-pass scatter: 0 = 4 x
                                bucket_target (at most bucket_cap), -1 = always count first
                                (exact two-pass). A bucket that outgrows its slots makes the

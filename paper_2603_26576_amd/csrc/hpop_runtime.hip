@@ -366,7 +366,7 @@ static void tuned(const hpop_tuning& t, long long records, int& target, int& cap
   // builds of few records, so that the streaming passes still spread over the
   // 256 CUs (whole rebuilds with tiles of 512 / 2048 / 4096: 65 / 68 / 69 us for
   // 8e4 records, 73 / 69 / 76 for 3e5, 116 / 97 / 99 for 1e6)
-  if (t.tile_elems == 0 && records < LLONG_MAX) tile = records <= (128ll << 10) ? 512 : 2048;
+  if (t.tile_elems == 0) tile = records <= (128ll << 10) ? 512 : 2048;
   // single-pass scatter slots: 4x the mean bucket, within the on-chip capacity
   if (t.scatter_slots < 0) slots = 0;
   else if (t.scatter_slots > 0) slots = std::min(cap, pow2ceil(std::max(64, t.scatter_slots)));
@@ -1409,7 +1409,8 @@ hpop_status hpop_session_set_tuning(hpop_session* s, const hpop_tuning* t) {
 hpop_status hpop_session_get_tuning(const hpop_session* s, hpop_tuning* out) {
   if (!s || !out) return HPOP_E_ARG;
   int target, cap, tile, slots;
-  tuned(s->tuning, LLONG_MAX, target, cap, tile, slots);  // the tile size asked for (4096: none was)
+  // what a build of the present records takes, so that setting it back changes nothing
+  tuned(s->tuning, s->n_events, target, cap, tile, slots);
   out->bucket_target = target;
   out->bucket_cap = cap;
   out->tile_elems = tile;
