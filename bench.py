@@ -55,7 +55,7 @@ def log(*a):
 
 # the sources that define the build kernels (their code, launch shapes and data layout)
 KERNEL_SOURCES = ("hpop_kernels.hip", "hpop_kernels.h", "hpop_device.h", "hpop_geom.h", "hpop_internal.h",
-                  "hpop_lds.h")
+                  "hpop_lds.h", "hpop_search.h")
 
 
 def kernel_source_hash():

@@ -123,12 +123,12 @@ __device__ __forceinline__ long long list_measure(const ListDev& L, long long t)
   const Comp* c = L.base;
   // lists hold up to millions of entries: five probes by interpolation before halving
   (void)find_comp<5>(
-      [&](int k, long long& s, long long& m) {
+      [&](long long k, long long& s, long long& m) {
         const Comp v = c[k];
         s = v.cs - first.cs;
         m = v.pl;
       },
-      (int)L.len, (long long)(t - first.cs), (long long)(last.cs - first.cs + 1), L.total, cs, pl, next);
+      L.len, (long long)(t - first.cs), (long long)(last.cs - first.cs + 1), L.total, cs, pl, next);
   cs += first.cs;
   const long long ce = cs + (next - pl);
   return pl + (ce < t ? ce : t) - cs;
