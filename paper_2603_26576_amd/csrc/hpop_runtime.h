@@ -90,6 +90,7 @@ struct Workspace {
   // (no allocation, no page-locked staging); fixed_needed is the last plan's size
   char* fixed = nullptr;
   size_t fixed_bytes = 0;
+  size_t fixed_margin = 0;  // bytes behind them (see prepare)
   size_t fixed_needed = 0;
   hpop_status prepare(Alloc& a, long long n_chunks, long long n_tiles, long long n_segs, long long n_buckets,
                       long long n_elems,

@@ -212,10 +212,14 @@ hpop_status Workspace::prepare(Alloc& a, long long n_chunks, long long n_tiles, 
   char* compn_p[3];
   if (fixed) {
     // one caller-provided region holds everything, in this order
+    // (fixed_margin more bytes lie behind the limit, for what the accumulators'
+    // slice counts, the handed-over buckets' lists and smaller tiles take beyond
+    // what a build needed when the limit was set: 8 B per region and 32 KiB)
+    const size_t beyond = std::min(fixed_margin, (size_t)n_regions * 8 + (32u << 10));
     fixed_needed = small + big_e + big_e2 + 3 * (big_c + big_n);
-    if (fixed_needed > fixed_bytes) {
+    if (fixed_needed > fixed_bytes + beyond) {
       err = "the build needs " + std::to_string(fixed_needed) + " bytes of scratch; " +
-            std::to_string(fixed_bytes) + " are available";
+            std::to_string(fixed_bytes + beyond) + " are available";
       return HPOP_E_ARG;
     }
     char* c = fixed;

@@ -22,11 +22,12 @@ using namespace hpop;
 // One copy per GPU, loaded with this file's code object and held until the
 // process ends. Host code never passes this name to a kernel or a copy: it
 // is a host-side stand-in; the device address comes from hipGetSymbolAddress.
-static __device__ __align__(256) unsigned char scratch[HPOP_STATIC_SCRATCH_BYTES];
+// The margin covers 8 B for each region that fits with its tree (296 B and more).
+constexpr size_t kScratchBytes = HPOP_STATIC_SCRATCH_BYTES, kScratchMargin = (size_t)8 << 20;
+static __device__ __align__(256) unsigned char scratch[kScratchBytes + kScratchMargin];
 
 namespace {
 
-constexpr size_t kScratchBytes = HPOP_STATIC_SCRATCH_BYTES;
 
 void* refuse_alloc(void*, size_t, void*) { return nullptr; }  // nothing here may allocate
 void ignore_free(void*, void*, void*) {}
@@ -65,6 +66,7 @@ hpop_status device_state(int dev, StaticDevice** out) {
     d->engine.sample_ranges = false;
     d->engine.ws.fixed = p;
     d->engine.ws.fixed_bytes = kScratchBytes;
+    d->engine.ws.fixed_margin = kScratchMargin;
     g_devices[dev] = d;
   }
   *out = g_devices[dev];
@@ -160,13 +162,22 @@ hpop_status plan(StaticDevice& d, int32_t n_hosts, int32_t n_devices, const hpop
   long long records = 0;
   for (long long n : seg_count) records += n;
   if (records > (1ll << 20)) defaults.bucket_target = 352;
-  hpop_status st = E.assemble_plan(defaults, seg_count, seg_host, 1, (long long)n_regions * R, err);
-  if (st == HPOP_E_ARG && E.ws.fixed_needed > E.ws.fixed_bytes && !E.exact_forced) {
+  auto assemble = [&] {
+    const hpop_status st = E.assemble_plan(defaults, seg_count, seg_host, 1, (long long)n_regions * R, err);
+    return st == HPOP_E_ARG && E.ws.fixed_needed > E.ws.fixed_bytes ? HPOP_E_OOM : st;  // for the scratch array
+  };
+  hpop_status st = assemble();
+  if (st == HPOP_E_OOM && !E.exact_forced) {
     // fixed scatter slots do not fit: exact offsets need less room
     E.exact_forced = true;
-    st = E.assemble_plan(defaults, seg_count, seg_host, 1, (long long)n_regions * R, err);
+    st = assemble();
   }
-  return st;
+  if (st == HPOP_E_OOM && defaults.bucket_target == 0) {
+    // nor do they: larger buckets need a little less
+    defaults.bucket_target = 352;
+    st = assemble();
+  }
+  return st == HPOP_E_OOM ? HPOP_E_ARG : st;
 }
 
 }  // namespace
