@@ -2467,9 +2467,15 @@ __global__ void k_status(Plan p, unsigned long long* status, bool reset) { put_s
 // threads per resource (level and end), clips them by binary search, writes
 // their state times and adds its sums and maxima to the region's accumulator.
 // The region's last slice to add makes the tree (FP64 ratios) and leaves the
-// accumulator clear. Only atomics pass between the slices, each one's results
-// back before the slice counts itself, so no fence is needed (a device-scope
-// release writes back the L2, which had made this slower than a second kernel).
+// accumulator clear. Only atomics pass between the slices: a wave asks for the
+// results of its adds and waits for them (s_waitcnt vmcnt(0): an atomic whose
+// result is back is done in memory) before one of its lanes counts the slice.
+// Relaxed atomics of several lanes are not ordered by the language, so the wait
+// stands in the code, and a test reads the order in what is built from it. What
+// the language offers costs more: a device-scope release per slice, which also
+// writes back the L2 (large trace 1117 -> 1149 us, mid 172 -> 176, a batch of 128
+// traces 376 -> 459), or the trees in a second kernel (1127 -> 1126, 168 -> 173,
+// 370 -> 378, 256 devices with their streams 528 -> 540).
 // A region of one slice needs no accumulator at all.
 //
 // The stage is a chain of about ten cache misses, and one CU has only so many
@@ -2511,8 +2517,8 @@ __global__ __launch_bounds__(256) void k_region(Plan p, const RegionDesc* region
       unsigned long long old = 0;
       if (threadIdx.x < 6) old = atomicAdd(acc + threadIdx.x, (unsigned long long)tot[threadIdx.x]);
       else if (threadIdx.x < 9) old = atomicMax(acc + threadIdx.x, (unsigned long long)tot[threadIdx.x]);
-      // the count is issued only once every lane's result is back
-      asm volatile("" ::"v"((unsigned int)old), "v"((unsigned int)(old >> 32)) : "memory");
+      // every lane's result is back, so its add is done in memory, before the count goes out
+      asm volatile("s_waitcnt vmcnt(0)" ::"v"((unsigned int)old), "v"((unsigned int)(old >> 32)) : "memory");
       if (threadIdx.x == 0) s_last = (int)atomicAdd(acc + 9, 1ull) == slices - 1;
     }
     __syncthreads();
