@@ -248,10 +248,9 @@ hpop_status hpop_region_format(hpop_session* s, int32_t region, int32_t format, 
  * hpop_resource_times (into times_out, optional: [n_regions][n + m][4]).
  * Chunk arrays must be device memory and are read in place. Every
  * intermediate lives in a library-owned device array of
- * HPOP_STATIC_SCRATCH_BYTES and 8 MiB per GPU, taken when the first call on
+ * HPOP_STATIC_SCRATCH_BYTES (and 32 KiB) per GPU, taken when the first call on
  * that GPU loads it and held until the process ends; each call overwrites it.
- * A call whose build needs more than HPOP_STATIC_SCRATCH_BYTES and 8 bytes per
- * region and 32 KiB fails with HPOP_E_ARG (message in
+ * A call whose build needs more than that fails with HPOP_E_ARG (message in
  * hpop_last_error(NULL) with the size needed). Calls on one GPU share that
  * array: within a process they are serialised by the library; work of one
  * call overlapping another's on the same GPU by other means would race.

@@ -99,16 +99,6 @@ __device__ __forceinline__ Elem widen(uint2 x, long long lo, const unsigned long
 // bucket of a valid record start inside its segment (min_s <= start <= max_s)
 __device__ __forceinline__ int bucket_of(long long s, const Geom& g) { return bucket_of_start(g, s); }
 
-// index of the last entry with key <= x in a sorted array of n int64 (n >= 1, a[0] <= x)
-__device__ __forceinline__ int upper_index_seg(const SegDesc* s, int n, long long x) {
-  int lo = 0, hi = n - 1;
-  while (lo < hi) {
-    int mid = (lo + hi + 1) >> 1;
-    if (s[mid].bucket_begin <= x) lo = mid; else hi = mid - 1;
-  }
-  return lo;
-}
-
 __device__ __forceinline__ long long wave_red_min(long long v) {
   for (int d = 32; d >= 1; d >>= 1) { long long o = __shfl_xor(v, d, 64); v = o < v ? o : v; }
   return v;
@@ -119,14 +109,6 @@ __device__ __forceinline__ unsigned long long wave_red_minu(unsigned long long v
 }
 __device__ __forceinline__ unsigned long long wave_red_maxu(unsigned long long v) {
   for (int d = 32; d >= 1; d >>= 1) { unsigned long long o = __shfl_xor(v, d, 64); v = o > v ? o : v; }
-  return v;
-}
-__device__ __forceinline__ long long wave_red_sum(long long v) {
-  for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
-  return v;
-}
-__device__ __forceinline__ long long wave_red_max(long long v) {
-  for (int d = 32; d >= 1; d >>= 1) { long long o = __shfl_xor(v, d, 64); v = o > v ? o : v; }
   return v;
 }
 

@@ -116,7 +116,6 @@ struct RegionDesc {
   int32_t n_devices;
   int32_t n_ivl;       // > 0: a region given as per-resource intervals (IvlDesc), not [t0, t1)
   int64_t times_off;   // offset (in resources) of the region's rows in the times array
-  int64_t ivl_begin;   // first IvlDesc of the region
 };
 
 // One interval of a region given per resource.

@@ -212,14 +212,13 @@ hpop_status Workspace::prepare(Alloc& a, long long n_chunks, long long n_tiles, 
   char* compn_p[3];
   if (fixed) {
     // one caller-provided region holds everything, in this order
-    // (fixed_margin more bytes lie behind the limit, for what the accumulators'
-    // slice counts, the handed-over buckets' lists and smaller tiles take beyond
-    // what a build needed when the limit was set: 8 B per region and 32 KiB)
-    const size_t beyond = std::min(fixed_margin, (size_t)n_regions * 8 + (32u << 10));
+    // (fixed_margin more bytes lie behind the limit, for what the handed-over
+    // buckets' lists and smaller tiles take beyond what a build needed when the
+    // limit was set)
     fixed_needed = small + big_e + big_e2 + 3 * (big_c + big_n);
-    if (fixed_needed > fixed_bytes + beyond) {
+    if (fixed_needed > fixed_bytes + fixed_margin) {
       err = "the build needs " + std::to_string(fixed_needed) + " bytes of scratch; " +
-            std::to_string(fixed_bytes + beyond) + " are available";
+            std::to_string(fixed_bytes + fixed_margin) + " are available";
       return HPOP_E_ARG;
     }
     char* c = fixed;
@@ -424,7 +423,6 @@ hpop_status Engine::assemble(hpop_session* const* ss, int k, std::string& err) {
       rd.n_devices = s->n_devices;
       rd.times_off = times;
       rd.n_ivl = (int32_t)s->region_ivls[g].size();
-      rd.ivl_begin = (int64_t)h_ivls.size();
       for (IvlDesc iv : s->region_ivls[g]) {
         iv.region = (int32_t)h_regions.size();
         iv.seg = seg_base + iv.resource;

@@ -22,8 +22,7 @@ using namespace hpop;
 // One copy per GPU, loaded with this file's code object and held until the
 // process ends. Host code never passes this name to a kernel or a copy: it
 // is a host-side stand-in; the device address comes from hipGetSymbolAddress.
-// The margin covers 8 B for each region that fits with its tree (296 B and more).
-constexpr size_t kScratchBytes = HPOP_STATIC_SCRATCH_BYTES, kScratchMargin = (size_t)8 << 20;
+constexpr size_t kScratchBytes = HPOP_STATIC_SCRATCH_BYTES, kScratchMargin = 32u << 10;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes + kScratchMargin];
 
 namespace {
@@ -154,7 +153,6 @@ hpop_status plan(StaticDevice& d, int32_t n_hosts, int32_t n_devices, const hpop
     rd.n_devices = n_devices;
     rd.n_ivl = 0;
     rd.times_off = (int64_t)g * R;
-    rd.ivl_begin = 0;
     E.h_regions.push_back(rd);
   }
   // a build near the scratch's limits takes the larger buckets, of which it needs fewer
