@@ -601,15 +601,18 @@ __device__ __forceinline__ bool sort_bins(SortSmem<THREADS, CAP>& sm, int n, lon
   group_sync<THREADS>();
   bool crowded = false;
   if (sh > 0) {
-    // the thread that placed a sub-bin's second record puts it in order
+    // the thread that placed a sub-bin's second record puts it in order; a
+    // larger one needs no order where its starts are all equal
 #pragma unroll
     for (int r = 0; r < MAXR; ++r) {
-      if (tid + r * THREADS < n && rk[r] == 1) {
+      const int i = tid + r * THREADS;
+      if (i < n && rk[r] >= 1) {
         const unsigned int st = start_of(bin[r]), c = stop_of(bin[r]) - st;
         if (c > kBinCrowd) {
-          crowded = true;
+          crowded |= sm.E[i].s != sm.E[sm.ordA[st]].s;
           continue;
         }
+        if (rk[r] > 1) continue;
         unsigned short* o = sm.ordA + st;
         for (int a = 1; a < (int)c; ++a) {
           const unsigned short x = o[a];

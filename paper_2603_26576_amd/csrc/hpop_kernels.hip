@@ -1714,6 +1714,20 @@ constexpr int kWavePre = 4;
 // (small trace at 8: 3.4 -> 8.9 us for k_merge_rest).
 constexpr int kWaveFix = 16, kWaveFixSplit = 32;
 
+// Whether the c keys from `ko` on have one start. Equal starts may stay as they
+// are, however many: those of a coarse clock crowd their sub-bins, and need no
+// sort.
+__device__ __forceinline__ bool equal_starts(const unsigned int* ko, int c) {
+  const unsigned int k0 = ko[0];
+  for (int a = 1; a < c; a += 4) {
+    unsigned int d = 0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) d |= ko[min(a + u, c - 1)] ^ k0;
+    if (d >> 2) return false;
+  }
+  return true;
+}
+
 // The second count: each sub-bin is split into as many parts as it holds
 // records, and the records' places come from counting the parts' starts up.
 // W.bins holds the sub-bins' starts, kr and er the records; leaves W.key and
@@ -1771,10 +1785,13 @@ __device__ __forceinline__ bool wave_split(WaveSmem& W, int ni, int ksh, const u
   bool crowded = false;
   for (int d = lane; d < ni; d += 64) {
     const int st = d ? (int)half((unsigned int)d - 1u) : 0, c = (int)half((unsigned int)d) - st;
-    if (c > kWaveFixSplit) crowded = true;
-    if (c < 2 || c > kWaveFixSplit) continue;
+    if (c < 2) continue;
     unsigned int* ko = W.key + st;
     unsigned int* eo = W.end + st;
+    if (c > kWaveFixSplit) {
+      crowded |= !equal_starts(ko, c);
+      continue;
+    }
     for (int a = 1; a < c; ++a) {
       const unsigned int kx = ko[a], ex = eo[a];
       int b = a - 1;
@@ -1914,12 +1931,12 @@ __device__ __forceinline__ bool wave_bucket(const Plan& p, WaveSmem& W, long lon
     const int st0 = (int)((W.bins[d >> 1] >> (16u * (d & 1u))) & 0xFFFFu);
     const int st1 = (int)d + 1 < nbins ? (int)((W.bins[(d + 1) >> 1] >> (16u * ((d + 1) & 1u))) & 0xFFFFu) : ni;
     const int c = st1 - st0;
-    if (c > kWaveFix) {
-      crowded = true;
-      return;
-    }
     unsigned int* ko = W.key + st0;
     unsigned int* eo = W.end + st0;
+    if (c > kWaveFix) {
+      crowded |= !equal_starts(ko, c);
+      return;
+    }
     for (int a = 1; a < c; ++a) {
       const unsigned int kx = ko[a], ex = eo[a];
       int b = a - 1;

@@ -2,6 +2,8 @@
 (a resource of more than 4096 records, so that no workgroup takes a whole
 resource): crowded sub-bins, many equal starts, wide buckets and buckets of
 more than 512 records side by side in one workgroup's list."""
+import time
+
 import numpy as np
 import pytest
 import torch  # noqa: F401  (its HIP runtime is loaded before the library's)
@@ -105,3 +107,51 @@ def test_orders_by_passes(n, wide, cap):
     chunks += resource((len(shapes) * 3, False), tg.T0 + many, rng, 50_000)
     check(tg.Trace(6, devices + 1, chunks, regions(tg.T0 + (1 << 40 if wide else 1 << 29) + 100)),
           {"bucket_target": 2047, "bucket_cap": cap, "scatter_slots": cap, "tile_elems": 2048})
+
+
+@pytest.mark.parametrize("passes", [True, False], ids=["passes", "one kernel"])
+@pytest.mark.parametrize("wide", [False, True], ids=["narrow", "wide"])
+@pytest.mark.parametrize("c", [15, 16, 17, 32, 33, 34, 200, 505, 1200])
+def test_crowds_of_equal_starts(c, wide, passes):
+    """c records of one start, of every kind and any length, alone in their sub-bin and with one start beside
+    them before or after: equal starts need no sort, a crowd with another start does."""
+    rng = np.random.default_rng(c + wide)
+    span = (1 << 40) if wide else (1 << 29)
+    chunks = []
+    for i in range(4):
+        s = np.full(c, span // 2, np.int64)
+        near = [np.zeros(0, np.int64), np.array([span // 2 - 1]), np.array([span // 2 + 1]),
+                np.array([span // 2 - 1, span // 2 + 3])][i]
+        s = np.concatenate([s, near, rng.integers(0, span, size=7), [0, span - 1]])
+        chunks += resource((i, i < 2), tg.T0 + rng.permutation(s), rng, int(span // 4 // (1 + i)))
+    n_devices = 2
+    if passes:
+        chunks += resource((4, False), tg.T0 + np.sort(rng.integers(0, 1 << 29, size=4500)), rng, 50_000)
+        n_devices = 3
+    check(tg.Trace(2, n_devices, chunks, regions(tg.T0 + 2 * span)),
+          {"bucket_target": 2047, "scatter_slots": 2048, "tile_elems": 2048})
+
+
+def test_equal_starts_cost_no_sort():
+    """A coarse clock's records take about as long as the same ones in ns (1.1 times with starts of 1 ms, where
+    a sort of every crowd took 5.6 times as long)."""
+    rng = np.random.default_rng(11)
+    n, mean, R = 60_000, 45_000, 64
+    took = []
+    for tick in (1, 1_000_000):
+        chunks = []
+        for r in range(R):
+            s = tg.T0 + np.sort(rng.integers(0, n * mean, size=n)) // tick * tick
+            chunks.append(tg.Chunk(r, tg.DEV_KERNEL, s, s + rng.integers(0, 2 * mean, size=n)))
+        s, keep = new_session(tg.Trace(0, R, chunks, [(tg.T0, tg.T0 + n * mean)]), device=True)
+        try:
+            v = []
+            for _ in range(25):
+                t = time.perf_counter()
+                hp.hpop_metrics_compute_all(s, hp.HPOP_FORCE_REBUILD)
+                v.append(time.perf_counter() - t)
+            took.append(sorted(v)[12])
+        finally:
+            hp.hpop_session_destroy(s)
+    print("ns %.1f us, 1 ms %.1f us" % (1e6 * took[0], 1e6 * took[1]), flush=True)
+    assert took[1] < 2 * took[0]
