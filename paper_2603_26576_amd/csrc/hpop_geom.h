@@ -44,6 +44,13 @@ __host__ __device__ inline long long bucket_lo(const Geom& g, long long b) {
   return g.min_s + (long long)((unsigned long long)((unsigned int)b * g.wx) << g.s0);
 }
 
+// The same for a bucket that may hold records past the range, which start at 2^31
+// units or later: that may lie before the last of very many narrow buckets.
+__host__ __device__ inline long long bucket_from(const Geom& g, long long b) {
+  const unsigned int x = (unsigned int)b * g.wx;
+  return g.min_s + (long long)((unsigned long long)(x < (1u << 31) ? x : 1u << 31) << g.s0);
+}
+
 // floor(x / wx) for x < 2^31: the high half of x * minv is the quotient or
 // one less; the remainder decides (it stays below 2 wx <= 2^32)
 __host__ __device__ inline unsigned int geom_div(const Geom& g, unsigned int x) {
@@ -65,13 +72,19 @@ __host__ __device__ inline int bucket_of_start(const Geom& g, long long s) {
   return (int)geom_div(g, (unsigned int)((unsigned long long)(s - g.min_s) >> g.s0));
 }
 
-// whether a start lies in the range its segment's buckets cover (always, where
-// that is the range of all of its records). Past 2^31 units bucket_index gives
-// the last bucket, which with many narrow buckets is not the start's.
-__host__ __device__ inline bool start_in_range(const Geom& g, long long s) {
+// the units of 2^s0 ns after its first start that a segment's buckets cover: up
+// to 2^31, past which bucket_index gives the last bucket, which with very many
+// narrow buckets is not the start's
+__host__ __device__ inline unsigned int range_units(const Geom& g) {
   // nb * wx <= 2^31 + nb: 32 bits
   const unsigned int cover = g.empty ? 0u : (unsigned int)g.nb * g.wx;
-  return ((unsigned long long)(s - g.min_s) >> g.s0) < (cover < (1u << 31) ? cover : 1u << 31);
+  return cover < (1u << 31) ? cover : 1u << 31;
+}
+
+// whether a start lies in the range its segment's buckets cover (always, where
+// that is the range of all of its records)
+__host__ __device__ inline bool start_in_range(const Geom& g, long long s) {
+  return ((unsigned long long)(s - g.min_s) >> g.s0) < (unsigned long long)range_units(g);
 }
 
 // buckets at most 2^kNarrowShift ns wide: records and components fit the 8 B forms

@@ -65,16 +65,16 @@ constexpr int kSmallBuckets = 64;    // buckets
 
 // Sampled start ranges (k_range): kRangeSample starts of each chunk, half from
 // its front and half from its back (records arrive roughly in time order), and
-// 1 / 2^kRangePad of what they span on either side. A sample does not always
-// hold: records spread evenly over their range pass in any order (a miss has a
-// chance below 3e-7 per segment), a few apart from the rest in the middle of a
-// chunk are outside, and the build is then redone with every start read (see
-// RangeChoice). Plans with a segment of more than kRangeChunks chunks read every
+// 1 / 2^kRangePad of what they span on either side. The range need not hold
+// every start: a record outside goes to its segment's first or last bucket, in
+// the 16 B form. Plans with a segment of more than kRangeChunks chunks read every
 // start.
 constexpr int kRangeSample = 2048;
 constexpr int kRangePad = 7;
 constexpr int kRangeChunks = 64;
-constexpr unsigned long long kRangeMiss = 1ull << 62;
+// in a count of components: a narrow segment's, of 16 B all the same, as the
+// bucket holds records outside the sampled range
+constexpr unsigned int kFarComps = 1u << 31;
 
 // Chunks smaller than half a tile share tiles: consecutive ones (in the
 // chunk table) fill a tile with at most this many chunks and tile_elems records.
@@ -103,10 +103,10 @@ struct SegGeom {
 };
 
 struct SegStats {
-  unsigned long long min_s;  // over valid non-empty records; ULLONG_MAX if none
+  unsigned long long min_s;  // over valid records (sampled: a start at or before all of them); ULLONG_MAX if none
   unsigned long long max_s;
   unsigned long long max_e;
-  unsigned long long pad;
+  unsigned long long far_e;  // largest end of the records past a sampled range
 };
 
 struct RegionDesc {
@@ -165,7 +165,9 @@ struct Elem {  // one record regrouped by bucket (the 16 B form)
 // where lo is the bucket's first time (a clamped end stands for the largest
 // end of the bucket's records of that slot, maxend); a record of a wide
 // segment takes two units from the back in the 16 B form. cursor[gb] counts
-// both: 8 B records in the low 32 bits, 16 B records in the high 32.
+// both: 8 B records in the low 32 bits, 16 B records in the high 32. Records
+// outside a sampled range are 16 B records of the first or the last bucket also
+// of a narrow segment, whose components in that bucket are 16 B then.
 constexpr int kRaccWords = 10;
 
 // Buckets the wave path hands over to k_merge_rest, in two sets of lists (for a
@@ -207,7 +209,7 @@ struct Plan {
   unsigned long long* maxend;        // [n_buckets][3] per slot, 0 = none
   long long* carry;                  // [n_buckets][3] per level
   long long* bsum;                    // [n_buckets][3] measure contributed by the bucket
-  unsigned int* ncomp;               // [n_buckets][3]
+  unsigned int* ncomp;               // [n_buckets][3] components, | kFarComps (see there)
   long long* base;                    // [n_buckets][3] measure of all earlier buckets (its place: queue, qlen until then)
   long long* seg_total;              // [n_segs][3]
   Elem* elems;                       // bucket regions, 16 B per record slot (see above)
@@ -221,8 +223,7 @@ struct Plan {
   unsigned int* queue;               // [2][kQueues][queue_cap] buckets the wave path handed over (in base's memory)
   unsigned int* qlen;                // [2][kQueues], kQueuePad words apart: their counts
   int64_t queue_cap;
-  unsigned long long* oversized;     // [0] buckets above the on-chip capacity, [1] buckets above slot_cap, and
-                                     // kRangeMiss if a start lay outside its segment's sampled range
+  unsigned long long* oversized;     // [0] buckets above the on-chip capacity, [1] buckets above slot_cap
   unsigned int* owner_err;           // [n_owners] set when an owner has an invalid record
   unsigned long long* racc;          // [n_racc][kRaccWords] per region: six sums, three maxima, slices added;
                                      // zero between launches

@@ -32,7 +32,7 @@ hipError_t launch_merge_wave(const Plan& p, hipStream_t st);
 hipError_t launch_merge_rest(const Plan& p, int cap, hipStream_t st);
 hipError_t launch_base(const Plan& p, hipStream_t st);
 // Regions (n_plain of them [t0, t1), the rest per resource) and the status
-// words {first bad record, oversized buckets, slot overflows (and kRangeMiss)}. trees and
+// words {first bad record, oversized buckets, slot overflows}. trees and
 // status: device or page-locked host memory. reset: the build's own status
 // words go back to their identities once they are stored. clear_macc: the
 // intervals' accumulators are cleared first (every pass leaves them clear).

@@ -98,7 +98,7 @@ __global__ void k_reset(Plan p) {
     p.stats[i].min_s = ULLONG_MAX;
     p.stats[i].max_s = 0;
     p.stats[i].max_e = 0;
-    p.stats[i].pad = 0;
+    p.stats[i].far_e = 0;
   }
 }
 
@@ -282,7 +282,8 @@ __device__ __forceinline__ void hist_shared(const Plan& p, long long tile, ShTil
   }
 }
 
-// Scatter of shared tile `tile`. s_rng, hist, bbase and bunit are the
+// Scatter of shared tile `tile` (its chunks have fewer than half a tile of
+// records, so a sampled range holds all of them). s_rng, hist, bbase and bunit are the
 // scatter kernel's LDS arrays; the largest ends are kept per bucket and kind
 // slot: slot 0 in the kernel's bmaxe, slots 1 and 2 in bmaxe12 (2 x HW).
 template <int THREADS, int IPT>
@@ -302,7 +303,7 @@ __device__ __forceinline__ void scatter_shared(const Plan& p, long long tile, Sh
   sh_load<true>(p, tile, T);
   const int n = T.off[T.n];
   int jj[IPT], gbk[IPT];
-  bool nr[IPT], miss = false;
+  bool nr[IPT];
   unsigned int kx[IPT], ex[IPT];
   {
     long long svs[IPT], evs[IPT];
@@ -322,8 +323,6 @@ __device__ __forceinline__ void scatter_shared(const Plan& p, long long tile, Sh
           const ChunkDesc& cd = p.chunks[T.first + j];
           atomicMin(p.err, ((unsigned long long)cd.chunk_id << 40) | (unsigned long long)(x - T.off[j]));
           p.owner_err[cd.owner] = 1u;
-        } else if (sv < ev && !start_in_range(T.g[j], sv)) {
-          miss = true;
         } else if (sv < ev) {
           const Geom& g = T.g[j];
           const int b = bucket_of(sv, g);
@@ -336,7 +335,6 @@ __device__ __forceinline__ void scatter_shared(const Plan& p, long long tile, Sh
       }
     }
   }
-  if (miss) atomicOr(&p.oversized[1], kRangeMiss);
   int bmin = INT_MAX, bmax = -1;
 #pragma unroll
   for (int k = 0; k < IPT; ++k) {
@@ -654,7 +652,7 @@ __global__ __launch_bounds__(THREADS) void k_range(Plan p, bool reset) {
     st.min_s = mn;
     st.max_s = mx;
     st.max_e = 0;
-    st.pad = 0;
+    st.far_e = 0;
     p.stats[seg] = st;
     p.geom[seg] = make_geom(st, p.segs[seg]);
   }
@@ -839,6 +837,67 @@ __global__ __launch_bounds__(THREADS) void k_scan(Plan p) {
   scan_tile<THREADS>(p);
 }
 
+// The records of a tile that start outside the sampled range of its segment, few
+// as a rule (fixed slots only), go to the segment's first or last bucket, in the
+// 16 B form. One before the range lowers the segment's first start, and its end
+// counts for the buckets after it; the end of one past the range must not pass for
+// the largest end of the last bucket's 8 B records (clamped ones take that), and
+// goes to the segment. Called by the threads that met one.
+//
+// Reading every start instead takes a pass over 8 of the build's first 24 B per
+// record, and building again where a sample missed up to twice as long (256
+// resources of 200,000 records, one start apart: 717 us with every start read,
+// 1042 with a second build, 478 so; without such a record the scatter of 1.25e8
+// records takes 511 us instead of 506). The two buckets have a branch each, in
+// which their counter's address is uniform, so the compiler adds once per wave:
+// where a third of all records lie outside, which fills the slots, an add per
+// record took 4.8 ms to find that out, now 0.6.
+struct OutsideArgs {
+  const int64_t* s;    // the tile's records, n of them
+  const int64_t* e;
+  int n, slot;
+  long long first;     // of the segment's buckets the first and the last
+  long long last;
+  long long min_s, cap;
+  unsigned int cover;  // start_in_range: units of 2^s0 ns
+  int s0;
+  unsigned long long* cursor;
+  unsigned long long* maxend;
+  unsigned long long* oversized;
+  SegStats* st;
+  uint2* units;
+};
+template <int THREADS>
+__device__ __forceinline__ void put_outside(const OutsideArgs& a) {
+  auto records = [](unsigned long long cu) { return (long long)((cu & 0xFFFFFFFFull) + (cu >> 32)); };
+#pragma unroll 1
+  for (int i = (int)threadIdx.x; i < a.n; i += THREADS) {
+    const long long sv = a.s[i], ev = a.e[i];
+    if (!rec_valid(sv, ev) || sv >= ev || ((unsigned long long)(sv - a.min_s) >> a.s0) < (unsigned long long)a.cover)
+      continue;
+    auto put = [&](long long gb, unsigned long long* end) {
+      // a bucket that is full already has its build redone: no more queueing at its counter
+      if (records(__hip_atomic_load(&a.cursor[gb], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) > a.cap) return;
+      const unsigned long long old = atomicAdd(&a.cursor[gb], 1ull << 32);
+      if (records(old) == a.cap) atomicAdd(a.oversized, 1ull);  // slot overflow: the build is redone with exact offsets
+      atomicMax(end, (unsigned long long)ev);
+      const long long rank = (long long)(old >> 32);
+      if (rank < a.cap) {
+        Elem el;
+        el.s = sv;
+        el.e_slot = (long long)((unsigned long long)ev | ((unsigned long long)a.slot << kSlotShift));
+        *(Elem*)(a.units + 2 * gb * a.cap + 2 * a.cap - 2 * (rank + 1)) = el;
+      }
+    };
+    if (sv >= a.min_s) {
+      put(a.last, &a.st->far_e);
+    } else {
+      put(a.first, a.maxend + a.first * 3 + a.slot);
+      atomicMin(&a.st->min_s, (unsigned long long)sv);
+    }
+  }
+}
+
 template <int THREADS, int IPT, bool kShared>
 __global__ __launch_bounds__(THREADS) void k_scatter(Plan p) {
   constexpr int NW = THREADS / 64;
@@ -870,7 +929,7 @@ __global__ __launch_bounds__(THREADS) void k_scatter(Plan p) {
   // per record: bucket (-1: none) and the 8 B form itself; a record in the 16 B
   // form (those of wide segments) is read again where it is needed
   int bk[IPT];
-  bool miss = false;
+  bool out = false;  // a record of this thread starts outside the sampled range
   unsigned int kx[IPT], ex[IPT];
   int bmin = INT_MAX, bmax = -1;
   // the loads of all rounds first, from positions clamped into the tile
@@ -896,7 +955,7 @@ __global__ __launch_bounds__(THREADS) void k_scatter(Plan p) {
         atomicMin(p.err, ((unsigned long long)cd.chunk_id << 40) | (unsigned long long)(base + i));
         p.owner_err[cd.owner] = 1u;
       } else if (sv < ev && !start_in_range(g, sv)) {
-        miss = true;
+        out = true;
       } else if (sv < ev) {
         const unsigned long long rel = (unsigned long long)(sv - g.min_s);
         bk[k] = (int)geom_div(g, (unsigned int)(rel >> g.s0));
@@ -912,7 +971,10 @@ __global__ __launch_bounds__(THREADS) void k_scatter(Plan p) {
       }
     }
   }
-  if (miss) atomicOr(&p.oversized[1], kRangeMiss);
+  if (out)
+    put_outside<THREADS>(OutsideArgs{ts, te, n_tile, cd.slot, sd.bucket_begin, sd.bucket_begin + sd.nb - 1, g.min_s,
+                                     p.slot_cap, range_units(g), g.s0, p.cursor, p.maxend, p.oversized + 1,
+                                     p.stats + cd.seg, (uint2*)p.elems});
   bmin = wave_reduce_i32<OpMinI>(bmin, INT_MAX);
   bmax = wave_reduce_i32<OpMaxI>(bmax, -1);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -1155,6 +1217,7 @@ __device__ __forceinline__ void carry_segment(const Plan& p, long long seg, int 
     }
   }
   // largest end of the segment (level 2 holds every kind); no record: the min start
+  run[2] = max(run[2], (long long)st.far_e);
   if (lane == 0) p.stats[seg].max_e = (unsigned long long)(run[2] > init ? run[2] : (init + 1 > 0 ? init + 1 : 0));
 }
 
@@ -1203,6 +1266,7 @@ __device__ __forceinline__ void carry_segment_big(const Plan& p, long long seg) 
       }
     }
   }
+  run[2] = max(run[2], (long long)st.far_e);
   if (threadIdx.x == 0)
     p.stats[seg].max_e = (unsigned long long)(run[2] > init ? run[2] : (init + 1 > 0 ? init + 1 : 0));
 }
@@ -1334,7 +1398,7 @@ __device__ __forceinline__ void carry_group(const Plan& p, long long w, int lane
       if (k < sd.nb) p.carry[(sd.bucket_begin + k) * 3 + l] = ex > init ? ex : init;
       if (l == 2) last2 = __shfl(inc, kSegGroup - 1, kSegGroup);
     }
-    const long long r2 = last2 > init ? last2 : init;
+    const long long r2 = max(max(last2, (long long)st.far_e), init);
     if (k == 0) p.stats[seg].max_e = (unsigned long long)(r2 > init ? r2 : (init + 1 > 0 ? init + 1 : 0));
   }
   unsigned long long big = __ballot(k == 0 && have && !small);
@@ -1444,16 +1508,18 @@ __device__ __forceinline__ void merge_bucket(const Plan& p, long long gb, SortSm
   const int nlev = sd.n_levels;
   Comp* comp[3] = {p.comp[0] + off, p.comp[1] + off, p.comp[2] + off};
   CompN* compn_b[3] = {p.compn[0] + off, p.compn[1] + off, p.compn[2] + off};
-  CompN* const* compn = seg_narrow(g) ? compn_b : nullptr;
+  // 16 B records of a narrow segment lie outside its sampled range: 16 B components
+  CompN* const* compn = seg_narrow(g) && br.n16 == 0 ? compn_b : nullptr;
   if (n > 0) {
-    const long long lo = bucket_lo(g, bl);
+    const long long lo = bucket_from(g, bl);
+    const long long first = bl == 0 ? min(lo, (long long)p.stats[seg].min_s) : lo;  // at or before every start
     if (n <= CAP) {
       const int ni = (int)n;
       group_copy<THREADS>(br.n8, [&](int i) { return br.narrow[i]; },
                           [&](int i, uint2 x) { sm.E[i] = widen(x, lo, mx); });
       group_copy<THREADS>(br.n16, [&](int i) { return br.wide[i]; }, [&](int i, Elem x) { sm.E[br.n8 + i] = x; });
       group_sync<THREADS>();
-      const unsigned short* ord = sort_lds<THREADS, CAP>(sm, ni, lo);
+      const unsigned short* ord = sort_lds<THREADS, CAP>(sm, ni, first);
       if (nlev == 2) flatten_tile<THREADS, MAXI, 2>(sm.E, ord, ni, comp, compn, lo, st, sm.lds_scan);
       else flatten_tile<THREADS, MAXI, 3>(sm.E, ord, ni, comp, compn, lo, st, sm.lds_scan);
     } else if constexpr (THREADS >= 256) {
@@ -1481,7 +1547,7 @@ __device__ __forceinline__ void merge_bucket(const Plan& p, long long gb, SortSm
 #pragma unroll
     for (int l = 0; l < 3; ++l) {
       p.bsum[gb * 3 + l] = st.P[l];
-      p.ncomp[gb * 3 + l] = (unsigned int)st.R[l];
+      p.ncomp[gb * 3 + l] = (unsigned int)st.R[l] | (seg_narrow(g) && br.n16 ? kFarComps : 0u);
     }
   }
   group_sync<THREADS>();
@@ -2261,7 +2327,7 @@ __global__ __launch_bounds__(kSmallThreads, 4) void k_build_small(Plan p) {
     st.min_s = mx < 0 ? ULLONG_MAX : (unsigned long long)mn;
     st.max_s = mx < 0 ? 0ull : (unsigned long long)mx;
     st.max_e = 0;
-    st.pad = 0;
+    st.far_e = 0;
     S.st = st;
     S.g = make_geom(st, sd);
   }
@@ -2453,21 +2519,22 @@ __global__ __launch_bounds__(kSmallThreads, 4) void k_build_small(Plan p) {
 __device__ __forceinline__ long long measure_before(const Plan& p, int seg, int l, long long t) {
   const SegDesc sd = p.segs[seg];
   const Geom g = seg_geom(p, seg);
-  const long long max_e = (long long)p.stats[seg].max_e;
-  if (g.empty || t <= g.min_s) return 0;
-  if (t >= max_e) return p.seg_total[seg * 3 + l];
-  const long long bl = bucket_index(g, (unsigned long long)(t - g.min_s));
+  const SegStats st = p.stats[seg];
+  if (g.empty || t <= (long long)st.min_s) return 0;
+  if (t >= (long long)st.max_e) return p.seg_total[seg * 3 + l];
+  const long long bl = t <= g.min_s ? 0 : bucket_index(g, (unsigned long long)(t - g.min_s));
   const long long gb = sd.bucket_begin + bl;
   const long long carry = p.carry[gb * 3 + l];
   const long long base = p.base[gb * 3 + l];
   const long long bs = p.bsum[gb * 3 + l];
-  const int cnt = (int)p.ncomp[gb * 3 + l];
+  const unsigned int nc = p.ncomp[gb * 3 + l];
+  const int cnt = (int)(nc & ~kFarComps);
   const long long off = (long long)p.offsets[gb];
-  const long long lo = bucket_lo(g, bl);
+  const long long lo = bucket_from(g, bl);
   const long long width = (long long)((unsigned long long)g.wx << g.s0);
   long long cs, pl, next;
   bool any;
-  if (seg_narrow(g)) {
+  if (seg_narrow(g) && !(nc & kFarComps)) {
     const CompN* c = p.compn[l] + off;
     // past the last bucket's width no component starts: any x there will do
     const unsigned int x = (unsigned int)min(t - lo, 0x7FFFFFFFll);
@@ -2482,14 +2549,15 @@ __device__ __forceinline__ long long measure_before(const Plan& p, int seg, int 
     cs = lo + (long long)c32;
   } else {
     const Comp* c = p.comp[l] + off;
+    const long long from = bl == 0 ? (long long)st.min_s : lo;  // at or before every start
     any = find_comp(
         [&](int k, long long& s, long long& m) {
           const Comp v = c[k];
-          s = v.cs - lo;
+          s = v.cs - from;
           m = v.pl;
         },
-        cnt, t - lo, width, bs, cs, pl, next);
-    cs += lo;
+        cnt, t - from, lo + width - from, bs, cs, pl, next);
+    cs += from;
   }
   if (!any) {
     // only the component carried in from earlier buckets lies before t

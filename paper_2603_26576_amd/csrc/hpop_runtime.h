@@ -8,7 +8,6 @@
 
 #include "hpop.h"
 #include "hpop_internal.h"
-#include "hpop_range.h"
 
 namespace hpop {
 
@@ -109,9 +108,6 @@ struct Engine {
   std::vector<SmallSeg> h_sseg;       // not empty: every segment is small (see k_build_small)
   std::vector<int32_t> h_seg_first;   // not empty: start ranges from a sample (see k_range), with
   std::vector<int32_t> h_seg_chunk;   // the chunks by segment
-  bool sample_ranges = true;          // they may come from one
-  RangeChoice range;                  // whether the present records' do
-  std::vector<unsigned long long> range_versions;  // of the sessions whose starts are read in full
   bool staged = false;                // the plan was made for a timed build, which keeps the passes apart
   bool small_fits = false;            // k_build_small could take the plan's segments (not in a timed build)
   bool keep_status = false;           // only builds are enqueued: the caller's kernels read what they leave

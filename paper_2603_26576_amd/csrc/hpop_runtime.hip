@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "hpop.h"
+#include "hpop_geom.h"
 #include "hpop_internal.h"
 #include "hpop_kernels.h"
 #include "hpop_runtime.h"
@@ -490,6 +491,7 @@ hpop_status Engine::assemble_plan(const hpop_tuning& tun, const std::vector<long
     share = small > own;
   }
   const long long small_below = share ? tile / 2 : 0;
+  static_assert(2048 / 2 <= kRangeSample, "the chunks of shared tiles are sampled whole");
   std::stable_partition(h_chunks.begin(), h_chunks.end(),
                         [&](const ChunkDesc& d) { return d.count >= small_below; });
   long long tiles = 0;
@@ -530,13 +532,12 @@ hpop_status Engine::assemble_plan(const hpop_tuning& tun, const std::vector<long
 }
 
 // Whether the segments' start ranges come from a sample, and the chunks by
-// segment for it. Fixed slots only: an exact build is the one whose records
-// already had their way with a guess. A caller that takes over the build's
-// results (keep_status) reads the ranges themselves, and one whose calls share
-// nothing (the entry point without allocation) would pay for a miss on each.
+// segment for it. Fixed slots only: an exact build's buckets are counted first. A
+// caller that takes over the build's results (keep_status) reads the ranges
+// themselves.
 void Engine::plan_range(int n_segs, int slots) {
   h_seg_first.clear();
-  if (n_segs == 0 || slots == 0 || !sample_ranges || range.exact || keep_status) return;
+  if (n_segs == 0 || slots == 0 || keep_status) return;
   std::vector<int32_t> first((size_t)n_segs + 1, 0);
   for (const ChunkDesc& d : h_chunks)
     if (++first[(size_t)d.seg + 1] > kRangeChunks) return;
@@ -784,15 +785,6 @@ hpop_status Engine::run(hpop_session* const* ss, int k, uint32_t flags, hpop_met
       forced_versions.clear();
     }
   }
-  auto versions = [&] {
-    std::vector<unsigned long long> v;
-    for (int i = 0; i < k; ++i) v.push_back(ss[i]->version);
-    return v;
-  };
-  if (!same && range.exact && versions() != range_versions) {
-    range.new_records();
-    range_versions = versions();
-  }
   const size_t nreg_total = [&] {
     size_t t = 0;
     for (int i = 0; i < k; ++i) t += ss[i]->regions.size();
@@ -875,14 +867,6 @@ hpop_status Engine::run(hpop_session* const* ss, int k, uint32_t flags, hpop_met
   memcpy(&over, h + bt + 8, 8);
   memcpy(&slot_over, h + bt + 16, 8);
   if (build) last_oversized = (long long)over;
-  if (build && bad == ULLONG_MAX && (slot_over & kRangeMiss)) {
-    // a start outside its segment's sampled range: redo this plan with every start read
-    range.missed();
-    range_versions = versions();
-    key_sessions.clear();
-    return run(ss, k, flags, out, timing, err);  // the keys are gone: a new plan, and a build
-  }
-  if (build && ws.plan.seg_first && !(slot_over & kRangeMiss)) range.held();
   if (build && bad == ULLONG_MAX && ws.plan.slot_cap > 0 && slot_over > 0) {
     // a bucket outgrew its fixed slots: redo this plan with exact offsets
     exact_forced = true;
@@ -1383,12 +1367,14 @@ hpop_status hpop_session_get_info(const hpop_session* s, hpop_session_info* out)
         hipMemcpy(nc.data(), En.ws.plan.ncomp, nc.size() * 4, hipMemcpyDeviceToHost) == hipSuccess &&
         (ns == 0 || hipMemcpy(geo.data(), En.ws.plan.geom, ns * sizeof(SegGeom), hipMemcpyDeviceToHost) == hipSuccess)) {
       long long t = 0, w = 0;
-      for (unsigned int v : nc) t += v;
+      for (unsigned int v : nc) t += v & ~kFarComps;
       for (size_t g = 0; g < ns; ++g) {
-        // buckets wider than 2^kNarrowShift ns keep their components in the 16 B form
-        if (geo[g].empty || ((unsigned long long)geo[g].wx << geo[g].s0) <= (1ull << kNarrowShift)) continue;
-        const long long b0 = En.h_segs[g].bucket_begin, b1 = b0 + En.h_segs[g].nb;
-        for (long long b = b0; b < b1; ++b) w += (long long)nc[3 * b] + nc[3 * b + 1] + nc[3 * b + 2];
+        // buckets wider than 2^kNarrowShift ns, or with records outside the sampled
+        // range, keep their components in the 16 B form
+        const bool wide = !geo[g].empty && !seg_narrow(geo[g]);
+        const long long b0 = 3 * En.h_segs[g].bucket_begin, b1 = b0 + 3 * En.h_segs[g].nb;
+        for (long long i = b0; i < b1; ++i)
+          if (wide || (nc[i] & kFarComps)) w += (long long)(nc[i] & ~kFarComps);
       }
       out->n_components = t;
       out->n_wide_components = w;

@@ -62,7 +62,6 @@ hpop_status device_state(int dev, StaticDevice** out) {
     d->engine.alloc.fn_alloc = refuse_alloc;
     d->engine.alloc.fn_free = ignore_free;
     d->engine.use_graphs = false;
-    d->engine.sample_ranges = false;
     d->engine.ws.fixed = p;
     d->engine.ws.fixed_bytes = kScratchBytes;
     d->engine.ws.fixed_margin = kScratchMargin;

@@ -1,0 +1,177 @@
+"""Records that start outside their segment's sampled range (the sample takes the
+ends of a chunk, these lie in its middle): before it and past it, near and
+far, few and many, short and over everything, in narrow and wide buckets, with
+one bucket per resource and with many, against the oracle at regions that cut
+through them."""
+import time
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2603_26576_amd as hp
+import tracegen as tg
+from engine_util import assert_same, engine_results, new_session
+
+pytestmark = pytest.mark.gpu
+
+LEAD = 1 << 40  # the records lie this far after T0, so that starts before them are valid ones
+
+
+def trace(rng, n, span, where, count, long_ends, hosts=1, devices=2):
+    """`count` records in the middle of every chunk of resource 0 and the last one start outside [LEAD, LEAD + span)."""
+    chunks, cuts = [], []
+    R = hosts + devices
+    for r in range(R):
+        for k in ((0, 1, 2) if r < hosts else (3, 4)):
+            s = np.sort(rng.integers(0, span, size=n))
+            e = s + rng.integers(0, 3 * span // n, size=n)
+            # a few ends further than an 8 B record holds, in the last bucket too
+            far = rng.integers(0, n, size=3)
+            e[far] += 1 << 33
+            e[-1] += (1 << 32) + 7
+            if r in (0, R - 1):
+                at = n // 2 - count // 2 + np.arange(count)
+                off = {"near": span // 16, "far": 1 << 36}[where.split()[1]]
+                jit = rng.integers(0, max(1, off // 4), size=count)
+                sides = {"before": [-1], "past": [1], "both": [-1, 1]}[where.split()[0]]
+                side = np.array(sides)[np.arange(count) % len(sides)]
+                s[at] = np.where(side < 0, -off - jit, span + off + jit)
+                e[at] = s[at] + (rng.integers(1, 1 << 37, size=count) if long_ends else rng.integers(0, 1000, size=count))
+                cuts += [int(s[at[0]]), int(e[at[0]]) - 1, int(s[at[-1]]) + 1, int(e[at[-1]]) + 1]
+            chunks.append(tg.Chunk(r, k, tg.T0 + LEAD + s, tg.T0 + LEAD + e))
+    lo, hi = min(int(c.start.min()) for c in chunks) - 5, max(int(c.end.max()) for c in chunks) + 5
+    pts = sorted({lo, hi, tg.T0 + LEAD, tg.T0 + LEAD + span // 3, tg.T0 + LEAD + span, tg.T0 + LEAD + span + (1 << 33)}
+                 | {tg.T0 + LEAD + c for c in cuts[:8]})
+    pts = [p for p in pts if lo <= p <= hi]
+    return tg.Trace(hosts, devices, chunks, [(lo, hi)] + list(zip(pts, pts[1:])) + [(pts[1], pts[-2])])
+
+
+def check(tr, tuning=None, flags=(0, hp.HPOP_FORCE_REBUILD, hp.HPOP_FORCE_REBUILD, 0)):
+    want = oracle.compute(tr)
+    s, keep = new_session(tr, device=True, tuning=tuning)
+    try:
+        for f in flags:
+            assert_same(engine_results(s, tr, f), want, "flags %d" % f)
+        return hp.hpop_session_get_info(s)
+    finally:
+        hp.hpop_session_destroy(s)
+
+
+@pytest.mark.parametrize("long_ends", [False, True], ids=["short", "long"])
+@pytest.mark.parametrize("count", [1, 2, 90])
+@pytest.mark.parametrize("where", ["before near", "before far", "past near", "past far", "both near", "both far"])
+@pytest.mark.parametrize("wide", [False, True], ids=["narrow", "wide"])
+def test_outside(wide, where, count, long_ends):
+    rng = np.random.default_rng(count + len(where) + long_ends)
+    tr = trace(rng, 5001, 1 << (42 if wide else 29), where, count, long_ends)
+    print("case: %s %d" % (where, count), flush=True)
+    info = check(tr)
+    # the outside records alone take the 16 B form in narrow segments
+    assert info.n_wide_records >= (2 if not wide else tr.n_events // 2)
+
+
+@pytest.mark.parametrize("where", ["before far", "past far", "both near"])
+@pytest.mark.parametrize("tuning", [{"bucket_target": 4096, "bucket_cap": 4096, "scatter_slots": 4096},  # one bucket
+                                    {"bucket_target": 64}, {"tile_elems": 512}, {"tile_elems": 8192},
+                                    {"bucket_target": 16, "scatter_slots": 64}],
+                         ids=["one bucket", "64", "tile 512", "tile 8192", "overflow"])
+def test_outside_tunings(tuning, where):
+    rng = np.random.default_rng(len(where))
+    n = 2900 if "bucket_cap" in tuning else 5001
+    tr = trace(rng, n, 1 << 29, where, 7, True, hosts=0, devices=2)
+    if "bucket_cap" in tuning:
+        tr = tg.Trace(0, 2, [c for c in tr.chunks if c.kind == tg.DEV_KERNEL], tr.regions)
+    check(tr, tuning)
+
+
+def test_many_outside_overflow():
+    """More outside records than a bucket's slots: the build is redone, and so is the next one's."""
+    rng = np.random.default_rng(1)
+    for _ in range(2):
+        check(trace(rng, 9000, 1 << 29, "both far", 6000, False))
+
+
+def test_sessions_batch_static_and_stream_of_sets():
+    """The same records through the entry points that sample, one set after another in the same sessions."""
+    rng = np.random.default_rng(2)
+    keep = [hp.hpop_session_create(1, 2) for _ in range(3)]
+    try:
+        regs = None
+        for where in ["before far", "past near", "both far"]:
+            trs = [trace(rng, 4001 + 500 * i, 1 << 29, where, 3, i == 1) for i in range(3)]
+            if regs is None:
+                regs = trs[0].regions
+                for s in keep:
+                    for a, b in regs:
+                        hp.hpop_region_define(s, a, b)
+            trs = [tg.Trace(1, 2, t.chunks, regs) for t in trs]
+            for s, t in zip(keep, trs):
+                hp.hpop_clear_events(s)
+                hp.add_chunks(s, [(c.resource, c.kind, c.start, c.end) for c in t.chunks], device=True)
+            wants = [oracle.compute(t) for t in trs]
+            got = hp.hpop_batch_compute(keep, 0)
+            for k in range(3):
+                np.testing.assert_array_equal(
+                    np.array([hp.tree_sums(x) for x in got[len(regs) * k:len(regs) * (k + 1)]]), wants[k]["sums"])
+                assert_same(engine_results(keep[k], trs[k]), wants[k], where)
+                dev = [(c.resource, c.kind, torch.from_numpy(c.start).cuda(), torch.from_numpy(c.end).cuda())
+                       for c in trs[k].chunks]
+                torch.cuda.synchronize()
+                trees, times = hp.hpop_metrics_compute_static(1, 2, dev, regs, times=True)
+                np.testing.assert_array_equal(np.array([hp.tree_sums(t) for t in trees]), wants[k]["sums"])
+                np.testing.assert_array_equal(times, wants[k]["times"])
+    finally:
+        for s in keep:
+            hp.hpop_session_destroy(s)
+
+
+def test_session_built_once_with_outside_records():
+    """A session's new records are built once, whatever of them lies outside (no overflow): the slots' build
+    is the one that answers, so that no count pass runs."""
+    rng = np.random.default_rng(3)
+    tr = trace(rng, 5001, 1 << 29, "both far", 4, True)
+    s, keep = new_session(tr, device=True)
+    try:
+        hp.hpop_session_enable_timing(s, True)
+        assert_same(engine_results(s, tr), oracle.compute(tr))
+        names = [n for n, _ in hp.hpop_session_stage_times(s)]
+        assert "hist" not in names and names[-1] == "region"
+    finally:
+        hp.hpop_session_destroy(s)
+
+
+def test_new_records_are_built_once():
+    """New records with a start outside the sample take about as long as without (1.0-1.1 times; building them
+    a second time takes 2.1 times as long)."""
+    rng = np.random.default_rng(5)
+    n, R, mean = 60_000, 64, 45_000
+    sets = []
+    for apart in (False, True):
+        dev = []
+        for r in range(R):
+            s = tg.T0 + n * mean // 20 + np.sort(rng.integers(0, n * mean, size=n))
+            if apart and r == 0:
+                s[n // 2] = tg.T0
+            e = s + rng.integers(0, 2 * mean, size=n)
+            dev.append((r, tg.DEV_KERNEL, torch.from_numpy(s).cuda(), torch.from_numpy(e).cuda()))
+        sets.append(dev)
+    torch.cuda.synchronize()
+    s = hp.hpop_session_create(0, R)
+    took = ([], [])
+    try:
+        hp.hpop_region_define(s, tg.T0, tg.T0 + 2 * n * mean)
+        for _ in range(21):
+            for k, dev in enumerate(sets):
+                hp.hpop_clear_events(s)
+                hp.hpop_add_events_multi(s, dev, hp.HPOP_MEM_DEVICE)
+                hp.hpop_session_synchronize(s)
+                t = time.perf_counter()
+                hp.hpop_metrics_compute_all(s)
+                took[k].append(time.perf_counter() - t)
+    finally:
+        hp.hpop_session_destroy(s)
+    plain, odd = (sorted(v)[10] for v in took)
+    print("plain %.1f us, with a start apart %.1f us" % (1e6 * plain, 1e6 * odd), flush=True)
+    assert odd < 1.6 * plain

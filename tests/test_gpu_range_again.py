@@ -1,6 +1,5 @@
 """Sets of records with and without a start outside its sampled range, in one
-session and in a batch that goes on: every answer is the oracle's, whichever
-of them are sampled and whichever are read in full."""
+session and in a batch that goes on: every answer is the oracle's."""
 import time
 
 import numpy as np

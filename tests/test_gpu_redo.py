@@ -1,5 +1,6 @@
-"""Builds redone for a start outside its sampled range or for full slots: new
-records answered once record no graph, and a forced rebuild still replays one."""
+"""Builds redone for full slots, and builds with a start outside the sampled range
+(which are not redone): new records answered once record no graph, and a forced
+rebuild still replays one."""
 import numpy as np
 import pytest
 import torch  # noqa: F401  (its HIP runtime is loaded before the library's)
