@@ -17,6 +17,7 @@ extern thread_local double g_alloc_us;
 const char* status_name(hpop_status s);
 int slot_of_kind(int kind);
 long long tuning_key(const hpop_tuning& t);
+unsigned long long next_version();  // 1, 2, ... in the process
 
 // Renderings (hpop_format.hip): a region's report with per-resource times
 // (4 int64 per resource, hosts then devices), and the buffer rule of the
@@ -174,7 +175,7 @@ struct hpop_session {
   int64_t n_calls = 0;
   std::vector<std::pair<int64_t, int64_t>> regions;  // [t0, t1), or the span of a per-resource region
   std::vector<std::vector<hpop::IvlDesc>> region_ivls;  // per region: its intervals (empty: [t0, t1))
-  unsigned long long version = 0;
+  unsigned long long version = hpop::next_version();  // of the records; no two sessions ever have the same
   bool copies_pending = false;  // record copies enqueued on `stream` since a batch last waited for it
   hpop::PinnedBuf staging;
   hpop_tuning tuning{};

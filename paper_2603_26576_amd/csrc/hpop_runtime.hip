@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <climits>
 #include <cstdio>
@@ -891,7 +892,7 @@ hpop_status Engine::run(hpop_session* const* ss, int k, uint32_t flags, hpop_met
       s->last_error = buf;
       s->n_events -= rc.count;
       s->chunks.erase(s->chunks.begin() + ci);
-      ++s->version;
+      s->version = next_version();
     } else {
       err = "invalid record";
     }
@@ -918,6 +919,13 @@ void Engine::release() {
   events.clear();
   ws.release(alloc);
   built = false;
+}
+
+// A batch's plan is kept by its sessions and their versions: with one count for
+// all of them, a session in a destroyed one's place is never taken for it.
+unsigned long long next_version() {
+  static std::atomic<unsigned long long> last{0};
+  return ++last;
 }
 
 long long tuning_key(const hpop_tuning& t) {
@@ -1160,7 +1168,7 @@ hpop_status hpop_add_events_multi(hpop_session* s, const hpop_event_chunk* chunk
     s->n_events += rc.count;
   }
   s->n_calls += n_chunks;
-  ++s->version;
+  s->version = next_version();
   return HPOP_OK;
   HPOP_GUARD_END(s)
 }
@@ -1181,7 +1189,7 @@ hpop_status hpop_clear_events(hpop_session* s) {
   s->arena_used = 0;
   s->arena.used = 0;
   s->n_events = 0;
-  ++s->version;
+  s->version = next_version();
   return HPOP_OK;
   HPOP_GUARD_END(s)
 }

@@ -166,7 +166,7 @@ hpop_status hpop_add_stream_events(hpop_session* s, int32_t resource, int32_t st
     in->arena.used = arena_used;
     in->n_events = n_events;
     in->n_calls = n_calls;
-    ++in->version;
+    in->version = hpop::next_version();
     return st;  // the outer session holds the message
   }
   return HPOP_OK;
