@@ -14,9 +14,10 @@
 // priority Useful > Offloading > MPI).
 //
 // Pipeline (one pass over the records per arrow):
-//   records --stats--> per-segment min / max start
-//           --scatter-> validated records regrouped by bucket (16 B each, bucket
-//                       = (start - min) >> shift) + per-bucket max end; by default
+//   records --range--> per-segment start range from a sample (or, --stats-->,
+//                       from every start) and bucket geometry
+//           --scatter-> validated records regrouped by time bucket (8 B each, or
+//                       16 B, see Elem) + per-bucket max end; by default
 //                       into fixed slots per bucket, else after an exact
 //                       --hist--> count and --scan--> offset pass
 //           --scan---> bucket offsets of the merged intervals

@@ -581,10 +581,9 @@ __global__ __launch_bounds__(256) void k_stats_small(Plan p) {
 }
 
 // Start range and bucket geometry of each segment (a workgroup per segment)
-// from a sample of its starts, with the reset pass on the side if asked: the
-// scatter checks every start against the range, and a build with one outside
-// is redone with the pass over all starts. That pass reads 8 of the 24 B per
-// record that the build's first half moves. With its reset and geometry
+// from a sample of its starts, with the reset pass on the side if asked. The
+// scatter checks every start against the range (put_outside). A pass over all
+// starts reads 8 of the 24 B per record that the build's first half moves. With its reset and geometry
 // kernels it took 178 us of the large trace's 1370, 28 of the mid trace's 232,
 // 75 of the streams' 660 and 66 of 440 on a batch of 128 traces; this takes 13,
 // 9, 17 and 37. What bounds it is four dependent reads, so a wave takes a
@@ -1037,8 +1036,9 @@ __global__ __launch_bounds__(THREADS) void k_scatter(Plan p) {
       // wave (lane 2k + i: bucket i of round k) instead of a dependent one per
       // bucket and round: the kernel is bound by these chains and by its waves
       // in flight as much as by its 24 B per record (large trace: 601 -> 567 us,
-      // 504 with 2048-record tiles, 6.0 TB/s; mid 73 -> 60; 256 devices with
-      // their streams 274 -> 213; the small trace 7.5 -> 5.9).
+      // 504 with 2048-record tiles, 5.9 TB/s; mid 73 -> 60; 256 devices with
+      // their streams 274 -> 213; the small trace 7.5 -> 5.9; put_outside has
+      // added 1-3 % since).
       int vb = 0;                     // bucket, window-relative
       unsigned int vn = 0, ve = 0;    // its records, and their largest end relative to the bucket
       unsigned int second = 0, done = 0;  // bit k: this lane's record of round k is in bucket 1 / has its rank already
@@ -2176,8 +2176,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
 // workgroup down, so those without a large bucket take the small ones first.
 // A build of 2.9e3 wide buckets (16 + 16 resources, 1e6 records over hours):
 // 131 us with a workgroup per bucket and a radix sort, 57 with the counting
-// sort, 27 so. A few buckets take 17 us, which is one bucket's chain of
-// dependent reads, barriers and scans.
+// sort, 38 so (27 with 352 records per bucket, 320 now). A few buckets take 17 us,
+// which is one bucket's chain of dependent reads, barriers and scans.
 template <int THREADS, int CAP>
 __global__ __launch_bounds__(THREADS, CAP == 2048 ? 3 : 1) void k_merge_rest(Plan p) {
   constexpr int NW = THREADS / 64;

@@ -820,8 +820,8 @@ hpop_status Engine::run(hpop_session* const* ss, int k, uint32_t flags, hpop_met
   // launches one by one, whose host time hides behind the first kernels: mid
   // trace 174 against 166 us, 1.25e8 records 1111 against 1102, a batch of 128
   // traces 379 against 363, 8e4 records 51 against 48. Builds of up to 256 Ki
-  // records keep the replay (and its count), as there the host would be busy
-  // launching for most of the build.
+  // records keep the replay all the same: hpop.h promises it for them and
+  // graph_replays counts it, and there it costs 3 us at most.
   constexpr long long kGraphRecords = 256ll << 10;
   if (build && use_graphs && !timing && !(flags & HPOP_NO_GRAPH) && ws.plan.n_elems <= kGraphRecords &&
       (plan_passes > 0 || (flags & HPOP_FORCE_REBUILD))) {
