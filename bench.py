@@ -823,7 +823,8 @@ def import_traffic(kernel, workload, fetch_csv, write_csv, cal_fetch_csv, cal_wr
     print(path, rec)
     # every build kernel of the same runs: the whole path's bytes per step
     fr, wr = _pmc_rows(fetch_csv, "FETCH_SIZE"), _pmc_rows(write_csv, "WRITE_SIZE")
-    names = sorted({k.split("(")[0] for k, _ in fr if "hpop::k_" in k})
+    # (k_gather loads the records before the builds)
+    names = sorted({k.split("(")[0] for k, _ in fr if "hpop::k_" in k and "k_gather" not in k})
     per = {}
     for n in names:
         fm, wm = mean_for(fr, n + "("), mean_for(wr, n + "(")
