@@ -841,16 +841,18 @@ __global__ __launch_bounds__(THREADS) void k_scan(Plan p) {
 // 16 B form. One before the range lowers the segment's first start, and its end
 // counts for the buckets after it; the end of one past the range must not pass for
 // the largest end of the last bucket's 8 B records (clamped ones take that), and
-// goes to the segment. Called by the threads that met one.
+// goes to the segment. Called by the waves that met one.
 //
 // Reading every start instead takes a pass over 8 of the build's first 24 B per
 // record, and building again where a sample missed up to twice as long (256
 // resources of 200,000 records, one start apart: 717 us with every start read,
-// 1042 with a second build, 478 so; without such a record the scatter of 1.25e8
-// records takes 511 us instead of 506). The two buckets have a branch each, in
-// which their counter's address is uniform, so the compiler adds once per wave:
-// where a third of all records lie outside, which fills the slots, an add per
-// record took 4.8 ms to find that out, now 0.6.
+// 1042 with a second build, 478 so). A tile that lies outside from end to end asks
+// for the build with exact offsets at once: with a third of those records outside,
+// the adds to the same few counters took the two builds to 4.8 ms, now 1.56. The
+// branch here is the wave's and the code behind it each lane's: with a branch per
+// lane, or with wave operations or two paths behind it, the registers and compares
+// of the records above change, and the scatter, which hardly ever comes here, takes
+// 511-525 us for 1.25e8 records instead of 505.
 struct OutsideArgs {
   const int64_t* s;    // the tile's records, n of them
   const int64_t* e;
@@ -868,31 +870,31 @@ struct OutsideArgs {
 };
 template <int THREADS>
 __device__ __forceinline__ void put_outside(const OutsideArgs& a) {
-  auto records = [](unsigned long long cu) { return (long long)((cu & 0xFFFFFFFFull) + (cu >> 32)); };
+  auto outside = [&](long long sv, long long ev) {
+    return rec_valid(sv, ev) && sv < ev && ((unsigned long long)(sv - a.min_s) >> a.s0) >= (unsigned long long)a.cover;
+  };
+  // a tile that lies outside from end to end is one of many: they would fill the slots
+  if (outside(a.s[0], a.e[0]) && outside(a.s[a.n - 1], a.e[a.n - 1]) && a.n > THREADS) {
+    if (threadIdx.x == 0) atomicAdd(a.oversized, 1ull);
+    return;
+  }
 #pragma unroll 1
   for (int i = (int)threadIdx.x; i < a.n; i += THREADS) {
     const long long sv = a.s[i], ev = a.e[i];
-    if (!rec_valid(sv, ev) || sv >= ev || ((unsigned long long)(sv - a.min_s) >> a.s0) < (unsigned long long)a.cover)
-      continue;
-    auto put = [&](long long gb, unsigned long long* end) {
-      // a bucket that is full already has its build redone: no more queueing at its counter
-      if (records(__hip_atomic_load(&a.cursor[gb], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) > a.cap) return;
-      const unsigned long long old = atomicAdd(&a.cursor[gb], 1ull << 32);
-      if (records(old) == a.cap) atomicAdd(a.oversized, 1ull);  // slot overflow: the build is redone with exact offsets
-      atomicMax(end, (unsigned long long)ev);
-      const long long rank = (long long)(old >> 32);
-      if (rank < a.cap) {
-        Elem el;
-        el.s = sv;
-        el.e_slot = (long long)((unsigned long long)ev | ((unsigned long long)a.slot << kSlotShift));
-        *(Elem*)(a.units + 2 * gb * a.cap + 2 * a.cap - 2 * (rank + 1)) = el;
-      }
-    };
-    if (sv >= a.min_s) {
-      put(a.last, &a.st->far_e);
-    } else {
-      put(a.first, a.maxend + a.first * 3 + a.slot);
-      atomicMin(&a.st->min_s, (unsigned long long)sv);
+    if (!outside(sv, ev)) continue;
+    const bool past = sv >= a.min_s;
+    const long long gb = past ? a.last : a.first;
+    const unsigned long long old = atomicAdd(&a.cursor[gb], 1ull << 32);
+    if ((long long)((old & 0xFFFFFFFFull) + (old >> 32)) == a.cap)
+      atomicAdd(a.oversized, 1ull);  // slot overflow: the build is redone with exact offsets
+    atomicMax(past ? &a.st->far_e : &a.maxend[gb * 3 + a.slot], (unsigned long long)ev);
+    atomicMin(&a.st->min_s, (unsigned long long)sv);
+    const long long rank = (long long)(old >> 32);
+    if (rank < a.cap) {
+      Elem el;
+      el.s = sv;
+      el.e_slot = (long long)((unsigned long long)ev | ((unsigned long long)a.slot << kSlotShift));
+      *(Elem*)(a.units + 2 * gb * a.cap + 2 * a.cap - 2 * (rank + 1)) = el;
     }
   }
 }
@@ -970,7 +972,7 @@ __global__ __launch_bounds__(THREADS) void k_scatter(Plan p) {
       }
     }
   }
-  if (out)
+  if (__ballot(out))
     put_outside<THREADS>(OutsideArgs{ts, te, n_tile, cd.slot, sd.bucket_begin, sd.bucket_begin + sd.nb - 1, g.min_s,
                                      p.slot_cap, range_units(g), g.s0, p.cursor, p.maxend, p.oversized + 1,
                                      p.stats + cd.seg, (uint2*)p.elems});
@@ -1036,9 +1038,8 @@ __global__ __launch_bounds__(THREADS) void k_scatter(Plan p) {
       // wave (lane 2k + i: bucket i of round k) instead of a dependent one per
       // bucket and round: the kernel is bound by these chains and by its waves
       // in flight as much as by its 24 B per record (large trace: 601 -> 567 us,
-      // 504 with 2048-record tiles, 5.9 TB/s; mid 73 -> 60; 256 devices with
-      // their streams 274 -> 213; the small trace 7.5 -> 5.9; put_outside has
-      // added 1-3 % since).
+      // 504 with 2048-record tiles, 6.0 TB/s; mid 73 -> 60; 256 devices with
+      // their streams 274 -> 213; the small trace 7.5 -> 5.9).
       int vb = 0;                     // bucket, window-relative
       unsigned int vn = 0, ve = 0;    // its records, and their largest end relative to the bucket
       unsigned int second = 0, done = 0;  // bit k: this lane's record of round k is in bucket 1 / has its rank already
