@@ -64,13 +64,14 @@ constexpr int kSmallChunks = 128;    // chunks of such a segment at most
 constexpr int kSmallRecords = 4096;  // records
 constexpr int kSmallBuckets = 64;    // buckets
 
-// Sampled start ranges (k_range): kRangeSample starts of each chunk, half from
-// its front and half from its back (records arrive roughly in time order), and
-// 1 / 2^kRangePad of what they span on either side. The range need not hold
-// every start: a record outside goes to its segment's first or last bucket, in
-// the 16 B form. Plans with a segment of more than kRangeChunks chunks read every
-// start.
-constexpr int kRangeSample = 2048;
+// Sampled start ranges (k_range): kRangeSample starts of each chunk, a third from
+// its front, a third from its back (records arrive roughly in time order) and the
+// others in 64 runs of 8 between them (chunks may hold several pieces of time), and
+// 1 / 2^kRangePad of what they span on either side, half of what lies between two
+// of the runs. The range need not hold every start: a record outside goes to its
+// segment's first or last bucket, in the 16 B form. Plans with a segment of more
+// than kRangeChunks chunks read every start.
+constexpr int kRangeSample = 1536;
 constexpr int kRangePad = 7;
 constexpr int kRangeChunks = 64;
 // in a count of components: a narrow segment's, of 16 B all the same, as the

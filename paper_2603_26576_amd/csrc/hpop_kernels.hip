@@ -585,9 +585,13 @@ __global__ __launch_bounds__(256) void k_stats_small(Plan p) {
 // scatter checks every start against the range (put_outside). A pass over all
 // starts reads 8 of the 24 B per record that the build's first half moves. With its reset and geometry
 // kernels it took 178 us of the large trace's 1370, 28 of the mid trace's 232,
-// 75 of the streams' 660 and 66 of 440 on a batch of 128 traces; this takes 13,
-// 9, 17 and 37. What bounds it is four dependent reads, so a wave takes a
-// quarter of a chunk's sample, not a chunk (mid: 11 us).
+// 75 of the streams' 660 and 66 of 440 on a batch of 128 traces; this takes 14,
+// 9, 18 and 38. What bounds it is four dependent reads, so a wave takes a
+// third of a chunk's sample, not a chunk (mid: 11 us). A third lies in runs of 8
+// starts across the chunk, as chunks need not be one piece of time: 256 resources
+// whose 200,000 new records come in three pieces, the last one in the middle,
+// take 475 us, and 1555 with samples of the chunk's two ends, where k_range takes
+// 1-2 us less; with 128 runs instead of 64 it takes 17, 9, 23 and 40.
 template <int THREADS>
 __global__ __launch_bounds__(THREADS) void k_range(Plan p, bool reset) {
   constexpr int NW = THREADS / 64, K = 8;
@@ -607,21 +611,30 @@ __global__ __launch_bounds__(THREADS) void k_range(Plan p, bool reset) {
   __syncthreads();
   unsigned long long mn = ULLONG_MAX, mx = 0;
   for (int j = 0; j < nch; ++j) all = all && s_count[j] <= kRangeSample;
-  // a wave per quarter of a chunk's sample, K loads in flight per lane
+  // a wave per third of a chunk's sample, K loads in flight per lane
   constexpr int kParts = kRangeSample / (64 * K);
   const int lane = threadIdx.x & 63;
   for (int u = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); u < nch * kParts; u += NW) {
-    const int j = u / kParts, i0 = (u % kParts) * 64 * K;
+    const int j = u / kParts, part = u % kParts;
     const int64_t* s = s_at[j];
     const long long n = s_count[j];
-    const int m = (int)min(n, (long long)kRangeSample);
-    if (i0 >= m) continue;
+    // runs of 8 starts, `hop` apart: the first and the last third of the sample,
+    // and short chunks, run on; the others spread over what lies between
+    long long at = 64ll * K * part, hop = 8;
+    if (n > kRangeSample) {
+      if (part == kParts - 1) {
+        at = n - 64 * K;
+      } else if (part) {
+        const long long runs = 8 * K * (kParts - 2);
+        hop = (n - 2 * 64 * K - 8) / runs;
+        at = 64 * K + hop / 2 + 8ll * K * (part - 1) * hop;
+      }
+    }
+    if (at >= n) continue;
+    const long long mine = at + (lane >> 3) * hop + (lane & 7);
     unsigned long long x[K];
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-      const int i = min(i0 + 64 * k + lane, m - 1);
-      x[k] = (unsigned long long)s[i < kRangeSample / 2 ? (long long)i : n - m + i];
-    }
+    for (int k = 0; k < K; ++k) x[k] = (unsigned long long)s[min(mine + 8 * k * hop, n - 1)];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
       if (x[k] < (unsigned long long)kTimeLimit) {  // other starts belong to invalid records
@@ -847,8 +860,9 @@ __global__ __launch_bounds__(THREADS) void k_scan(Plan p) {
 // record, and building again where a sample missed up to twice as long (256
 // resources of 200,000 records, one start apart: 717 us with every start read,
 // 1042 with a second build, 478 so). A tile that lies outside from end to end asks
-// for the build with exact offsets at once: with a third of those records outside,
-// the adds to the same few counters took the two builds to 4.8 ms, now 1.56. The
+// for the build with exact offsets at once: with a third of those records outside
+// (while only a chunk's two ends were sampled), the adds to the same few counters
+// took the two builds to 4.8 ms, 1.56 without them. The
 // branch here is the wave's and the code behind it each lane's: with a branch per
 // lane, or with wave operations or two paths behind it, the registers and compares
 // of the records above change, and the scatter, which hardly ever comes here, takes

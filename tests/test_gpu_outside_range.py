@@ -1,5 +1,5 @@
 """Records that start outside their segment's sampled range (the sample takes the
-ends of a chunk, these lie in its middle): before it and past it, near and
+ends of a chunk and short runs between them, these lie in its middle): before it and past it, near and
 far, few and many, short and over everything, in narrow and wide buckets, with
 one bucket per resource and with many, against the oracle at regions that cut
 through them."""
@@ -68,8 +68,9 @@ def test_outside(wide, where, count, long_ends):
     tr = trace(rng, 5001, 1 << (42 if wide else 29), where, count, long_ends)
     print("case: %s %d" % (where, count), flush=True)
     info = check(tr)
-    # the outside records alone take the 16 B form in narrow segments
-    assert info.n_wide_records >= (2 if not wide else tr.n_events // 2)
+    # the outside records alone take the 16 B form in narrow segments (of 90 in a row the sample sees some)
+    if wide or count < 90:
+        assert info.n_wide_records >= (2 if not wide else tr.n_events // 2)
 
 
 @pytest.mark.parametrize("where", ["before far", "past far", "both near"])
